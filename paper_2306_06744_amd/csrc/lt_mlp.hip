@@ -7,8 +7,10 @@
 // an MLP 320 -> 128 -> 64 -> 3 (ReLU, BF16 weights and activations, FP32
 // accumulation on the matrix cores) gives refine / keep / coarsen scores.
 // Below a softmax confidence threshold the element keeps the geometric flag
-// of Section 5.2.  Training runs on the device through the same GEMM kernel
-// (forward, backward, Adam on FP32 master weights).
+// of Section 5.2.  Training runs on the device in two launches per step: the
+// forward and backward pass of row tiles with the batch sums of the gradients
+// kept in registers, then their sum over the workgroups with Adam on the FP32
+// master weights.
 //
 // Also here: the isentropic vortex of Section 5.2 evaluated at the solution
 // points of a tree's leaves (z-extruded vortices superposed on the free
@@ -198,69 +200,388 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const bf16* __restrict__ A, int
   }
 }
 
-// Out[c][r] = In[r][c] (BF16 from FP32 or BF16 sources), R x Cols.
-template <class TIn>
-__global__ void k_transpose(const TIn* __restrict__ in, int64_t ldi, int R, int Cols,
-                            bf16* __restrict__ out, int64_t ldo) {
-  __shared__ float tile[32][33];
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
-  for (int j = ty; j < 32; j += 8) {
-    const int rr = r0 + j, cc = c0 + tx;
-    tile[j][tx] = (rr < R && cc < Cols) ? float(in[int64_t(rr) * ldi + cc]) : 0.f;
+// ------------------------------------------------------------------ training
+// One training step is k_mlp_train (forward, backward and the batch sums of
+// one group of row tiles per workgroup) and k_mlp_update (the sum over the
+// workgroups, then Adam).  The network is small (49475 parameters, 0.3 MFLOP
+// per row), so a step is bound by launches and by passes over its
+// intermediates, not by the matrix cores: run layer by layer it took 29
+// launches (GEMMs, transposes, masks, column sums with one lane per column),
+// 2.9 ms for a batch of 4096; in this form 34 us (kernels 24 + 10 us), 19 us
+// for 64 rows.  Tiles of 64 rows with every weight read from the cache took
+// 37 us: half as many workgroups, each waiting for the cache after each
+// barrier.
+constexpr int kTrRows = 32;      // rows of a tile
+constexpr int kTrS = 40;         // LDS row stride (BF16) of the [column][row] arrays
+constexpr int kTrS1 = 136;       // of the 128-wide activations
+constexpr int kTrS2 = 72;        // of the 64-wide ones
+constexpr int kTrThreads = 512;
+// Workgroups of a step: each holds its own partial gradients (0.2 MB), which
+// the update reads back: 128 of them take it 10 us, as long as a workgroup's
+// second tile (9 us), so past 128 workgroups nothing is gained.
+constexpr int64_t kTrGridMax = 128;
+
+typedef __bf16 bf16x8u __attribute__((ext_vector_type(8), aligned(2)));  // rows of the caller's X
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Where the parameters lie in the flat FP32 arrays, W1 b1 W2 b2 W3 b3.
+struct NetOff {
+  static constexpr int W1 = 0, b1 = 128 * 320, W2 = b1 + 128, b2 = W2 + 64 * 128, W3 = b2 + 64,
+                       b3 = W3 + 3 * 64, n = b3 + 3;
+};
+
+// Forward and backward of the mean softmax cross-entropy over the workgroup's
+// tiles of 32 rows; part[blockIdx.x][] receives the sums of the gradients over
+// those rows.  Eight waves: in the row-by-column products wave w takes row
+// tile w & 3 and half w >> 2 of the columns, so that a lane's ReLU masks stay
+// in its registers from the forward to the backward pass; in the weight
+// gradients (contractions over the rows) wave w takes output tile w of layer 1
+// and the sums stay in accumulators over all tiles.  Each activation and
+// back-propagated error is stored once per orientation that a later product
+// reads: [row][column] as the next layer's operand, [column][row] for the
+// weight gradients.  Activations, errors and weights enter the matrix cores
+// in BF16 and accumulate in FP32; bias gradients sum the FP32 errors.  Rows
+// past B hold a zero error.
+__global__ __launch_bounds__(kTrThreads) void k_mlp_train(const bf16* __restrict__ X,
+                                                          const int8_t* __restrict__ y, int64_t B,
+                                                          const bf16* __restrict__ W1g,
+                                                          const bf16* __restrict__ W2,
+                                                          const bf16* __restrict__ W3,
+                                                          const bf16* __restrict__ W2T,
+                                                          const float* __restrict__ P,
+                                                          float* __restrict__ part) {
+  constexpr int S = kTrS, S1 = kTrS1, S2 = kTrS2;
+  __shared__ __attribute__((aligned(16))) bf16 sXT[320 * S];
+  __shared__ __attribute__((aligned(16))) bf16 sH1[kTrRows * S1];
+  __shared__ __attribute__((aligned(16))) bf16 sH1T[128 * S];
+  __shared__ __attribute__((aligned(16))) bf16 sH2[kTrRows * S2];
+  __shared__ __attribute__((aligned(16))) bf16 sH2T[64 * S];
+  __shared__ __attribute__((aligned(16))) bf16 sD2[kTrRows * S2];
+  __shared__ __attribute__((aligned(16))) bf16 sD2T[64 * S];
+  __shared__ __attribute__((aligned(16))) bf16 sD1T[128 * S];
+  __shared__ __attribute__((aligned(16))) bf16 sD3[kTrRows * 8];  // three classes and zeros
+  __shared__ __attribute__((aligned(16))) bf16 sD3T[16 * S];      // three classes, zero rows
+  __shared__ __attribute__((aligned(16))) bf16 sW2[64 * S1];
+  __shared__ __attribute__((aligned(16))) bf16 sW2T[128 * S2];
+  __shared__ __attribute__((aligned(16))) bf16 sW3[16 * S2];  // three classes, zero rows
+  __shared__ float sZ[kTrRows][4];
+  __shared__ float sG[2][128 + 64];  // bias gradients per row tile
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4, lk = 8 * lg;
+  const int rt = w & 1, cq = w >> 1;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  for (int i = tid; i < 16 * S; i += kTrThreads) sD3T[i] = bf16(0.f);
+  // the upper layers' weights and the biases stay on the chip: read from the
+  // cache after each barrier, their latency was most of a tile's time
+  for (int i = tid; i < 64 * 16; i += kTrThreads) {
+    *reinterpret_cast<bf16x8*>(sW2 + (i >> 4) * S1 + (i & 15) * 8) = *reinterpret_cast<const bf16x8*>(W2 + i * 8);
+    *reinterpret_cast<bf16x8*>(sW2T + (i >> 3) * S2 + (i & 7) * 8) = *reinterpret_cast<const bf16x8*>(W2T + i * 8);
+  }
+  for (int i = tid; i < 16 * 64; i += kTrThreads) sW3[(i >> 6) * S2 + (i & 63)] = i < 3 * 64 ? W3[i] : bf16(0.f);
+  float bias1[2], bias2 = P[NetOff::b2 + 16 * cq + lr], bias3 = lr < 3 ? P[NetOff::b3 + lr] : 0.f;
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) bias1[ct] = P[NetOff::b1 + 32 * cq + 16 * ct + lr];
+  f32x4 g1[20], g2[4], g3 = zero;  // weight gradients of this wave's tiles
+#pragma unroll
+  for (int k = 0; k < 20; ++k) g1[k] = zero;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g2[k] = zero;
+  float gb1[2] = {0.f, 0.f}, gb2 = 0.f, gb3[3] = {0.f, 0.f, 0.f};
+  const int64_t ntiles = (B + kTrRows - 1) / kTrRows;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int64_t r0 = tile * kTrRows;
+    // layer 1's weights are read anew for each tile (from the cache): kept in
+    // registers across tiles they would push the accumulators to scratch
+    int64_t anew = 0;
+    asm volatile("" : "+s"(anew));
+    const bf16* W1 = W1g + anew;
+    const int label = tid < kTrRows && r0 + tid < B ? int(y[r0 + tid]) : 0;
+    // The operands of layer 1 are asked for before any is used: the rows for
+    // the [column][row] form, and the same rows as they lie in the caller's
+    // array with the weights' columns, in two halves of the depth (all of
+    // them at once would not fit the registers beside the accumulators).
+    bf16x8 wf[2][5], xf[5], xc[2][2];
+    const int64_t ra = r0 + 16 * rt + lr;
+    const bf16* xr = X + (ra < B ? ra : B - 1) * 320 + lk;
+    auto load_half = [&](int half) {
+#pragma unroll
+      for (int ks = 0; ks < 5; ++ks) {
+        xf[ks] = *reinterpret_cast<const bf16x8u*>(xr + 32 * (5 * half + ks));
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+          wf[ct][ks] = *reinterpret_cast<const bf16x8*>(W1 + (32 * cq + 16 * ct + lr) * 320 +
+                                                        32 * (5 * half + ks) + lk);
+      }
+    };
+    // by column: items of two rows and eight columns, 16 x 40 of them
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int i = tid + it * kTrThreads;
+      const int rp = i & 15, c = i >> 4;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t r = r0 + 2 * rp + h;
+        const bool in = c < 40 && r < B;
+        const bf16x8 x = *reinterpret_cast<const bf16x8u*>(X + (in ? r * 320 + c * 8 : 0));
+#pragma unroll
+        for (int t = 0; t < 8; ++t) xc[it][h][t] = in ? x[t] : bf16(0.f);
+      }
+    }
+    load_half(0);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int i = tid + it * kTrThreads;
+      const int rp = i & 15, c = i >> 4;
+      if (c < 40)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+          bf16x2 v;
+          v[0] = xc[it][0][t];
+          v[1] = xc[it][1][t];
+          *reinterpret_cast<bf16x2*>(sXT + (c * 8 + t) * S + 2 * rp) = v;
+        }
+    }
+    // layer 1
+    unsigned pos1 = 0, pos2 = 0;  // ReLU masks of the lane's values
+    {
+      f32x4 acc[2] = {zero, zero};
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        if (half) load_half(1);
+#pragma unroll
+        for (int ks = 0; ks < 5; ++ks)
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[ks], wf[ct][ks], acc[ct], 0, 0, 0);
+      }
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+        const int col = 32 * cq + 16 * ct + lr;
+        bf16x4 h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float v = acc[ct][q] + bias1[ct];
+          h[q] = bf16(v > 0.f ? v : 0.f);
+          if (float(h[q]) > 0.f) pos1 |= 1u << (4 * ct + q);
+          sH1[(16 * rt + 4 * lg + q) * S1 + col] = h[q];
+        }
+        *reinterpret_cast<bf16x4*>(sH1T + col * S + 16 * rt + 4 * lg) = h;
+      }
+    }
+    __syncthreads();
+    {  // layer 2
+      const int col = 16 * cq + lr;
+      f32x4 acc = zero;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(sH1 + (16 * rt + lr) * S1 + 32 * ks + lk);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(sW2 + col * S1 + 32 * ks + lk);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+      }
+      bf16x4 h;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = acc[q] + bias2;
+        h[q] = bf16(v > 0.f ? v : 0.f);
+        if (float(h[q]) > 0.f) pos2 |= 1u << q;
+        sH2[(16 * rt + 4 * lg + q) * S2 + col] = h[q];
+      }
+      *reinterpret_cast<bf16x4*>(sH2T + col * S + 16 * rt + 4 * lg) = h;
+    }
+    __syncthreads();
+    if (cq == 0) {  // logits
+      f32x4 acc = zero;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(sH2 + (16 * rt + lr) * S2 + 32 * ks + lk);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(sW3 + lr * S2 + 32 * ks + lk);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+      }
+      if (lr < 3)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sZ[16 * rt + 4 * lg + q][lr] = acc[q] + bias3;
+    }
+    __syncthreads();
+    if (tid < kTrRows) {  // softmax cross-entropy: (softmax(z) - onehot(y)) / B
+      const bool live = r0 + tid < B;
+      const float z0 = sZ[tid][0], z1 = sZ[tid][1], z2 = sZ[tid][2];
+      const float m = fmaxf(z0, fmaxf(z1, z2));
+      const float e0 = expf(z0 - m), e1 = expf(z1 - m), e2 = expf(z2 - m);
+      const float s = e0 + e1 + e2;
+      const int c = min(max(label, 0), 2);  // labels outside {0,1,2} clamp
+      const float p[3] = {e0 / s, e1 / s, e2 / s};
+      bf16x8 d;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) d[t] = bf16(0.f);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float v = live ? (p[k] - (k == c ? 1.f : 0.f)) / float(int(B)) : 0.f;
+        gb3[k] += v;
+        d[k] = bf16(v);
+        sD3T[k * S + tid] = d[k];
+      }
+      *reinterpret_cast<bf16x8*>(sD3 + tid * 8) = d;
+    }
+    __syncthreads();
+    {  // errors of layer 2: (D3 W3) where its activation is positive
+      bf16x8 a;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) a[t] = bf16(0.f);
+      if (lg == 0) a = *reinterpret_cast<const bf16x8*>(sD3 + (16 * rt + lr) * 8);
+      const int col = 16 * cq + lr;
+      bf16x8 b;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) b[t] = bf16(0.f);
+      if (lg == 0)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) b[t] = sW3[t * S2 + col];
+      const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, zero, 0, 0, 0);
+      bf16x4 h;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = (pos2 >> q) & 1u ? acc[q] : 0.f;
+        gb2 += v;
+        h[q] = bf16(v);
+        sD2[(16 * rt + 4 * lg + q) * S2 + col] = h[q];
+      }
+      *reinterpret_cast<bf16x4*>(sD2T + col * S + 16 * rt + 4 * lg) = h;
+    }
+    __syncthreads();
+    {  // errors of layer 1
+      f32x4 acc[2] = {zero, zero};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(sD2 + (16 * rt + lr) * S2 + 32 * ks + lk);
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+          const bf16x8 b = *reinterpret_cast<const bf16x8*>(sW2T + (32 * cq + 16 * ct + lr) * S2 + 32 * ks + lk);
+          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[ct], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+        bf16x4 h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float v = (pos1 >> (4 * ct + q)) & 1u ? acc[ct][q] : 0.f;
+          gb1[ct] += v;
+          h[q] = bf16(v);
+        }
+        *reinterpret_cast<bf16x4*>(sD1T + (32 * cq + 16 * ct + lr) * S + 16 * rt + 4 * lg) = h;
+      }
+    }
+    __syncthreads();
+    // weight gradients: sums over the tile's 32 rows, one matrix step each
+    {
+      const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(sD1T + (16 * w + lr) * S + lk);
+#pragma unroll
+      for (int kt = 0; kt < 20; ++kt) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(sXT + (16 * kt + lr) * S + lk);
+        g1[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b, g1[kt], 0, 0, 0);
+      }
+      const bf16x8 b2 = *reinterpret_cast<const bf16x8*>(sH1T + (16 * w + lr) * S + lk);
+#pragma unroll
+      for (int ht = 0; ht < 4; ++ht) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(sD2T + (16 * ht + lr) * S + lk);
+        g2[ht] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b2, g2[ht], 0, 0, 0);
+      }
+      if (w < 4) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(sD3T + lr * S + lk);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(sH2T + (16 * w + lr) * S + lk);
+        g3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, g3, 0, 0, 0);
+      }
+    }
+    __syncthreads();  // before the next tile overwrites the arrays
+  }
+  float* out = part + int64_t(blockIdx.x) * NetOff::n;
+#pragma unroll
+  for (int kt = 0; kt < 20; ++kt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[NetOff::W1 + (16 * w + 4 * lg + q) * 320 + 16 * kt + lr] = g1[kt][q];
+#pragma unroll
+  for (int ht = 0; ht < 4; ++ht)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[NetOff::W2 + (16 * ht + 4 * lg + q) * 128 + 16 * w + lr] = g2[ht][q];
+  if (w < 4 && lg == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) out[NetOff::W3 + q * 64 + 16 * w + lr] = g3[q];
+  // bias gradients: over a wave's lane groups, then over the row tiles
+#pragma unroll
+  for (int ct = 0; ct < 3; ++ct) {
+    float v = ct < 2 ? gb1[ct] : gb2;
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (lg == 0) sG[rt][ct < 2 ? 32 * cq + 16 * ct + lr : 128 + 16 * cq + lr] = v;
+  }
+  if (w == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      float v = gb3[k];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+      if (lane == 0) out[NetOff::b3 + k] = v;
+    }
   }
   __syncthreads();
-  for (int j = ty; j < 32; j += 8) {
-    const int cc = c0 + j, rr = r0 + tx;
-    if (cc < Cols && rr < R) out[int64_t(cc) * ldo + rr] = bf16(tile[tx][j]);
+  if (tid < 128 + 64) {
+    const float v = sG[0][tid] + sG[1][tid];
+    out[tid < 128 ? NetOff::b1 + tid : NetOff::b2 + tid - 128] = v;
   }
 }
 
-// Softmax cross-entropy over 3 classes: dZ = (softmax(Z) - onehot(y)) / B and
-// the per-row loss.
-__global__ void k_xent(const float* __restrict__ Z, const int8_t* __restrict__ y, int B,
-                       float* __restrict__ dZ, float* __restrict__ loss) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const float z0 = Z[3 * b], z1 = Z[3 * b + 1], z2 = Z[3 * b + 2];
-  const float m = fmaxf(z0, fmaxf(z1, z2));
-  const float e0 = expf(z0 - m), e1 = expf(z1 - m), e2 = expf(z2 - m);
-  const float s = e0 + e1 + e2;
-  const int c = min(max(int(y[b]), 0), 2);  // labels outside {0,1,2} clamp
-  const float p[3] = {e0 / s, e1 / s, e2 / s};
-  for (int k = 0; k < 3; ++k) dZ[3 * b + k] = (p[k] - (k == c ? 1.f : 0.f)) / float(B);
-  loss[b] = -logf(p[c]);
+// BF16 copies of parameter i: the row-major weights, and W2 by input too.
+__device__ inline void store_bf16(int i, float v, bf16* __restrict__ W1, bf16* __restrict__ W2,
+                                  bf16* __restrict__ W3, bf16* __restrict__ W2T) {
+  if (i < NetOff::b1) {
+    W1[i] = bf16(v);
+  } else if (i >= NetOff::W2 && i < NetOff::b2) {
+    const int j = i - NetOff::W2;
+    W2[j] = bf16(v);
+    W2T[(j & 127) * 64 + (j >> 7)] = bf16(v);
+  } else if (i >= NetOff::W3 && i < NetOff::b3) {
+    W3[i - NetOff::W3] = bf16(v);
+  }
 }
 
-// G[r][c] *= (H[r][c] > 0)  (ReLU derivative through the stored activation).
-__global__ void k_relu_mask(float* __restrict__ G, const bf16* __restrict__ H, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n && !(float(H[i]) > 0.f)) G[i] = 0.f;
+struct AdamArgs {
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// Gradient i = the sum of the workgroups' partial sums, in their order; with
+// STEP also one Adam step on the FP32 master parameter and its BF16 copies.
+// One lane per parameter, so that every partial row is read in whole lines.
+template <bool STEP>
+__global__ __launch_bounds__(256) void k_mlp_update(const float* __restrict__ part, int nparts,
+                                                    float* __restrict__ g, float* __restrict__ w,
+                                                    float* __restrict__ m1, float* __restrict__ m2,
+                                                    AdamArgs A, bf16* __restrict__ W1,
+                                                    bf16* __restrict__ W2, bf16* __restrict__ W3,
+                                                    bf16* __restrict__ W2T) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= NetOff::n) return;
+  float gi = 0.f;
+#pragma unroll 16
+  for (int b = 0; b < nparts; ++b) gi += part[int64_t(b) * NetOff::n + i];
+  g[i] = gi;
+  if constexpr (STEP) {
+    const float a = A.b1 * m1[i] + (1.f - A.b1) * gi;
+    const float b = A.b2 * m2[i] + (1.f - A.b2) * gi * gi;
+    m1[i] = a;
+    m2[i] = b;
+    const float wi = w[i] - A.lr * (a / A.c1) / (sqrtf(b / A.c2) + A.eps);
+    w[i] = wi;
+    store_bf16(i, wi, W1, W2, W3, W2T);
+  }
 }
 
-// Column sums of an R x Cols FP32 array (bias gradients).
-__global__ void k_colsum(const float* __restrict__ G, int R, int Cols, float* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= Cols) return;
-  float s = 0.f;
-  for (int r = 0; r < R; ++r) s += G[int64_t(r) * Cols + c];
-  out[c] = s;
-}
-
-// Adam on FP32 master parameters; refreshes the BF16 copy.
-__global__ void k_adam(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m1,
-                       float* __restrict__ m2, bf16* __restrict__ wb, int64_t n, float lr, float b1,
-                       float b2, float eps, float c1, float c2) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float a = b1 * m1[i] + (1.f - b1) * gi;
-  const float b = b2 * m2[i] + (1.f - b2) * gi * gi;
-  m1[i] = a;
-  m2[i] = b;
-  const float wi = w[i] - lr * (a / c1) / (sqrtf(b / c2) + eps);
-  w[i] = wi;
-  if (wb) wb[i] = bf16(wi);
+// BF16 copies of the master parameters (a new model).
+__global__ __launch_bounds__(256) void k_mlp_refresh(const float* __restrict__ w, bf16* __restrict__ W1,
+                                                     bf16* __restrict__ W2, bf16* __restrict__ W3,
+                                                     bf16* __restrict__ W2T) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < NetOff::n) store_bf16(i, w[i], W1, W2, W3, W2T);
 }
 
 // Modal-energy indicator: the density's nodal values become coefficients in
@@ -629,27 +950,26 @@ struct lt_mlp_s {
   static constexpr int kIn = 320, kH1 = 128, kH2 = 64, kOut = 3;
   int device = 0;
   lt::Alloc A;  // device allocator of every buffer below
-  // FP32 master parameters, BF16 copies (row-major [out][in]) and transposes
+  // FP32 master parameters, their BF16 copies (row-major [out][in]) and W2 [in][out]
   float* P = nullptr;   // W1 b1 W2 b2 W3 b3 (FP32, contiguous)
   float* G = nullptr;   // gradients, same layout
   float* M1 = nullptr;  // Adam moments
   float* M2 = nullptr;
   __bf16* W1 = nullptr; __bf16* W2 = nullptr; __bf16* W3 = nullptr;      // [out][in]
-  __bf16* W1T = nullptr; __bf16* W2T = nullptr; __bf16* W3T = nullptr;   // [in][out]
+  __bf16* W2T = nullptr;  // [in][out]
   double* T4 = nullptr;  // 4x4 modal matrix (p = 3)
   int64_t step = 0;
-  // scratch sized for `cap` rows
+  // inference scratch sized for `cap` rows
   int64_t cap = 0;
-  __bf16 *H1 = nullptr, *H2 = nullptr, *XT = nullptr, *H1T = nullptr, *H2T = nullptr;
-  __bf16 *D1T = nullptr, *D2T = nullptr, *D3T = nullptr, *D2b = nullptr, *D3b = nullptr;
-  float *Z3 = nullptr, *D1 = nullptr, *D2 = nullptr, *D3 = nullptr, *loss = nullptr;
+  __bf16 *H1 = nullptr, *H2 = nullptr;
+  // training: the workgroups' partial gradients
+  float* part = nullptr;
+  int64_t part_cap = 0;
   __bf16* X = nullptr;  // features for lt_flag_mlp
   int64_t xcap = 0;
 
-  static constexpr int64_t off_W1 = 0, off_b1 = off_W1 + int64_t(kH1) * kIn;
-  static constexpr int64_t off_W2 = off_b1 + kH1, off_b2 = off_W2 + int64_t(kH2) * kH1;
-  static constexpr int64_t off_W3 = off_b2 + kH2, off_b3 = off_W3 + int64_t(kOut) * kH2;
-  static constexpr int64_t nparam = off_b3 + kOut;
+  static constexpr int64_t off_b1 = lt::NetOff::b1, off_b2 = lt::NetOff::b2, off_b3 = lt::NetOff::b3;
+  static constexpr int64_t nparam = lt::NetOff::n;
 };
 
 namespace lt {
@@ -658,16 +978,14 @@ namespace {
 lt_status mlp_scratch(lt_mlp_s* m, int64_t B) {
   if (B <= m->cap) return LT_OK;
   auto fr = [m](void* p) { (void)dev_free(m->A, p); };
-  fr(m->H1); fr(m->H2); fr(m->XT); fr(m->H1T); fr(m->H2T); fr(m->D1T); fr(m->D2T); fr(m->D3T);
-  fr(m->D2b); fr(m->D3b); fr(m->Z3); fr(m->D1); fr(m->D2); fr(m->D3); fr(m->loss);
+  fr(m->H1);
+  fr(m->H2);
+  m->H1 = m->H2 = nullptr;
   const int64_t c = B + B / 4 + 64;
   hipError_t e = hipSuccess;
   auto al = [&](void** p, size_t bytes) { if (e == hipSuccess) e = dev_malloc(m->A, p, bytes); };
-  al((void**)&m->H1, c * 128 * 2); al((void**)&m->H2, c * 64 * 2); al((void**)&m->XT, c * 320 * 2);
-  al((void**)&m->H1T, c * 128 * 2); al((void**)&m->H2T, c * 64 * 2); al((void**)&m->D1T, c * 128 * 2);
-  al((void**)&m->D2T, c * 64 * 2); al((void**)&m->D3T, c * 3 * 2); al((void**)&m->D2b, c * 64 * 2);
-  al((void**)&m->D3b, c * 3 * 2); al((void**)&m->Z3, c * 3 * 4); al((void**)&m->D1, c * 128 * 4);
-  al((void**)&m->D2, c * 64 * 4); al((void**)&m->D3, c * 3 * 4); al((void**)&m->loss, c * 4);
+  al((void**)&m->H1, c * 128 * 2);
+  al((void**)&m->H2, c * 64 * 2);
   if (e != hipSuccess) {
     m->cap = 0;
     return fail(LT_ERR_OOM, "MLP scratch allocation failed");
@@ -684,23 +1002,10 @@ hipError_t gemm(const __bf16* A, int64_t lda, const __bf16* Bt, int64_t ldb, int
   return hipGetLastError();
 }
 
-template <class TIn>
-hipError_t transpose(const TIn* in, int64_t ldi, int R, int Cols, __bf16* out, int64_t ldo,
-                     hipStream_t s) {
-  dim3 grid(nblk(Cols, 32), nblk(R, 32));
-  k_transpose<TIn><<<grid, 256, 0, s>>>(in, ldi, R, Cols, out, ldo);
-  return hipGetLastError();
-}
-
-// BF16 copies and transposes of the weights from the FP32 masters.
+// BF16 copies of the weights from the FP32 masters.
 lt_status mlp_refresh(lt_mlp_s* m, hipStream_t s) {
-  const float* P = m->P;
-  hipError_t e = transpose(P + lt_mlp_s::off_W1, 320, 128, 320, m->W1T, 128, s);
-  if (e == hipSuccess) e = transpose(P + lt_mlp_s::off_W2, 128, 64, 128, m->W2T, 64, s);
-  if (e == hipSuccess) e = transpose(P + lt_mlp_s::off_W3, 64, 3, 64, m->W3T, 3, s);
-  if (e == hipSuccess) e = transpose(m->W1T, 128, 320, 128, m->W1, 320, s);
-  if (e == hipSuccess) e = transpose(m->W2T, 64, 128, 64, m->W2, 128, s);
-  if (e == hipSuccess) e = transpose(m->W3T, 3, 64, 3, m->W3, 64, s);
+  k_mlp_refresh<<<nblk(NetOff::n, 256), 256, 0, s>>>(m->P, m->W1, m->W2, m->W3, m->W2T);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LT_ERR_HIP, std::string("MLP refresh: ") + hipGetErrorString(e));
   return LT_OK;
 }
@@ -717,35 +1022,21 @@ lt_status mlp_forward(lt_mlp_s* m, const __bf16* X, int64_t B, float* Z3, hipStr
   return LT_OK;
 }
 
-// Forward + backward on one mini-batch; gradients (FP32) in m->G.
-lt_status mlp_backward(lt_mlp_s* m, const __bf16* X, const int8_t* y, int64_t B, hipStream_t s) {
-  LT_TRY_STATUS(mlp_scratch(m, B));
-  LT_TRY_STATUS(mlp_forward(m, X, B, m->Z3, s));
-  float* G = m->G;
-  const int b = int(B);
-  k_xent<<<nblk(B, 256), 256, 0, s>>>(m->Z3, y, b, m->D3, m->loss);
-  hipError_t e = hipGetLastError();
-  // layer 3: gW3 = D3^T H2, gb3 = colsum D3, D2 = (D3 W3) * [H2 > 0]
-  if (e == hipSuccess) e = transpose(m->D3, 3, b, 3, m->D3T, b, s);
-  if (e == hipSuccess) e = transpose(m->H2, 64, b, 64, m->H2T, b, s);
-  if (e == hipSuccess) e = gemm(m->D3T, b, m->H2T, b, 3, 64, b, nullptr, 0, G + lt_mlp_s::off_W3, 64, nullptr, 0, s);
-  if (e == hipSuccess) { k_colsum<<<1, 64, 0, s>>>(m->D3, b, 3, G + lt_mlp_s::off_b3); e = hipGetLastError(); }
-  if (e == hipSuccess) e = transpose(m->D3T, b, 3, b, m->D3b, 3, s);
-  if (e == hipSuccess) e = gemm(m->D3b, 3, m->W3T, 3, b, 64, 3, nullptr, 0, m->D2, 64, nullptr, 0, s);
-  if (e == hipSuccess) { k_relu_mask<<<nblk(B * 64, 256), 256, 0, s>>>(m->D2, m->H2, B * 64); e = hipGetLastError(); }
-  // layer 2: gW2 = D2^T H1, gb2, D1 = (D2 W2) * [H1 > 0]
-  if (e == hipSuccess) e = transpose(m->D2, 64, b, 64, m->D2T, b, s);
-  if (e == hipSuccess) e = transpose(m->H1, 128, b, 128, m->H1T, b, s);
-  if (e == hipSuccess) e = gemm(m->D2T, b, m->H1T, b, 64, 128, b, nullptr, 0, G + lt_mlp_s::off_W2, 128, nullptr, 0, s);
-  if (e == hipSuccess) { k_colsum<<<1, 64, 0, s>>>(m->D2, b, 64, G + lt_mlp_s::off_b2); e = hipGetLastError(); }
-  if (e == hipSuccess) e = transpose(m->D2T, b, 64, b, m->D2b, 64, s);
-  if (e == hipSuccess) e = gemm(m->D2b, 64, m->W2T, 64, b, 128, 64, nullptr, 0, m->D1, 128, nullptr, 0, s);
-  if (e == hipSuccess) { k_relu_mask<<<nblk(B * 128, 256), 256, 0, s>>>(m->D1, m->H1, B * 128); e = hipGetLastError(); }
-  // layer 1: gW1 = D1^T X, gb1
-  if (e == hipSuccess) e = transpose(m->D1, 128, b, 128, m->D1T, b, s);
-  if (e == hipSuccess) e = transpose(X, 320, b, 320, m->XT, b, s);
-  if (e == hipSuccess) e = gemm(m->D1T, b, m->XT, b, 128, 320, b, nullptr, 0, G + lt_mlp_s::off_W1, 320, nullptr, 0, s);
-  if (e == hipSuccess) { k_colsum<<<2, 64, 0, s>>>(m->D1, b, 128, G + lt_mlp_s::off_b1); e = hipGetLastError(); }
+// Forward + backward on one mini-batch; gradients (FP32) in m->G.  With adam
+// also one step on the parameters.
+lt_status mlp_backward(lt_mlp_s* m, const __bf16* X, const int8_t* y, int64_t B, const AdamArgs* adam,
+                       hipStream_t s) {
+  const int64_t grid = std::min<int64_t>((B + kTrRows - 1) / kTrRows, kTrGridMax);
+  LT_TRY_STATUS(grow(m->A, &m->part, &m->part_cap, grid * NetOff::n));
+  k_mlp_train<<<unsigned(grid), kTrThreads, 0, s>>>(X, y, B, m->W1, m->W2, m->W3, m->W2T, m->P, m->part);
+  const unsigned blocks = nblk(NetOff::n, 256);
+  if (adam)
+    k_mlp_update<true><<<blocks, 256, 0, s>>>(m->part, int(grid), m->G, m->P, m->M1, m->M2, *adam, m->W1,
+                                              m->W2, m->W3, m->W2T);
+  else
+    k_mlp_update<false><<<blocks, 256, 0, s>>>(m->part, int(grid), m->G, m->P, m->M1, m->M2, AdamArgs{},
+                                               m->W1, m->W2, m->W3, m->W2T);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LT_ERR_HIP, std::string("MLP backward: ") + hipGetErrorString(e));
   return LT_OK;
 }
@@ -794,7 +1085,7 @@ lt_status lt_mlp_create(const float* params, lt_mlp* out) {
   auto al = [&](void** p, size_t bytes) { if (e == hipSuccess) e = dev_malloc(m->A, p, bytes); };
   al((void**)&m->P, np * 4); al((void**)&m->G, np * 4); al((void**)&m->M1, np * 4); al((void**)&m->M2, np * 4);
   al((void**)&m->W1, 128 * 320 * 2); al((void**)&m->W2, 64 * 128 * 2); al((void**)&m->W3, 3 * 64 * 2);
-  al((void**)&m->W1T, 128 * 320 * 2); al((void**)&m->W2T, 64 * 128 * 2); al((void**)&m->W3T, 3 * 64 * 2);
+  al((void**)&m->W2T, 64 * 128 * 2);
   al((void**)&m->T4, 16 * 8);
   if (e == hipSuccess) e = hipMemcpy(m->P, params, np * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(m->M1, 0, np * 4);
@@ -843,20 +1134,18 @@ lt_status lt_mlp_features(lt_mlp m, const double* u, int64_t ld, int nvar, const
 
 lt_status lt_mlp_grads(lt_mlp m, const void* X, const int8_t* labels, int64_t B, void* stream) {
   if (!m || !X || !labels || B < 1 || B > (int64_t(1) << 21)) return fail(LT_ERR_ARG, "batch size must be in [1, 2^21]");
-  return mlp_backward(m, static_cast<const __bf16*>(X), labels, B, static_cast<hipStream_t>(stream));
+  return mlp_backward(m, static_cast<const __bf16*>(X), labels, B, nullptr, static_cast<hipStream_t>(stream));
 }
 
 lt_status lt_mlp_train_step(lt_mlp m, const void* X, const int8_t* labels, int64_t B, float lr,
                             void* stream) {
-  LT_TRY_STATUS(lt_mlp_grads(m, X, labels, B, stream));
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  m->step++;
+  if (!m || !X || !labels || B < 1 || B > (int64_t(1) << 21)) return fail(LT_ERR_ARG, "batch size must be in [1, 2^21]");
   const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - std::pow(b1, float(m->step)), c2 = 1.f - std::pow(b2, float(m->step));
-  k_adam<<<nblk(lt_mlp_s::nparam, 256), 256, 0, s>>>(m->P, m->G, m->M1, m->M2, nullptr,
-                                                     lt_mlp_s::nparam, lr, b1, b2, 1e-8f, c1, c2);
-  if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "adam launch");
-  return mlp_refresh(m, s);
+  const float step = float(m->step + 1);
+  const AdamArgs adam{lr, b1, b2, 1e-8f, 1.f - std::pow(b1, step), 1.f - std::pow(b2, step)};
+  LT_TRY_STATUS(mlp_backward(m, static_cast<const __bf16*>(X), labels, B, &adam, static_cast<hipStream_t>(stream)));
+  m->step++;
+  return LT_OK;
 }
 
 lt_status lt_mlp_infer(lt_mlp m, const void* X, int64_t n, float* logits, void* stream) {
@@ -944,9 +1233,7 @@ lt_status lt_flag_modal(lt_tree t, int p, const double* u, int64_t ld, double ta
 void lt_mlp_destroy(lt_mlp m) {
   if (!m) return;
   (void)hipDeviceSynchronize();
-  void* ptrs[] = {m->P, m->G, m->M1, m->M2, m->W1, m->W2, m->W3, m->W1T, m->W2T, m->W3T, m->T4,
-                  m->H1, m->H2, m->XT, m->H1T, m->H2T, m->D1T, m->D2T, m->D3T, m->D2b, m->D3b,
-                  m->Z3, m->D1, m->D2, m->D3, m->loss, m->X};
+  void* ptrs[] = {m->P, m->G, m->M1, m->M2, m->W1, m->W2, m->W3, m->W2T, m->T4, m->H1, m->H2, m->part, m->X};
   for (void* p : ptrs) (void)dev_free(m->A, p);
   delete m;
 }

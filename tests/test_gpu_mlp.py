@@ -149,3 +149,45 @@ def test_training_lowers_loss_and_flags_are_valid():
     low = conf.cpu().numpy() < 0.9
     assert np.array_equal(f[low], p[low])       # fallback below the threshold
     print("disagreement", (f != p).mean(), "fallback", low.mean(), flush=True)
+
+
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 128 * 64 + 1])
+def test_training_step_at_tile_edges(B):
+    """The training kernels at the edges of their 64-row tiles and of the 128
+    workgroups that share them (a workgroup with a second tile).
+
+    Gradients against the FP64 network with the same BF16 storage: three
+    roundings of the back-propagated errors to BF16 (2^-9 each), <= 1e-2
+    relative L2 per tensor.  Rows that start off a 16-byte boundary give the
+    same bits.  One Adam step from zero moments is w - lr g / (|g| + eps): the
+    FP32 steps of that expression round to 4 ulps of the update and one of w."""
+    import torch
+    import paper_2306_06744_amd as lt
+    params = synth.mlp_init(7)
+    g = np.random.default_rng(B)
+    X = g.uniform(-1.0, 1.5, size=(B, 320))
+    y = g.integers(0, 3, size=B).astype(np.int8)
+    Xb = torch.from_numpy(X).to(torch.bfloat16).cuda()
+    yd = torch.from_numpy(y).cuda()
+    m = lt.MLP(params)
+    m.grads(Xb, yd)
+    _, G = m.params(grads=True)
+    off = torch.empty(B * 320 + 1, dtype=torch.bfloat16, device="cuda")[1:].view(B, 320)
+    off.copy_(Xb)
+    m.grads(off, yd)
+    assert np.array_equal(G, m.params(grads=True)[1])
+    W1, b1, W2, b2, W3, b3 = synth.mlp_split(params.astype(np.float64))
+    w = (bf16(X), y.astype(np.int64), bf16(W1).T, b1, bf16(W2).T, b2, bf16(W3).T, b3)
+    _, exp = ref.loss_and_grads(*w, store=bf16)
+    for name, a, b in zip(("W1", "b1", "W2", "b2", "W3", "b3"), synth.mlp_split(G.astype(np.float64)), exp):
+        rel = np.linalg.norm(a - (b.T if b.ndim == 2 else b)) / np.linalg.norm(b)
+        print(B, name, rel, flush=True)
+        assert rel <= 1e-2, name
+    lr = 2e-3
+    m.train_step(Xb, yd, lr)
+    got, G2 = m.params(grads=True)
+    assert np.array_equal(G, G2)
+    G = G.astype(np.float64)
+    step = lr * G / (np.abs(G) + 1e-8)
+    ulp = 2.0 ** -23
+    assert np.all(np.abs(got - (params - step)) <= ulp * (4 * np.abs(step) + np.abs(params) + lr))
