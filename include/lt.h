@@ -315,8 +315,9 @@ lt_status lt_get_tuning(lt_tree t, lt_tune* tune);
  * u[(v * n_p + i) * ld + e] as lt_transfer; gamma > 1; the tree's cube has
  * physical edge `length`.  All three need lt_connect on the current leaves
  * (LT_ERR_STATE otherwise), a tree periodic on every axis and a single mesh
- * (LT_ERR_ARG), p 1..3 in 3D and 1..7 in 2D.  Asynchronous; the tree keeps a
- * face buffer of 2 dim (dim+2) (p+1)^(dim-1) doubles per leaf.
+ * (LT_ERR_ARG), p 1..3 in 3D and 1..7 in 2D.  Asynchronous; the tree keeps the
+ * fluxes of its hanging faces ((2^(dim-1) + 1) (dim+2) (p+1)^(dim-1) doubles a
+ * row) and, for lt_fr_rk3, one state array ((dim+2) (p+1)^dim doubles a leaf).
  * ------------------------------------------------------------------------ */
 
 /* Common normal fluxes at every element face (Section 4.3, Algorithm

@@ -3,10 +3,10 @@
 // three-stage Runge-Kutta step (Section 2.1, eq. rk3), for the Euler
 // equations on Gauss-Legendre solution points.
 //
-// A face buffer FB[f][v][q][ld] (face f = 2 axis + side, variable v, face
-// point q with the tangential axes in increasing order, the lower fastest,
-// element fastest) first holds the solution's traces, then -- overwritten in
-// place -- the common normal fluxes:
+// Common fluxes alone (lt_fr_face_flux): a face buffer FB[f][v][q][ld] (face
+// f = 2 axis + side, variable v, face point q with the tangential axes in
+// increasing order, the lower fastest, element fastest) first holds the
+// solution's traces, then -- overwritten in place -- the common normal fluxes:
 //   k_fr_trace   one lane per element: u -> traces of every face;
 //   k_fr_conf    one lane per element and axis: a conforming face pair is
 //                owned by its low-side element, which reads both traces and
@@ -18,15 +18,12 @@
 //                slot, and the coarse slot's L2 projection of the mortar
 //                fluxes (the half-interval projection factors P_b) summed
 //                over the mortars through LDS.
-// Every slot is read and written by exactly one owner: no atomics, and the
-// result is the same on every run (the paper accumulates the coarse side with
-// atomic additions).
-//   k_fr_volume  a lane holds one x-line of points of one element (lanes
-//                of a wave part = consecutive elements, so every load of a
-//                point row is one contiguous run); the x derivative in
-//                registers, the y and z derivatives through LDS, the Radau
-//                corrections from the face buffer, and the stage combination
-//                out = c0 u0 + c1 u + c2 dt R fused in.
+// Residual and Runge-Kutta stages: no face buffer; k_fr_stage forms traces and
+// fluxes where it uses them, and only the hanging faces' fluxes are stored
+// (k_fr_rows, k_fr_hang; see there).
+// Every slot is read and written by exactly one owner: no atomics on values,
+// and the result is the same on every run (the paper accumulates the coarse
+// side with atomic additions).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -458,203 +455,460 @@ __global__ __launch_bounds__(256) void k_fr_mortar(const int32_t* __restrict__ h
   }
 }
 
-// Entry r of N compile-time values, r uniform across the wave, as
-// sum_k [k == r] row[k] (exact: the other terms are zeros), so that no array
-// is indexed at run time (which would place it in scratch memory).
-template <int N>
-__device__ inline double row_at(const double* row, int r) {
-  double x = 0.0;
+// ------------------------------------------------- residual and RK3 stages
+// A stage reads the state and writes the next one in a single kernel,
+// k_fr_stage: a lane takes one line of points of one element along one axis
+// after the other, and at both ends of its line forms the neighbour's trace
+// from the neighbour's own line.  Nothing is stored per face, except for the
+// few hanging faces (k_fr_rows once per call, k_fr_hang before each stage).
+//
+// Per p = 3 element in 3D a stage moves 2560 B of state in and out (2560 more
+// where the step's first state enters) and reads the neighbours' lines, six
+// elements' worth, through the caches: in Morton order nearly all of them are
+// being worked on nearby.  The form with a face buffer (traces written, both
+// traces read and the fluxes written by face, the fluxes read by element)
+// moved 23 to 25.6 KB per element and stage.
+//
+// Hanging faces: HB[row][S + 1][nvar][nfp] holds a row's S fine fluxes and
+// its coarse one; code[e * 2 dim + f] = row * (S + 1) + slot where bit f of
+// hm[e] is set.
+
+// Pointwise quantities of a state along axis a.
+template <int DIM>
+struct Point {
+  double ua, p, c;
+};
+
+template <int DIM>
+__device__ inline Point<DIM> point_of(const double* U, int a, double gamma) {
+  const double ir = 1.0 / U[0];
+  double kin = 0.0;
 #pragma unroll
-  for (int k = 0; k < N; ++k) x += (r == k ? 1.0 : 0.0) * row[k];
-  return x;
+  for (int b = 0; b < DIM; ++b) kin += U[1 + b] * U[1 + b];
+  Point<DIM> r;
+  r.p = (gamma - 1.0) * (U[DIM + 1] - 0.5 * kin * ir);
+  r.ua = U[1 + a] * ir;
+  r.c = sqrt(gamma * r.p * ir);
+  return r;
 }
 
-// Volume part and stage combination.  A lane holds one x-line of N points
-// of one element; a workgroup holds every line of EB = 64 / H elements
-// (lane = element within each of the H parts of a wave, so that every load
-// of a point row is one contiguous run).  Wave w holds lines w + (NL / H) h,
-// h = 0..H-1 (NL = N^2 lines in 3D, N in 2D); NL / H is a multiple of N so
-// that the line's y is uniform across the wave.  Each point's inverse density
-// and pressure are formed once per pass; the variables are taken one at a
-// time (a loop that is not unrolled, to bound the code and the registers),
-// with component v of the flux along axis a written as
-//   F_a[v] = (U[v] + [v is energy] p) m_a / rho + [v is momentum a] p
-// (the mass flux m_a for v = 0).  U[v] is formed as sum_k [k == v] U[k]
-// (exact: the other terms are zeros), so that no register array is indexed
-// by the loop variable (that would move it to scratch memory).  The x
-// derivative stays in registers; the y and z fluxes go through LDS for the
-// derivatives across lines.  The 1D operators are literal constants.
-template <int DIM, int N, int H>
-__global__ __launch_bounds__(64 * (DIM == 3 ? N * N : N) / H) void k_fr_volume(
-    KeyGeom g, const uint64_t* __restrict__ keys, int64_t n, double length, double gamma,
-    const double* __restrict__ uin, int64_t ld, const double* __restrict__ fb, int64_t ldf,
-    const double* __restrict__ u0, double c0, double c1, double c2, double* __restrict__ out,
-    int64_t ldo) {
-  constexpr int NL = DIM == 3 ? N * N : N;  // x-lines
+// Rusanov flux, UL on the low side (one reciprocal and one root per side).
+template <int DIM>
+__device__ inline void rusanov1(const double* UL, const double* UR, int a, double gamma, double* F) {
+  const Point<DIM> L = point_of<DIM>(UL, a, gamma), R = point_of<DIM>(UR, a, gamma);
+  const double lam = fmax(fabs(L.ua) + L.c, fabs(R.ua) + R.c);
+#pragma unroll
+  for (int v = 0; v < DIM + 2; ++v) {
+    double fl = v == DIM + 1 ? (UL[v] + L.p) * L.ua : UL[v] * L.ua;
+    double fr = v == DIM + 1 ? (UR[v] + R.p) * R.ua : UR[v] * R.ua;
+    if (v == 1 + a) {
+      fl += L.p;
+      fr += R.p;
+    }
+    F[v] = 0.5 * (fl + fr) - 0.5 * lam * (UR[v] - UL[v]);
+  }
+}
+
+// First point of line q along axis a, and the distance between its points:
+// q counts the points of a face normal to a (face_point's order).
+template <int DIM, int N>
+__device__ inline int line_base(int a, int q) {
+  if (a == 0) return q * N;
+  if (DIM == 2) return q;
+  return a == 1 ? q % N + (q / N) * (N * N) : q;
+}
+constexpr int line_stride(int n, int a) { return a == 0 ? 1 : (a == 1 ? n : n * n); }
+
+// The hanging faces' codes and mask bits (hm zeroed before), once per call.
+__global__ __launch_bounds__(256) void k_fr_rows(const int32_t* __restrict__ hang, int64_t nrows, int dim,
+                                                 int64_t n, int32_t* __restrict__ code,
+                                                 uint32_t* __restrict__ hm, unsigned* err) {
+  const int S = 1 << (dim - 1), nf = 2 * dim, W = 2 + S;
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t r = t / (S + 1);
+  const int slot = int(t % (S + 1));
+  if (r >= nrows) return;
+  const int64_t e = slot == S ? hang[r * W] : hang[r * W + 2 + slot];
+  const int fc = hang[r * W + 1];
+  if (e < 0 || e >= n || fc < 0 || fc >= nf) {
+    atomicOr(err, ERR_FR_ROW);
+    return;
+  }
+  const int f = slot == S ? fc : fc ^ 1;
+  code[e * nf + f] = int32_t(t);
+  atomicOr(&hm[e >> 2], 1u << (8 * int(e & 3) + f));  // one byte per leaf
+}
+
+// Fluxes of the hanging faces from the state: one wave per row, lane = (slot
+// s, face point q), with the traces formed from the elements' lines.
+template <int DIM, int N>
+__global__ __launch_bounds__(256) void k_fr_hang(const int32_t* __restrict__ hang, int64_t nrows,
+                                                 int64_t n, const double* __restrict__ tab, double gamma,
+                                                 const double* __restrict__ u, int64_t ld,
+                                                 double* __restrict__ HB) {
+  constexpr int NFP = DIM == 3 ? N * N : N;
+  constexpr int NP = NFP * N;
+  constexpr int S = 1 << (DIM - 1);
+  constexpr int NV = DIM + 2;
+  constexpr int W = 2 + S;
+  static_assert(S * NFP <= 64, "one wave per row");
+  __shared__ double Fm[4][S * NFP][NV];  // mortar fluxes of the wave's row
+  __shared__ double Uc[4][NFP][NV];      // coarse trace
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t r = int64_t(blockIdx.x) * (blockDim.x >> 6) + wv;
+  const int s = lane / NFP, q = lane % NFP;
+  int64_t c = 0, k = 0;
+  int f = 0;
+  if (r < nrows) {
+    c = hang[r * W];
+    f = hang[r * W + 1];
+    if (s < S) k = hang[r * W + 2 + s];
+  }
+  // rows with a bad entry were reported when their codes were written
+  const bool go = r < nrows && s < S && c >= 0 && c < n && f >= 0 && f < 2 * DIM && k >= 0 && k < n;
+  const int a = f >> 1, side = f & 1;
+  // end values of element e's line through face point q, at its side `hi`
+  auto trace = [&](int64_t e, bool hi, double* T) {
+    const double* l = tab + (hi ? FrTab::lR(N) : FrTab::lL(N));
+    const int b0 = a == 0 ? line_base<DIM, N>(0, q) : (a == 1 ? line_base<DIM, N>(1, q) : line_base<DIM, N>(2, q));
+    const int st = line_stride(N, a);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double x[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) x[i] = u[(int64_t(v) * NP + b0 + i * st) * ld + e];
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < N; ++i) t += l[i] * x[i];
+      T[v] = t;
+    }
+  };
+  double Uk[NV];
+  if (go) {
+    trace(k, side == 0, Uk);
+    if (s == 0) {
+      double T[NV];
+      trace(c, side == 1, T);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Uc[wv][q][v] = T[v];
+    }
+  }
+  __syncthreads();
+  // tangential child bits of mortar s and the face point's tangential indices
+  const int b0 = s & 1, b1 = (s >> 1) & 1;
+  const int q0 = q % N, q1 = q / N;
+  double* out = HB + r * (S + 1) * NV * NFP;
+  if (go) {
+    const double* A0 = tab + FrTab::A(N, b0);
+    const double* A1 = tab + FrTab::A(N, b1);
+    double Um[NV], F[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double acc = 0.0;
+      if (DIM == 2) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc += A0[q0 * N + i] * Uc[wv][i][v];
+      } else {
+#pragma unroll
+        for (int i1 = 0; i1 < N; ++i1) {
+          double t = 0.0;
+#pragma unroll
+          for (int i0 = 0; i0 < N; ++i0) t += A0[q0 * N + i0] * Uc[wv][i1 * N + i0][v];
+          acc += A1[q1 * N + i1] * t;
+        }
+      }
+      Um[v] = acc;
+    }
+    double L[NV], H[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      L[v] = side ? Um[v] : Uk[v];
+      H[v] = side ? Uk[v] : Um[v];
+    }
+    if (a == 0)
+      rusanov1<DIM>(L, H, 0, gamma, F);
+    else if (DIM == 2 || a == 1)
+      rusanov1<DIM>(L, H, 1, gamma, F);
+    else
+      rusanov1<DIM>(L, H, DIM - 1, gamma, F);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      out[(s * NV + v) * NFP + q] = F[v];
+      Fm[wv][lane][v] = F[v];
+    }
+  }
+  __syncthreads();
+  // coarse face: sum over the mortars of (P_b1 x P_b0) applied to their fluxes
+  if (go && s == 0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double acc = 0.0;
+#pragma unroll
+      for (int m = 0; m < S; ++m) {
+        const double* P0 = tab + FrTab::P(N, m & 1);
+        const double* P1 = tab + FrTab::P(N, (m >> 1) & 1);
+        if (DIM == 2) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) acc += P0[q0 * N + i] * Fm[wv][m * NFP + i][v];
+        } else {
+#pragma unroll
+          for (int i1 = 0; i1 < N; ++i1) {
+            double t = 0.0;
+#pragma unroll
+            for (int i0 = 0; i0 < N; ++i0) t += P0[q0 * N + i0] * Fm[wv][m * NFP + i1 * N + i0][v];
+            acc += P1[q1 * N + i1] * t;
+          }
+        }
+      }
+      out[(S * NV + v) * NFP + q] = acc;
+    }
+  }
+}
+
+// Elements of a workgroup.  3D keeps the state and the residual sums of its
+// elements in LDS (80 KB at p = 3 with 16 elements, so that two workgroups
+// share a compute unit), 2D the sums alone.  Few elements in flight also keep
+// a neighbour's lines in the L2 (4 MB per XCD) until they are wanted.
+constexpr bool stage_lds(int dim) { return dim == 3; }
+constexpr int stage_elems(int dim, int n) {
+  return dim == 3 ? (n >= 3 ? 16 : 64) : (n >= 7 ? 32 : 64);
+}
+
+// Rows of one variable: base address and length in bytes.  A lane that wants
+// nothing from a row passes kNoLoad, which lies past any length: the load
+// returns zero and reaches no memory, without a branch around it.
+constexpr uint32_t kNoLoad = 0xFFFFFFF0u;
+__device__ inline __amdgpu_buffer_rsrc_t var_rsrc(const double* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0, int(bytes), 0x00020000);
+}
+typedef unsigned int u32x2 __attribute__((__vector_size__(2 * sizeof(unsigned int))));
+constexpr int kStream = 2;  // cache-policy bit of the buffer access: streaming
+
+// One stage out = c0 u0 + c1 u + c2 R(u) for EB elements per workgroup: lane =
+// element, wave (or wave part) = line.  Axis by axis (z, y, x) the lane takes
+// its line, forms the line's end values, the common fluxes and the corrected
+// flux derivative along it, and the axes' sums pass from one axis' lines to
+// the next through LDS; in 3D the state does too, so that it is read once.  A
+// neighbour's end value comes from its lane of the same wave where the
+// neighbour is one of the wave's elements (consecutive elements are a block in
+// space), else the lane sums the neighbour's own line; those lines are asked
+// for at the start, for every axis.  Every lane holds a whole line, so the 1D
+// operators are literal constants.
+//
+// Bound: bytes from beyond the L2.  At 1.90M p = 3 elements in 3D a step of
+// three stages takes 16.8 ms (35.2 ms with the face buffer, 22.2
+// with every neighbour's line loaded and the state read again for each axis;
+// without the lines outside the wave it would take 10.0, of which 3.4 is the
+// issue of their loads).  p = 2: 17.2 -> 8.9 ms, p = 1: 6.2 -> 2.0 ms; 2D p = 4,
+// 40 006 leaves, one residual: 71 -> 42 us.
+// WIDE: 64-bit addresses, for arrays whose rows of one variable pass 2^32
+// bytes.
+template <int DIM, int N, bool WIDE>
+__global__ __launch_bounds__(stage_elems(DIM, N) * (DIM == 3 ? N * N : N), 2) void k_fr_stage(
+    KeyGeom g, const uint64_t* __restrict__ keys, const int32_t* __restrict__ nbr,
+    const uint8_t* __restrict__ hm, const int32_t* __restrict__ code, const double* __restrict__ HB,
+    int64_t n, double length, double gamma, const double* __restrict__ u, int64_t ld,
+    const double* u0, int64_t ld0, double c0, double c1, double c2, double* out, int64_t ldo,
+    unsigned* err) {
+  constexpr int NL = DIM == 3 ? N * N : N;  // lines along each axis, points of a face
   constexpr int NP = NL * N;
   constexpr int NV = DIM + 2;
-  constexpr int NFP = NL;  // points of a face
-  constexpr int EB = 64 / H;  // elements of a workgroup
-  static_assert(NL % H == 0 && (NL / H) % N == 0, "the parts of a wave must share y");
+  constexpr int EB = stage_elems(DIM, N);
   constexpr Ops1D<N> O = ops_1d<N>();
   const double* D = O.t + FrTab::kD;
   const double* lL = O.t + FrTab::lL(N);
   const double* lR = O.t + FrTab::lR(N);
   const double* dgL = O.t + FrTab::dgL(N);
   const double* dgR = O.t + FrTab::dgR(N);
-  __shared__ double Hy[NP][EB];
-  __shared__ double Hz[DIM == 3 ? NP : 1][EB];
+  constexpr bool kLds = stage_lds(DIM);
+  __shared__ double Rs[NV * NP * EB];
+  __shared__ double Us[kLds ? NV * NP * EB : 1];
   const int lane = threadIdx.x & 63;
-  const int el = lane % EB;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l = w + (NL / H) * (lane / EB);  // the lane's line
-  const int y = w % N;                       // uniform
-  const int z = l / N;                       // uniform when H = 1
-  const int64_t e0 = int64_t(blockIdx.x) * EB;
+  const int el = threadIdx.x % EB;
+  // the lane's line
+  const int q = EB == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / EB) : int(threadIdx.x / EB);
+  // contiguous runs of elements per XCD (workgroups are dealt round-robin), so
+  // that neighbouring lines are read into one L2
+  const int64_t nb = gridDim.x, bq = nb >> 3, br = nb & 7;
+  const int64_t bx = blockIdx.x & 7, bk = blockIdx.x >> 3;
+  const int64_t e0 = (bx * bq + (bx < br ? bx : br) + bk) * EB;
   const bool live = e0 + el < n;
-  // lanes past the last element read the last element's values and store nothing
-  const int64_t e = live ? e0 + el : n - 1;
+  const int64_t e = live ? e0 + el : n - 1;  // lanes past the end repeat the last element
+  int32_t nbe[2 * DIM];
+#pragma unroll
+  for (int f = 0; f < 2 * DIM; ++f) nbe[f] = nbr[e * (2 * DIM) + f];
+  const unsigned hmask = hm[e];
   const double gm1 = gamma - 1.0;
-  auto row = [&](auto* p, int64_t r, int64_t stride) { return p + (r * stride + e); };
-  double U[NV][N];
+  const double scale = -2.0 / ldexp(length, -key_depth(g, keys[e]));
+  const uint32_t bytes = uint32_t(NP * ld * 8);
+  // value of variable v at point row `row` (uniform) + lane's part: element j
+  // at point `base` of the lane's line
+  auto load = [&](int v, int row, int base, int64_t j, bool want) -> double {
+    if constexpr (WIDE) {
+      const double x = u[int64_t(v * NP + row + base) * ld + (want ? j : e)];
+      return want ? x : 0.0;
+    } else {
+      const uint32_t o = want ? uint32_t((uint32_t(base) * uint64_t(ld) + j) * 8) : kNoLoad;
+      return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                            var_rsrc(u + int64_t(v) * NP * ld, bytes), o,
+                                            uint32_t(row * ld * 8), 0));
+    }
+  };
+  // 16-element rows start on alternate halves of the banks; swapping point
+  // pairs by bit 2 spreads the lines of every axis over both halves
+  auto at = [&](int v, int pt) {
+    if (EB == 16) pt ^= (pt >> 2) & 1;
+    return (v * NP + pt) * EB + el;
+  };
+  // Hanging faces take their flux from HB; neighbours in the wave are
+  // exchanged, the others' lines are read: their end values, per axis.
+  bool xl[DIM], xr[DIM];
+  int sl[DIM], sr[DIM];
+  double zl[DIM][NV], zr[DIM][NV];
+  auto outside = [&](int a) {
+    const int base = line_base<DIM, N>(a, q);
+    const int st = line_stride(N, a);
+    const bool hl = (hmask >> (2 * a)) & 1u, hr = (hmask >> (2 * a + 1)) & 1u;
+    const int64_t nl = nbe[2 * a], nr = nbe[2 * a + 1];
+    const bool okl = nl >= 0 && nl < n, okr = nr >= 0 && nr < n;
+    if ((!hl && !okl) || (!hr && !okr)) atomicOr(err, ERR_INVALID_TREE);
+    const bool inl = nl >= e0 && nl < e0 + EB, inr = nr >= e0 && nr < e0 + EB;
+    xl[a] = !hl && okl && !inl;
+    xr[a] = !hr && okr && !inr;
+    sl[a] = (lane & ~(EB - 1)) + (inl ? int(nl - e0) : el);
+    sr[a] = (lane & ~(EB - 1)) + (inr ? int(nr - e0) : el);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      zl[a][v] = zr[a][v] = 0.0;
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        zl[a][v] += lR[k] * load(v, k * st, base, nl, xl[a]);
+        zr[a][v] += lL[k] * load(v, k * st, base, nr, xr[a]);
+      }
+    }
+  };
+  // asked for an axis ahead where the registers hold it
+  constexpr bool kAhead = DIM == 3 || N <= 4;
+  double U[NV][N], U0[kAhead ? NV : 1][N];
+  constexpr int kFirst = DIM - 1;
+#pragma unroll
+  for (int v = 0; v < (kAhead ? NV : 1); ++v)
+#pragma unroll
+    for (int k = 0; k < N; ++k) U0[v][k] = 0.0;
+  auto load_u0 = [&](int v, double* x) {
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      x[k] = __builtin_nontemporal_load(u0 + int64_t(v * NP + line_base<DIM, N>(0, q) + k) * ld0 + e);
+  };
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int i = 0; i < N; ++i) U[v][i] = *row(uin, int64_t(v) * NP + l * N + i, ld);
-  const double h = ldexp(length, -key_depth(g, keys[e]));
-  const double scale = -2.0 / h;
-  // the operators' rows at the line's y and z
-  double Dy[N], Dz[N];
+    for (int k = 0; k < N; ++k) U[v][k] = load(v, k * line_stride(N, kFirst), line_base<DIM, N>(kFirst, q), e, true);
+  outside(kFirst);
+  if constexpr (kLds)
 #pragma unroll
-  for (int k = 0; k < N; ++k) {
-    double c[N];
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int r = 0; r < N; ++r) c[r] = D[r * N + k];
-    Dy[k] = row_at<N>(c, y);
-    Dz[k] = row_at<N>(c, z);
-  }
-  const double gLy = row_at<N>(dgL, y), gRy = row_at<N>(dgR, y);
-  const double gLz = row_at<N>(dgL, z), gRz = row_at<N>(dgR, z);
-#pragma unroll 1
-  for (int v = 0; v < NV; ++v) {
-    // values derived from the state are not kept across passes
+      for (int k = 0; k < N; ++k)
+        Us[at(v, line_base<DIM, N>(kFirst, q) + k * line_stride(N, kFirst))] = U[v][k];
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
+  for (int a = DIM - 1; a >= 0; --a) {
+    const int base = line_base<DIM, N>(a, q);
+    const int st = line_stride(N, a);
+    const bool hl = (hmask >> (2 * a)) & 1u, hr = (hmask >> (2 * a + 1)) & 1u;
+    if (a != kFirst) {
+      if constexpr (!kLds)
 #pragma unroll
-      for (int i = 0; i < N; ++i) asm volatile("" : "+v"(U[k][i]));
-    double ir[N], pr[N];
+        for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      ir[i] = 1.0 / U[0][i];
-      double kin = 0.0;
+          for (int k = 0; k < N; ++k) U[v][k] = load(v, k * st, base, e, true);
+      __syncthreads();  // the sums (and the state) of the axis before
+      if constexpr (kLds)
 #pragma unroll
-      for (int b = 0; b < DIM; ++b) kin += U[1 + b][i] * U[1 + b][i];
-      pr[i] = gm1 * (U[NV - 1][i] - 0.5 * kin * ir[i]);
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int k = 0; k < N; ++k) U[v][k] = Us[at(v, base + k * st)];
     }
-    const double HxL = *row(fb, fb_index<DIM>(0, v, l, NFP, 1, 0), ldf);
-    const double HxR = *row(fb, fb_index<DIM>(1, v, l, NFP, 1, 0), ldf);
-    // the y and z face values too: consumed (below) before the barrier, so
-    // that their loads overlap this variable's flux work instead of being
-    // sunk to their use after the barrier, where nothing hides them
-    double HyL[N], HyR[N], HzL[N], HzR[N];
+    if (!kAhead) {
+      if (a != kFirst) outside(a);
+    } else if (a > 0) {
+      outside(a - 1);
+    } else if (c0 != 0.0) {
+      // u0's line at once: point by point each load would wait for the
+      // stores before it
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      HyL[i] = *row(fb, fb_index<DIM>(2, v, i + N * z, NFP, 1, 0), ldf);
-      HyR[i] = *row(fb, fb_index<DIM>(3, v, i + N * z, NFP, 1, 0), ldf);
-      HzL[i] = HzR[i] = 0.0;
-      if constexpr (DIM == 3) {
-        HzL[i] = *row(fb, fb_index<DIM>(4, v, i + N * y, NFP, 1, 0), ldf);
-        HzR[i] = *row(fb, fb_index<DIM>(5, v, i + N * y, NFP, 1, 0), ldf);
-      }
+      for (int v = 0; v < NV; ++v) load_u0(v, U0[kAhead ? v : 0]);
     }
-    // the stage's u0 term likewise (u0 is read only when c0 is nonzero): one
-    // round trip for the line instead of one per point in the store loop
-    double U0[N];
+    double FL[NV], FR[NV];
+    {
+      double tl[NV], tr[NV], yl[NV], yr[NV];
 #pragma unroll
-    for (int i = 0; i < N; ++i) U0[i] = 0.0;
-    if (c0 != 0.0)
-#pragma unroll
-      for (int i = 0; i < N; ++i) U0[i] = *row(u0, int64_t(v) * NP + l * N + i, ld);
-    const bool is_e = v == NV - 1;
-    double cur[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      double x = 0.0;
-#pragma unroll
-      for (int k = 0; k < NV; ++k) x += (v == k ? 1.0 : 0.0) * U[k][i];
-      cur[i] = x;
-    }
-    auto flux = [&](int a, int i) {
-      const double x = cur[i] + (is_e ? pr[i] : 0.0);
-      return x * (U[1 + a][i] * ir[i]) + (v == 1 + a ? pr[i] : 0.0);
-    };
-    // fluxes across lines to LDS first, so that the x work below hides the barrier's wait
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      Hy[l * N + i][el] = flux(1, i);
-      if constexpr (DIM == 3) Hz[l * N + i][el] = flux(2, i);
-    }
-    double R[N];
-    {  // x: the lane's own line
-      double F[N];
-#pragma unroll
-      for (int k = 0; k < N; ++k) F[k] = flux(0, k);
-      double FL = 0.0, FR = 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        FL += lL[k] * F[k];
-        FR += lR[k] * F[k];
-      }
-      const double jL = HxL - FL, jR = HxR - FR;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        double d = 0.0;
-#pragma unroll
-        for (int k = 0; k < N; ++k) d += D[i * N + k] * F[k];
-        R[i] = d + dgL[i] * jL + dgR[i] * jR;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      asm volatile("" ::"v"(HyL[i]), "v"(HyR[i]), "v"(HzL[i]), "v"(HzR[i]), "v"(U0[i]));
-    __syncthreads();
-    // y: point (i, y, z) on the line of points (i, k, z)
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      double d = 0.0, FL = 0.0, FR = 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        const double x = Hy[i + N * k + N * N * z][el];
-        d += Dy[k] * x;
-        FL += lL[k] * x;
-        FR += lR[k] * x;
-      }
-      R[i] += d + gLy * (HyL[i] - FL) + gRy * (HyR[i] - FR);
-    }
-    if constexpr (DIM == 3) {  // z: the line of points (i, y, k)
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        double d = 0.0, FL = 0.0, FR = 0.0;
+      for (int v = 0; v < NV; ++v) {
+        tl[v] = tr[v] = 0.0;
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          const double x = Hz[i + N * y + N * N * k][el];
-          d += Dz[k] * x;
-          FL += lL[k] * x;
-          FR += lR[k] * x;
+          tl[v] += lL[k] * U[v][k];
+          tr[v] += lR[k] * U[v][k];
         }
-        R[i] += d + gLz * (HzL[i] - FL) + gRz * (HzR[i] - FR);
+        const double wl = __shfl(tr[v], sl[a]), wr = __shfl(tl[v], sr[a]);
+        yl[v] = xl[a] ? zl[a][v] : wl;
+        yr[v] = xr[a] ? zr[a][v] : wr;
       }
+      rusanov1<DIM>(yl, tl, a, gamma, FL);
+      rusanov1<DIM>(tr, yr, a, gamma, FR);
     }
-    if (live) {
+    if (hl) {
+      const double* F = HB + int64_t(code[e * (2 * DIM) + 2 * a]) * (NV * NL) + q;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) FL[v] = F[v * NL];
+    }
+    if (hr) {
+      const double* F = HB + int64_t(code[e * (2 * DIM) + 2 * a + 1]) * (NV * NL) + q;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) FR[v] = F[v * NL];
+    }
+    double ua[N], pr[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const double ir = 1.0 / U[0][k];
+      double kin = 0.0;
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) kin += U[1 + b][k] * U[1 + b][k];
+      pr[k] = gm1 * (U[NV - 1][k] - 0.5 * kin * ir);
+      ua[k] = U[1 + a][k] * ir;
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double F[N], fl = 0.0, fr = 0.0;
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        F[k] = (U[v][k] + (v == NV - 1 ? pr[k] : 0.0)) * ua[k] + (v == 1 + a ? pr[k] : 0.0);
+        fl += lL[k] * F[k];
+        fr += lR[k] * F[k];
+      }
+      const double jl = FL[v] - fl, jr = FR[v] - fr;
+      double R[N];
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const int64_t o = int64_t(v) * NP + l * N + i;
-        double r = c1 * cur[i] + c2 * (scale * R[i]);
-        if (c0 != 0.0) r += c0 * U0[i];
-        *row(out, o, ldo) = r;
+        double d = dgL[i] * jl + dgR[i] * jr;
+#pragma unroll
+        for (int k = 0; k < N; ++k) d += D[i * N + k] * F[k];
+        R[i] = a == kFirst ? d : d + Rs[at(v, base + i * st)];
+      }
+      if (a > 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) Rs[at(v, base + i * st)] = R[i];
+      } else if (live) {
+        double* w = U0[kAhead ? v : 0];
+        if (!kAhead && c0 != 0.0) load_u0(v, w);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const int64_t row = int64_t(v * NP + base + i);
+          const double r = c1 * U[v][i] + c2 * (scale * R[i]);
+          __builtin_nontemporal_store(c0 != 0.0 ? r + c0 * w[i] : r, out + row * ldo + e);
+        }
       }
     }
-    __syncthreads();  // before the next variable overwrites Hy, Hz
   }
 }
 
@@ -672,20 +926,46 @@ lt_status fr_faces(lt_tree_s* t, const double* u, int64_t ld, const double* tab,
   return LT_OK;
 }
 
+// Hanging-face tables of the current connectivity, for the stages of one call.
+lt_status fr_rows(lt_tree_s* t, int p, hipStream_t s) {
+  const int64_t n = t->n_cur, rows = t->n_hang;
+  const int dim = t->g.dim, S = 1 << (dim - 1);
+  int64_t nfp = 1;
+  for (int a = 0; a < dim - 1; ++a) nfp *= p + 1;
+  LT_TRY_STATUS(grow(t->A, &t->fr_hm, &t->fr_hm_cap, (n + 3) / 4));
+  LT_TRY_STATUS(grow(t->A, &t->fr_code, &t->fr_code_cap, n * 2 * dim));
+  LT_TRY_STATUS(grow(t->A, &t->fr_hb, &t->fr_hb_cap, std::max<int64_t>(rows, 1) * (S + 1) * (dim + 2) * nfp));
+  launch_fill_u32(t->fr_hm, (n + 3) / 4, 0u, s);
+  if (rows > 0)
+    k_fr_rows<<<unsigned((rows * (S + 1) + 255) / 256), 256, 0, s>>>(t->hang, rows, dim, n, t->fr_code,
+                                                                    t->fr_hm, &t->dctr->err);
+  if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "FR row kernels launch");
+  return LT_OK;
+}
+
 template <int DIM, int N>
-lt_status fr_volume(lt_tree_s* t, const double* tab, double length, double gamma, const double* uin,
-                    int64_t ld, const double* fb, int64_t ldf, const double* u0, double c0, double c1,
-                    double c2, double* out, int64_t ldo, hipStream_t s) {
+lt_status fr_stage(lt_tree_s* t, const double* tab, double length, double gamma, const double* uin,
+                   int64_t ld, const double* u0, int64_t ld0, double c0, double c1, double c2, double* out,
+                   int64_t ldo, hipStream_t s) {
   const int64_t n = t->n_cur;
-  // p = 3 in 3D: four parts of 16 elements per wave, 4 waves (16 lines of
-  // 16 elements): no spills at 224 VGPRs and two workgroups per CU; else one
-  // part of 64 elements, one wave per line
-  constexpr int H = (DIM == 3 && N == 4) ? 4 : 1;
-  constexpr int waves = (DIM == 3 ? N * N : N) / H;
-  constexpr int EB = 64 / H;
-  k_fr_volume<DIM, N, H><<<unsigned((n + EB - 1) / EB), 64 * waves, 0, s>>>(
-      t->g, t->kbuf[t->cur], n, length, gamma, uin, ld, fb, ldf, u0, c0, c1, c2, out, ldo);
-  if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "FR volume kernel launch");
+  constexpr int NL = DIM == 3 ? N * N : N;
+  constexpr int EB = stage_elems(DIM, N);
+  if (t->n_hang > 0)
+    k_fr_hang<DIM, N><<<unsigned((t->n_hang + 3) / 4), 256, 0, s>>>(t->hang, t->n_hang, n, tab, gamma, uin,
+                                                                    ld, t->fr_hb);
+  const unsigned blocks = unsigned((n + EB - 1) / EB);
+  const uint8_t* hm = reinterpret_cast<const uint8_t*>(t->fr_hm);
+  // one variable's rows within 32-bit byte offsets (8.3M leaves at p = 3 in
+  // 3D), and short of the offset that stands for no load
+  if (int64_t(NL) * N * ld * 8 <= int64_t(kNoLoad))
+    k_fr_stage<DIM, N, false><<<blocks, EB * NL, 0, s>>>(t->g, t->kbuf[t->cur], t->nbr, hm, t->fr_code,
+                                                         t->fr_hb, n, length, gamma, uin, ld, u0, ld0, c0, c1,
+                                                         c2, out, ldo, &t->dctr->err);
+  else
+    k_fr_stage<DIM, N, true><<<blocks, EB * NL, 0, s>>>(t->g, t->kbuf[t->cur], t->nbr, hm, t->fr_code,
+                                                        t->fr_hb, n, length, gamma, uin, ld, u0, ld0, c0, c1,
+                                                        c2, out, ldo, &t->dctr->err);
+  if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "FR stage kernel launch");
   return LT_OK;
 }
 
@@ -725,12 +1005,6 @@ lt_status fr_tab(lt_tree_s* t, int p, hipStream_t s, const double** out) {
   return LT_OK;
 }
 
-int64_t face_doubles(int dim, int p) {
-  int64_t nfp = 1;
-  for (int a = 0; a < dim - 1; ++a) nfp *= p + 1;
-  return int64_t(2 * dim) * (dim + 2) * nfp;
-}
-
 lt_status faces(lt_tree_s* t, int p, const double* u, int64_t ld, const double* tab, double gamma,
                 double* fb, int64_t ldf, hipStream_t s) {
 #define LT_F(D, NN) return fr_faces<D, NN>(t, u, ld, tab, gamma, fb, ldf, s)
@@ -753,10 +1027,10 @@ lt_status faces(lt_tree_s* t, int p, const double* u, int64_t ld, const double* 
 #undef LT_F
 }
 
-lt_status volume(lt_tree_s* t, int p, const double* tab, double length, double gamma, const double* uin,
-                 int64_t ld, const double* fb, int64_t ldf, const double* u0, double c0, double c1,
-                 double c2, double* out, int64_t ldo, hipStream_t s) {
-#define LT_V(D, NN) return fr_volume<D, NN>(t, tab, length, gamma, uin, ld, fb, ldf, u0, c0, c1, c2, out, ldo, s)
+lt_status stage(lt_tree_s* t, int p, const double* tab, double length, double gamma, const double* uin,
+                int64_t ld, const double* u0, int64_t ld0, double c0, double c1, double c2, double* out,
+                int64_t ldo, hipStream_t s) {
+#define LT_V(D, NN) return fr_stage<D, NN>(t, tab, length, gamma, uin, ld, u0, ld0, c0, c1, c2, out, ldo, s)
   if (t->g.dim == 3) {
     switch (p) {
       case 1: LT_V(3, 2);
@@ -774,13 +1048,6 @@ lt_status volume(lt_tree_s* t, int p, const double* tab, double length, double g
     default: LT_V(2, 8);
   }
 #undef LT_V
-}
-
-lt_status internal_faces(lt_tree_s* t, int p, int64_t* ldf) {
-  const int64_t n = t->n_cur;
-  LT_TRY_STATUS(grow(t->A, &t->fr_fb, &t->fr_fb_cap, face_doubles(t->g.dim, p) * n));
-  *ldf = n;
-  return LT_OK;
 }
 
 }  // namespace
@@ -811,10 +1078,8 @@ lt_status lt_fr_residual(lt_tree t, int p, const double* u, int64_t ld, double g
   hipStream_t s = static_cast<hipStream_t>(stream);
   const double* tab = nullptr;
   LT_TRY_STATUS(fr_tab(t, p, s, &tab));
-  int64_t ldf = 0;
-  LT_TRY_STATUS(internal_faces(t, p, &ldf));
-  LT_TRY_STATUS(faces(t, p, u, ld, tab, gamma, t->fr_fb, ldf, s));
-  return volume(t, p, tab, length, gamma, u, ld, t->fr_fb, ldf, nullptr, 0.0, 0.0, 1.0, R, ld_r, s);
+  LT_TRY_STATUS(fr_rows(t, p, s));
+  return stage(t, p, tab, length, gamma, u, ld, u, ld, 0.0, 0.0, 1.0, R, ld_r, s);
 }
 
 lt_status lt_fr_rk3(lt_tree t, int p, double* u, int64_t ld, double* work, double dt, double gamma,
@@ -827,20 +1092,23 @@ lt_status lt_fr_rk3(lt_tree t, int p, double* u, int64_t ld, double* work, doubl
   hipStream_t s = static_cast<hipStream_t>(stream);
   const double* tab = nullptr;
   LT_TRY_STATUS(fr_tab(t, p, s, &tab));
-  int64_t ldf = 0;
-  LT_TRY_STATUS(internal_faces(t, p, &ldf));
-  double* fb = t->fr_fb;
+  if (steps == 0) return LT_OK;
+  LT_TRY_STATUS(fr_rows(t, p, s));
+  // the first stage's result: a stage reads its neighbours' state, so it
+  // cannot write where it reads
+  int64_t np = 1;
+  for (int a = 0; a < t->g.dim; ++a) np *= p + 1;
+  const int64_t n = t->n_cur;
+  LT_TRY_STATUS(grow(t->A, &t->fr_u1, &t->fr_u1_cap, (t->g.dim + 2) * np * n));
+  double* u1 = t->fr_u1;
   for (int k = 0; k < steps; ++k) {
     // u1 = u + dt R(u)
-    LT_TRY_STATUS(faces(t, p, u, ld, tab, gamma, fb, ldf, s));
-    LT_TRY_STATUS(volume(t, p, tab, length, gamma, u, ld, fb, ldf, nullptr, 0.0, 1.0, dt, work, ld, s));
-    // u2 = 3/4 u + 1/4 u1 + 1/4 dt R(u1)   (written over u1)
-    LT_TRY_STATUS(faces(t, p, work, ld, tab, gamma, fb, ldf, s));
-    LT_TRY_STATUS(volume(t, p, tab, length, gamma, work, ld, fb, ldf, u, 0.75, 0.25, 0.25 * dt, work, ld, s));
+    LT_TRY_STATUS(stage(t, p, tab, length, gamma, u, ld, u, ld, 0.0, 1.0, dt, u1, n, s));
+    // u2 = 3/4 u + 1/4 u1 + 1/4 dt R(u1)
+    LT_TRY_STATUS(stage(t, p, tab, length, gamma, u1, n, u, ld, 0.75, 0.25, 0.25 * dt, work, ld, s));
     // u_next = 1/3 u + 2/3 u2 + 2/3 dt R(u2)   (written over u)
-    LT_TRY_STATUS(faces(t, p, work, ld, tab, gamma, fb, ldf, s));
-    LT_TRY_STATUS(volume(t, p, tab, length, gamma, work, ld, fb, ldf, u, 1.0 / 3.0, 2.0 / 3.0,
-                         2.0 / 3.0 * dt, u, ld, s));
+    LT_TRY_STATUS(stage(t, p, tab, length, gamma, work, ld, u, ld, 1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0 * dt, u,
+                        ld, s));
   }
   return LT_OK;
 }

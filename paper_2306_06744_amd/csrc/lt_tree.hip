@@ -906,6 +906,10 @@ lt_status read_ctr(lt_tree t, hipStream_t stream) {
   return LT_OK;
 }
 
+void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream) {
+  if (n > 0) k_fill_u32<<<unsigned(ceil_div(n, 256)), 256, 0, stream>>>(p, n, v);
+}
+
 lt_status clear_err(lt_tree t, hipStream_t stream) {
   k_clear_scan<<<1, 64, 0, stream>>>(t->status, 0, t->dctr, 1, 0, 0, 0, nullptr, nullptr);
   LT_HIP(hipGetLastError());
@@ -1643,7 +1647,10 @@ void lt_destroy(lt_tree t) {
   for (auto& o : t->fr_tab) fr(o);
   fr(t->mesh_np);
   fr(t->chunk_np);
-  fr(t->fr_fb);
+  fr(t->fr_u1);
+  fr(t->fr_hb);
+  fr(t->fr_code);
+  fr(t->fr_hm);
   if (t->hctr) (void)hipHostFree(t->hctr);
   if (t->hcctr) (void)hipHostFree(t->hcctr);
   if (t->xs) (void)hipStreamDestroy(t->xs);

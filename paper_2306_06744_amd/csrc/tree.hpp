@@ -155,6 +155,8 @@ lt_status prep_scan_conn(lt_tree_s* t, int64_t n_items, hipStream_t stream, int 
 lt_status create_tree(const lt_geom* geom, lt_tree_s** out);
 // Copy the device counters to the pinned mirror and wait for the stream.
 lt_status read_ctr(lt_tree_s* t, hipStream_t stream);
+// p[0, n) = v (a kernel: a captured graph must hold no memset node).
+void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream);
 // Zero the counters and the error word.
 lt_status clear_err(lt_tree_s* t, hipStream_t stream);
 // Key-directory size for n leaves: 2^L buckets of 2^shift key values.
@@ -277,8 +279,14 @@ struct lt_tree_s {
   int32_t* split_F = nullptr;   // fused parents
   int64_t split_F_cap = 0;
   double* fr_tab[LT_MAX_DEGREE + 1] = {};  // flux reconstruction: 1D tables per degree
-  double* fr_fb = nullptr;                  // flux reconstruction: face traces / common fluxes
-  int64_t fr_fb_cap = 0;
+  double* fr_u1 = nullptr;                  // flux reconstruction: the first stage's state
+  int64_t fr_u1_cap = 0;
+  double* fr_hb = nullptr;                  //   fluxes of the hanging faces, by row
+  int64_t fr_hb_cap = 0;
+  int32_t* fr_code = nullptr;               //   per (leaf, hanging face): its place there
+  int64_t fr_code_cap = 0;
+  uint32_t* fr_hm = nullptr;                //   per leaf one byte: its hanging faces
+  int64_t fr_hm_cap = 0;
   uint8_t* mesh_np = nullptr;   // ensemble with per-mesh degrees: points per element of each mesh
   int mesh_npm = 0;             //   the largest of them (the solution layout's point stride)
   unsigned mesh_degs = 0;       //   bit p set: some mesh has degree p

@@ -128,3 +128,49 @@ def test_errors():
     with pytest.raises(lt.LtError) as ei:
         h.fr_residual(2, u, L)
     assert ei.value.status == 7
+
+
+@pytest.mark.parametrize("dim,p", [(2, p) for p in range(1, 8)] + [(3, p) for p in range(1, 4)])
+@pytest.mark.parametrize("depth", [0, 1, None])
+def test_residual_at_workgroup_edges(dim, p, depth):
+    """Every degree of the stage kernel, on trees smaller than one workgroup
+    (one leaf, its own neighbour on every face; one family) and on an adapted
+    tree whose leaf count leaves a remainder (depth None)."""
+    import torch
+    print("fr edges", dim, p, depth, flush=True)
+    d_max = 3 if dim == 3 else 5
+    if depth is None:
+        g, keys, nbr, hang = tree_pair(dim, d_max, 40 + p, cycles=2)
+        assert g.size() % 64
+    else:
+        g, o = both(dim, 0, d_max, depth=depth)
+        assert_same_connectivity(g, o, "tree")
+        keys = o.keys()
+        nbr, hang = o.connect()
+    u = fields(fr.solution_points(keys, dim, d_max, p, (LO,) * dim, L), dim)
+    u = u * (1.0 + 0.02 * np.random.default_rng(p).standard_normal(u.shape))
+    R_o, _ = fr.residual(keys, nbr, hang, u, dim, d_max, L, p)
+    R = g.fr_residual(p, torch.from_numpy(u).cuda(), L).cpu().numpy()
+    rel, mx = np.linalg.norm(R - R_o) / np.linalg.norm(R_o), np.abs(R - R_o).max()
+    print(f"residual rel L2 {rel:.2e} max {mx:.2e} bar {bar(u, keys, d_max):.2e}", flush=True)
+    assert rel <= 1e-12 and mx <= bar(u, keys, d_max)
+
+
+@pytest.mark.parametrize("dim,p", [(2, 7), (3, 3)])
+def test_wide_rows(dim, p):
+    """Arrays whose rows of one variable pass 2^32 bytes take the 64-bit form
+    of the stage kernel: the same step as with a tight leading dimension, to
+    the rounding of one contraction order against another."""
+    import torch
+    d_max = 5 if dim == 2 else 3
+    g, keys, nbr, hang = tree_pair(dim, d_max, 60 + p, cycles=2)
+    u = torch.from_numpy(fields(fr.solution_points(keys, dim, d_max, p, (LO,) * dim, L), dim)).cuda()
+    n, ld = u.shape[2], 2 ** 32 // (8 * 64) + 8
+    wide = torch.empty((dim + 2, 64, ld), dtype=torch.float64, device="cuda")
+    wide[:, :, :n] = u
+    R = g.fr_residual(p, u, L)
+    assert (R - g.fr_residual(p, wide, L)).abs().max() <= bar(u.cpu().numpy(), keys, d_max)
+    work = torch.empty_like(wide)
+    a = g.fr_rk3(p, u.clone(), torch.empty_like(u), 1e-3, L)
+    b = g.fr_rk3(p, wide, work, 1e-3, L)[:, :, :n]
+    assert (a - b).abs().max() <= 1e-14 * a.abs().max()
