@@ -193,6 +193,60 @@ __device__ inline void list_put(int32_t* __restrict__ l, int64_t i, int64_t cap,
   if (i < cap) l[i] = v;
 }
 
+// What a tile of leaves emits, from one mask per wave and round: a lane's
+// output offset is the tile's prefix, plus its wave's, plus the outputs of the
+// wave's earlier rounds and of the lower lanes of its own, all of them
+// population counts.
+struct WaveOut {
+  int base;  // outputs of the block's earlier waves
+  int all;   // of the whole block
+};
+
+// Exclusive scan over the block's waves of two small counts packed in one
+// word (each below 2^31 over a block), every thread calling with its wave's.
+__device__ inline void block_waves(int a, int b, WaveOut* A, WaveOut* B) {
+  constexpr int kWaves = kScanBig / 64;
+  __shared__ int wa[kWaves], wb[kWaves];
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    wa[w] = a;
+    wb[w] = b;
+  }
+  __syncthreads();
+  int ea = 0, eb = 0, ta = 0, tb = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    ea += i < w ? wa[i] : 0;
+    eb += i < w ? wb[i] : 0;
+    ta += wa[i];
+    tb += wb[i];
+  }
+  __syncthreads();
+  *A = WaveOut{ea, ta};
+  *B = WaveOut{eb, tb};
+}
+
+// Reserves `all` entries of a device-side list for the block (one atomic);
+// returns where they start.
+__device__ inline int64_t block_append(int all, int64_t* count) {
+  __shared__ int64_t s_at;
+  if (threadIdx.x == 0)
+    s_at = all > 0 ? int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(count), (unsigned long long)all)) : 0;
+  __syncthreads();
+  const int64_t at = s_at;
+  __syncthreads();
+  return at;
+}
+
+__device__ inline uint64_t lanes_below() { return (uint64_t(1) << (threadIdx.x & 63)) - 1; }
+
+// R rounds of 64 consecutive leaves per wave.  Bound: latency (the ticket, the
+// leaves, a flagged leaf's family, the look-back, the stores), so a tile's
+// loads and stores are whole rows of consecutive leaves and its counts are
+// ballots.  With eight consecutive leaves per thread and 64-bit scans of their
+// counts adapt took 36 us at 37 000 leaves and 44 at 1.9M, a refinement pass 18
+// and 40; in this form 12 and 32, 8 and 19.
+template <int R>
 __global__ __launch_bounds__(kScanBig) void k_adapt(KeyGeom g, const uint64_t* __restrict__ in,
                                                   const int8_t* __restrict__ flags,
                                                   uint64_t* __restrict__ out, int64_t cap,
@@ -203,112 +257,116 @@ __global__ __launch_bounds__(kScanBig) void k_adapt(KeyGeom g, const uint64_t* _
   const int64_t tile = take_ticket(st);
   if (tile >= scan_tiles(st)) return;
   const int64_t n = st.items.get();
-  const int64_t base = tile * kTileMax + int64_t(threadIdx.x) * kItems;
+  const int lane = threadIdx.x & 63;
+  const int64_t base = tile * (int64_t(kScanBig) * R) + int64_t(threadIdx.x >> 6) * (64 * R) + lane;
   const int nc = g.nchild();
-  uint64_t key[kItems];
-  int act[kItems];  // 0 keep, 1 refine, 2 emit parent, 3 drop
-  int64_t local = 0;
+  uint64_t key[R];
+  uint64_t one[R], ref[R], par[R];  // lanes that emit themselves or their parent; their children; their parent
+  int n_one = 0, n_ref = 0, n_par = 0;
   unsigned err = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t i = base + k;
-    act[k] = 3;
+  for (int k = 0; k < R; ++k) {
+    const int64_t i = base + 64 * k;
+    int a = 3;  // 0 keep, 1 refine, 2 emit parent, 3 drop
     key[k] = 0;
-    if (i >= n) continue;
-    const uint64_t kk = in[i];
-    key[k] = kk;
-    int f = flags[i];
-    if (f < -1 || f > 1) {
-      err |= ERR_BAD_FLAG;
-      f = 0;
-    }
-    const int d = key_depth(g, kk);
-    int lo, hi;
-    depth_limits(g, kk, &lo, &hi);
-    if (f == 1 && d >= hi) f = 0;
-    if (f == -1 && d <= lo) f = 0;
-    int a = 0;
-    if (f == 1) {
-      a = 1;
-    } else if (f == -1) {
-      // The family is complete iff the 2^dim keys around i are exactly the
-      // siblings (consecutive, same depth, raw IDs incrementing by one).
-      const uint64_t m = key_m(g, kk);
-      const int c = child_index(g, m, d);
-      const int64_t h = i - c;
-      const uint64_t step = uint64_t(1) << (g.dim * (g.dmax - d) + g.mb);
-      const uint64_t k0 = kk - uint64_t(c) * step;
-      bool all = h >= 0 && h + nc <= n;
-      if (all) {
-        // every sibling's key and flag loaded before any is compared: one
-        // round trip instead of a chain of 2^dim dependent ones
-        uint64_t sk[8];
-        int sf[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (j < nc) {
-            sk[j] = in[h + j];
-            sf[j] = flags[h + j];
-          }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (j < nc) all = all && sk[j] == k0 + uint64_t(j) * step && sf[j] == -1;
+    if (i < n) {
+      const uint64_t kk = in[i];
+      key[k] = kk;
+      int f = flags[i];
+      if (f < -1 || f > 1) {
+        err |= ERR_BAD_FLAG;
+        f = 0;
       }
-      if (all) a = c == 0 ? 2 : 3;
+      const int d = key_depth(g, kk);
+      int lo, hi;
+      depth_limits(g, kk, &lo, &hi);
+      if (f == 1 && d >= hi) f = 0;
+      if (f == -1 && d <= lo) f = 0;
+      a = 0;
+      if (f == 1) {
+        a = 1;
+      } else if (f == -1) {
+        // The family is complete iff the 2^dim keys around i are exactly the
+        // siblings (consecutive, same depth, raw IDs incrementing by one).
+        const uint64_t m = key_m(g, kk);
+        const int c = child_index(g, m, d);
+        const int64_t h = i - c;
+        const uint64_t step = uint64_t(1) << (g.dim * (g.dmax - d) + g.mb);
+        const uint64_t k0 = kk - uint64_t(c) * step;
+        bool all = h >= 0 && h + nc <= n;
+        if (all) {
+          // every sibling's key and flag loaded before any is compared: one
+          // round trip instead of a chain of 2^dim dependent ones
+          uint64_t sk[8];
+          int sf[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (j < nc) {
+              sk[j] = in[h + j];
+              sf[j] = flags[h + j];
+            }
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (j < nc) all = all && sk[j] == k0 + uint64_t(j) * step && sf[j] == -1;
+        }
+        if (all) a = c == 0 ? 2 : 3;
+      }
     }
-    act[k] = a;
-    local += a == 1 ? nc : (a == 3 ? 0 : 1);
+    ref[k] = __ballot(a == 1);
+    par[k] = __ballot(a == 2);
+    one[k] = __ballot(a == 0) | par[k];
+    n_one += __popcll(one[k]);
+    n_ref += __popcll(ref[k]);
+    n_par += __popcll(par[k]);
   }
-  // the new children go on the list of leaves the first balance pass examines
-  int64_t ex = 0, fx = 0;
+  // new children go on the list of leaves the first balance pass examines,
+  // fused parents on the list it probes around
+  WaveOut wr, wp;
+  block_waves(n_ref * nc, n_par, &wr, &wp);
+  WaveOut wo, unused;
+  block_waves(n_one, 0, &wo, &unused);
+  int64_t eo = elist ? block_append(wr.all, nexam) + wr.base : 0;
+  int64_t fo = flist ? block_append(wp.all, nflist) + wp.base : 0;
+  int64_t o = tile_prefix(st, tile, int64_t(wr.all) + wo.all) + wr.base + wo.base;
+  const uint64_t below = lanes_below();
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    ex += act[k] == 1 ? nc : 0;
-    fx += act[k] == 2 ? 1 : 0;
-  }
-  int64_t eo = elist ? wave_append(ex, nexam) : 0;
-  // the fused parents go on the list the first balance pass probes around
-  int64_t fo = flist ? wave_append(fx, nflist) : 0;
-  int64_t blk;
-  const int64_t thr = block_exclusive<kScanBig>(local, &blk);
-  int64_t o = tile_prefix(st, tile, blk) + thr;
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int a = act[k];
-    if (a == 3) continue;
-    const int cnt = a == 1 ? nc : 1;
-    if (o + cnt > cap) {
+  for (int k = 0; k < R; ++k) {
+    const int rb = __popcll(ref[k] & below);
+    const int64_t q = o + int64_t(rb) * nc + __popcll(one[k] & below);
+    const int64_t eq = eo + int64_t(rb) * nc, fq = fo + __popcll(par[k] & below);
+    o += int64_t(__popcll(ref[k])) * nc + __popcll(one[k]);
+    eo += int64_t(__popcll(ref[k])) * nc;
+    fo += __popcll(par[k]);
+    const bool is_ref = (ref[k] >> lane) & 1, is_par = (par[k] >> lane) & 1;
+    if (!is_ref && !((one[k] >> lane) & 1)) continue;
+    const int cnt = is_ref ? nc : 1;
+    const uint64_t kk = key[k];
+    if (q + cnt > cap) {
       err |= ERR_CAPACITY;
       // the slots below the capacity still get a valid key: the kernels after
       // this one in a captured cycle read them before the result is discarded
-      for (int64_t q = o; q < cap && q < o + cnt; ++q) {
-        out[q] = key[k];
-        if (marks) marks[q] = 0u;
+      for (int64_t t = q; t < cap && t < q + cnt; ++t) {
+        out[t] = kk;
+        if (marks) marks[t] = 0u;
       }
-      if (elist && a == 1)
-        for (int c = 0; c < nc; ++c) list_put(elist, eo++, ecap, -1);
-      if (flist && a == 2) list_put(flist, fo++, fcap, -1);
-      o += cnt;
+      if (elist && is_ref)
+        for (int c = 0; c < nc; ++c) list_put(elist, eq + c, ecap, -1);
+      if (flist && is_par) list_put(flist, fq, fcap, -1);
       continue;
     }
-    const uint64_t kk = key[k];
     const int d = key_depth(g, kk);
-    if (a == 0) {
-      out[o] = kk;
-      if (marks) marks[o] = 0u;
-    } else if (a == 2) {
-      out[o] = make_key(g, key_m(g, kk), d - 1);
-      if (marks) marks[o] = kMarkFused;
-      if (flist) list_put(flist, fo++, fcap, int32_t(o));
+    if (!is_ref) {
+      out[q] = is_par ? make_key(g, key_m(g, kk), d - 1) : kk;
+      if (marks) marks[q] = is_par ? kMarkFused : 0u;
+      if (flist && is_par) list_put(flist, fq, fcap, int32_t(q));
     } else {
       const uint64_t m = key_m(g, kk);
       for (int c = 0; c < nc; ++c) {
-        out[o + c] = child_key(g, m, d, c);
-        if (marks) marks[o + c] = kMarkExamine;
-        if (elist) list_put(elist, eo++, ecap, int32_t(o + c));
+        out[q + c] = child_key(g, m, d, c);
+        if (marks) marks[q + c] = kMarkExamine;
+        if (elist) list_put(elist, eq + c, ecap, int32_t(q + c));
       }
     }
-    o += cnt;
   }
   if (err) atomicOr(st.err, err);
 }
@@ -482,6 +540,7 @@ __global__ __launch_bounds__(256) void k_build_dir(const uint64_t* __restrict__ 
 // 2:1 balance, refinement pass: split bit-0 leaves one level, in order.  The
 // new mark array holds bit 2 for leaves to examine next pass: the children of
 // split leaves and the leaves that found a violation.
+template <int R>
 __global__ __launch_bounds__(kScanBig) void k_balance_refine(KeyGeom g, const uint64_t* __restrict__ in,
                                                            const uint32_t* __restrict__ mark,
                                                            uint64_t* __restrict__ out,
@@ -489,12 +548,13 @@ __global__ __launch_bounds__(kScanBig) void k_balance_refine(KeyGeom g, const ui
                                                            ScanState st, const unsigned* conv,
                                                            int32_t* __restrict__ elist, int64_t* nexam,
                                                            int64_t ecap) {
+  constexpr int64_t kTile = int64_t(kScanBig) * R;
   if (conv && *conv) {
     // captured cycles past the fixpoint: the pass is the identity, a plain copy
     const int64_t n = st.items.get();
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const int64_t i = int64_t(blockIdx.x) * kTileMax + int64_t(k) * kScanBig + threadIdx.x;
+    for (int k = 0; k < R; ++k) {
+      const int64_t i = int64_t(blockIdx.x) * kTile + int64_t(k) * kScanBig + threadIdx.x;
       if (i < n) {
         out[i] = in[i];
         mark_out[i] = 0u;
@@ -506,64 +566,90 @@ __global__ __launch_bounds__(kScanBig) void k_balance_refine(KeyGeom g, const ui
   const int64_t tile = take_ticket(st);
   if (tile >= scan_tiles(st)) return;
   const int64_t n = st.items.get();
-  const int64_t base = tile * kTileMax + int64_t(threadIdx.x) * kItems;
+  const int lane = threadIdx.x & 63;
+  const int64_t base = tile * kTile + int64_t(threadIdx.x >> 6) * (64 * R) + lane;
   const int nc = g.nchild();
-  uint32_t w[kItems];
-  uint64_t key[kItems];  // read with the marks, ahead of the look-back
-  int64_t local = 0;
+  uint64_t key[R];  // read with the marks, ahead of the look-back
+  uint64_t one[R], ref[R], chk[R];  // lanes kept, split, and kept but to be examined again
+  int n_one = 0, n_ref = 0, n_chk = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t i = base + k;
-    w[k] = 0;
-    key[k] = 0;
-    if (i >= n) continue;
-    w[k] = mark[i] | 8u;  // bit 3: valid item
-    key[k] = in[i];
-    local += (w[k] & 1u) ? nc : 1;
+  for (int k = 0; k < R; ++k) {
+    const int64_t i = base + 64 * k;
+    const uint32_t w = i < n ? mark[i] : 0u;
+    key[k] = i < n ? in[i] : 0;
+    ref[k] = __ballot(w & 1u);
+    one[k] = __ballot(i < n && !(w & 1u));
+    chk[k] = __ballot((w & 3u) == 2u);
+    n_one += __popcll(one[k]);
+    n_ref += __popcll(ref[k]);
+    n_chk += __popcll(chk[k]);
   }
   // leaves the next pass examines (bit 2): the children of split leaves and
   // the leaves that found a violation, also put on the examine list
-  int64_t ex = 0;
-#pragma unroll
-  for (int k = 0; k < kItems; ++k)
-    if (w[k] & 8u) ex += (w[k] & 1u) ? nc : ((w[k] & 2u) ? 1 : 0);
-  int64_t eo = wave_append(ex, nexam);
-  int64_t blk;
-  const int64_t thr = block_exclusive<kScanBig>(local, &blk);
-  int64_t o = tile_prefix(st, tile, blk) + thr;
+  WaveOut wr, we;
+  block_waves(n_ref * nc + n_one, n_ref * nc + n_chk, &wr, &we);
+  int64_t eo = block_append(we.all, nexam) + we.base;
+  int64_t o = tile_prefix(st, tile, wr.all) + wr.base;
+  const uint64_t below = lanes_below();
   unsigned err = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    if (!(w[k] & 8u)) continue;
+  for (int k = 0; k < R; ++k) {
+    const int rb = __popcll(ref[k] & below);
+    const int64_t q = o + int64_t(rb) * nc + __popcll(one[k] & below);
+    const int64_t eq = eo + int64_t(rb) * nc + __popcll(chk[k] & below);
+    o += int64_t(__popcll(ref[k])) * nc + __popcll(one[k]);
+    eo += int64_t(__popcll(ref[k])) * nc + __popcll(chk[k]);
+    const bool is_ref = (ref[k] >> lane) & 1, is_chk = (chk[k] >> lane) & 1;
+    if (!is_ref && !((one[k] >> lane) & 1)) continue;
+    const int cnt = is_ref ? nc : 1;
     const uint64_t kk = key[k];
-    const int cnt = (w[k] & 1u) ? nc : 1;
-    const int nex = (w[k] & 1u) ? nc : ((w[k] & 2u) ? 1 : 0);
-    if (o + cnt > cap) {
+    if (q + cnt > cap) {
       err |= ERR_CAPACITY;
-      for (int64_t q = o; q < cap && q < o + cnt; ++q) {  // valid keys below the capacity
-        out[q] = kk;
-        mark_out[q] = 0u;
+      for (int64_t t = q; t < cap && t < q + cnt; ++t) {  // valid keys below the capacity
+        out[t] = kk;
+        mark_out[t] = 0u;
       }
-      for (int c = 0; c < nex; ++c) list_put(elist, eo++, ecap, -1);
-      o += cnt;
+      for (int c = 0; c < (is_ref ? nc : (is_chk ? 1 : 0)); ++c) list_put(elist, eq + c, ecap, -1);
       continue;
     }
-    if (w[k] & 1u) {
+    if (is_ref) {
       const uint64_t m = key_m(g, kk);
       const int d = key_depth(g, kk);
       for (int c = 0; c < nc; ++c) {
-        out[o + c] = child_key(g, m, d, c);
-        mark_out[o + c] = 4u;
-        list_put(elist, eo++, ecap, int32_t(o + c));
+        out[q + c] = child_key(g, m, d, c);
+        mark_out[q + c] = 4u;
+        list_put(elist, eq + c, ecap, int32_t(q + c));
       }
     } else {
-      out[o] = kk;
-      mark_out[o] = (w[k] & 2u) ? 4u : 0u;
-      if (w[k] & 2u) list_put(elist, eo++, ecap, int32_t(o));
+      out[q] = kk;
+      mark_out[q] = is_chk ? 4u : 0u;
+      if (is_chk) list_put(elist, eq, ecap, int32_t(q));
     }
-    o += cnt;
   }
   if (err) atomicOr(st.err, err);
+}
+
+// Launches over the look-back tiles of st (prepared with tile_of(count)).
+void launch_adapt(const KeyGeom& g, const uint64_t* in, const int8_t* flags, uint64_t* out, int64_t cap,
+                  const ScanState& st, uint32_t* marks, int32_t* elist, int64_t* nexam, int64_t ecap,
+                  int32_t* flist, int64_t* nflist, int64_t fcap, hipStream_t s) {
+  if (st.tile == kScanBig)
+    k_adapt<1><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, flags, out, cap, st, marks, elist, nexam, ecap,
+                                                   flist, nflist, fcap);
+  else
+    k_adapt<kRounds><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, flags, out, cap, st, marks, elist, nexam,
+                                                         ecap, flist, nflist, fcap);
+}
+
+void launch_balance_refine(const KeyGeom& g, const uint64_t* in, const uint32_t* mark, uint64_t* out,
+                           uint32_t* mark_out, int64_t cap, const ScanState& st, const unsigned* conv,
+                           int32_t* elist, int64_t* nexam, int64_t ecap, hipStream_t s) {
+  if (st.tile == kScanBig)
+    k_balance_refine<1><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, conv, elist,
+                                                            nexam, ecap);
+  else
+    k_balance_refine<kRounds><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, conv,
+                                                                  elist, nexam, ecap);
 }
 
 // Face connectivity (Section 3.3).  For face f = 2a + side the same-size box
@@ -1062,13 +1148,12 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
   // adapt K0 -> K[0]; its scan's clear also starts the cycle: leaves before
   // the cycle S[1] <- S[0], the fixpoint flag cleared
   ScanState st;
-  LT_TRY(prep_scan(t, C, kTileMax, s, 1 | 4 | 8, &st, &S[1], &S[0]));
+  LT_TRY(prep_scan(t, C, tile_of(C), s, 1 | 4 | 8, &st, &S[1], &S[0]));
   st.items.p = &S[1];
   st.commit = &S[0];
   st.commit_cap = C;
-  k_adapt<<<grid_tiles(st), kScanBig, 0, s>>>(g, K0, F, K[0], C, st, t->mbuf[0], t->elist,
-                                              &t->dctr->nexam, t->elist_cap, t->fused,
-                                              &t->dctr->nfused, t->fused_cap);
+  launch_adapt(g, K0, F, K[0], C, st, t->mbuf[0], t->elist, &t->dctr->nexam, t->elist_cap, t->fused,
+               &t->dctr->nfused, t->fused_cap, s);
   LT_HIP(hipGetLastError());
   // balance: fixed passes, then a check
   // (the tree entering the cycle is balanced, so adapt's marks restrict the
@@ -1091,13 +1176,12 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
     // to S[4], where the pass reads it: the last tile commits the new count
     // to S[0] while workgroups of the capacity-sized grid may still be taking
     // tickets, and each must see the count the scan started from
-    LT_TRY(prep_scan(t, C, kTileMax, s, 2 | 4, &st, &S[4], &S[0]));
+    LT_TRY(prep_scan(t, C, tile_of(C), s, 2 | 4, &st, &S[4], &S[0]));
     st.items.p = &S[4];
     st.commit = &S[0];
     st.commit_cap = C;
-    k_balance_refine<<<grid_tiles(st), kScanBig, 0, s>>>(g, K[ki], t->mbuf[mi], K[1 - ki],
-                                                        t->mbuf[1 - mi], C, st, conv, t->elist,
-                                                        &t->dctr->nexam, t->elist_cap);
+    launch_balance_refine(g, K[ki], t->mbuf[mi], K[1 - ki], t->mbuf[1 - mi], C, st, conv, t->elist,
+                          &t->dctr->nexam, t->elist_cap, s);
     ki = 1 - ki;
     mi = 1 - mi;
   }
@@ -1359,12 +1443,10 @@ lt_status lt_adapt(lt_tree t, const int8_t* flags, void* stream) {
     cap = std::min(cap, std::min(t->mcap[0], std::min(t->elist_cap, t->fused_cap)));
   }
   ScanState st;
-  LT_TRY(prep_scan(t, n, kTileMax, s, 1 | 4, &st));
-  k_adapt<<<grid_tiles(st), kScanBig, 0, s>>>(t->g, t->kbuf[t->cur], flags, t->kbuf[out], cap, st,
-                                              marks ? t->mbuf[0] : nullptr,
-                                              marks ? t->elist : nullptr, &t->dctr->nexam,
-                                              t->elist_cap, marks ? t->fused : nullptr,
-                                              &t->dctr->nfused, t->fused_cap);
+  LT_TRY(prep_scan(t, n, tile_of(n), s, 1 | 4, &st));
+  launch_adapt(t->g, t->kbuf[t->cur], flags, t->kbuf[out], cap, st, marks ? t->mbuf[0] : nullptr,
+               marks ? t->elist : nullptr, &t->dctr->nexam, t->elist_cap, marks ? t->fused : nullptr,
+               &t->dctr->nfused, t->fused_cap, s);
   LT_HIP(hipGetLastError());
   LT_TRY(read_ctr(t, s));
   if (t->hctr->err & ERR_BAD_FLAG) return fail(LT_ERR_ARG, "flags must be -1, 0 or 1");
@@ -1448,12 +1530,10 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
     LT_TRY(grow(t->A, &t->elist, &t->elist_cap, n_new));
     ScanState st;
     // also zeroes the mark count and the examine list for the next pass
-    LT_TRY(prep_scan(t, t->n_cur, kTileMax, s, 4, &st));
+    LT_TRY(prep_scan(t, t->n_cur, tile_of(t->n_cur), s, 4, &st));
     const int64_t cap = std::min(std::min(t->kcap[out], t->mcap[1 - mi]), t->elist_cap);
-    k_balance_refine<<<grid_tiles(st), kScanBig, 0, s>>>(t->g, t->kbuf[t->cur], t->mbuf[mi],
-                                                        t->kbuf[out], t->mbuf[1 - mi], cap, st,
-                                                        nullptr, t->elist, &t->dctr->nexam,
-                                                        t->elist_cap);
+    launch_balance_refine(t->g, t->kbuf[t->cur], t->mbuf[mi], t->kbuf[out], t->mbuf[1 - mi], cap, st,
+                          nullptr, t->elist, &t->dctr->nexam, t->elist_cap, s);
     LT_HIP(hipGetLastError());
     expect_total = n_new;
     t->cur = out;

@@ -18,16 +18,20 @@ namespace lt {
 constexpr int kBlock = 256;   // workgroup of the plain kernels
 constexpr int kItems = 8;     // items per thread in scan-emit kernels
 // Scan-emit kernels over the leaves on the critical path (adapt, balance
-// refinement) run 1024-thread tiles of 8192 items: ~1.6M leaves are 200
-// tiles, and the look-back of the last one crosses about 4 windows of 64
-// predecessors (each window one round trip to device-coherent memory) instead
-// of 13.  Short scans (transfer groups) and scans that may run beside another
+// refinement) run 1024-thread tiles, each wave over rounds of 64 consecutive
+// leaves.  Short scans (transfer groups) and scans that may run beside another
 // stream's kernels (connectivity rows, the split transfer's lists), where a
 // 1024-thread workgroup would wait for a whole free CU, keep 256-thread tiles
 // of 2048 items.
 constexpr int kScanBig = 1024;
 constexpr int kScanSmall = kBlock;
-constexpr int64_t kTileMax = int64_t(kScanBig) * kItems;
+constexpr int kRounds = 8;  // rounds of a wave in a large tile
+// Items per tile of the leaf scans: one round per wave up to 2^18 leaves (256
+// tiles, one per compute unit, so that no tile's latency is spent on a second
+// round), eight beyond.
+inline int64_t tile_of(int64_t n) {
+  return n <= (int64_t(1) << 18) ? int64_t(kScanBig) : int64_t(kScanBig) * kRounds;
+}
 constexpr int64_t kTileMin = int64_t(kScanSmall) * kItems;
 
 enum : unsigned {
@@ -57,7 +61,7 @@ struct ScanState {
   unsigned* err;
   int64_t* total;         // written by the last tile: sum of all counts
   Count items;            // items scanned; tiles = max(1, ceil(items / tile))
-  int64_t tile;           // items per tile: the kernel's workgroup size times kItems
+  int64_t tile;           // items per tile (kTileMin, or tile_of for the leaf scans)
   int64_t* commit;        // optional (captured cycles): also receives min(total, commit_cap),
   int64_t commit_cap;     // with ERR_CAPACITY raised when the total exceeds it
 };
@@ -124,18 +128,6 @@ __device__ inline int64_t block_exclusive(int64_t v, int64_t* total) {
   __syncthreads();
   *total = all;
   return before + inc - v;
-}
-
-// Appends v entries per lane to a list whose length is *count (one atomic per
-// wave); returns this lane's first position.  Every lane of the wave calls it.
-__device__ inline int64_t wave_append(int64_t v, int64_t* count) {
-  const int64_t inc = wave_inclusive(v);
-  const int64_t tot = __shfl(inc, 63, 64);
-  int64_t b = 0;
-  if ((threadIdx.x & 63) == 63 && tot > 0)
-    b = int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(count), (unsigned long long)tot));
-  b = __shfl(b, 63, 64);
-  return b + inc - v;
 }
 
 // Sum of v over the 64 lanes of a wave (result in every lane).

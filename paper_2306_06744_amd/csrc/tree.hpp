@@ -134,7 +134,7 @@ struct lt_tree_s;
 namespace lt {
 
 // Zero the look-back words for n_items of scan work in tiles of `tile`
-// items (kTileMax or kTileMin, matching the kernel's workgroup) and the
+// items (tile_of(n) or kTileMin, matching the kernel's workgroup) and the
 // counters; fills st for a scan kernel on `stream`.  flags: 1 = also clear
 // the error word, 2 = record the balance fixpoint (no marks since the last
 // clear; captured cycles), 4 = also clear the lists, 8 = clear the fixpoint

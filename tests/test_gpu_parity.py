@@ -326,3 +326,19 @@ def test_deterministic_rerun():
         res.append((np_keys(g).copy(), g.nbr().cpu().numpy(), g.hang().cpu().numpy()))
     for a, b in zip(res[0], res[1]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dim,depth", [(2, 0), (2, 1), (2, 5), (2, 9), (3, 0), (3, 3), (3, 6)])
+def test_adapt_and_balance_at_tile_edges(dim, depth):
+    """Adapt and balance refinement at the sizes of their scan tiles: less
+    than a wave, one tile of 1024 leaves, 2^18 leaves (the last size with one
+    round per wave) and, after an adaptation, more (eight rounds)."""
+    g, o = both(dim, 0, depth + 2, depth=depth)
+    for c in range(3):
+        print("tile edges", dim, depth, "leaves", o.size(), flush=True)
+        adapt_both(g, o, synth.random_flags(70 + c, o.size(), 0.2, 0.6))
+        assert_same_tree(g, o, "adapt")
+        g.balance()
+        o.balance()
+        assert_same_tree(g, o, "balance")
+        assert_same_map(g, o, "map")
