@@ -27,7 +27,7 @@ struct lt_cycle_s {
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   int parity = 0;                  // u[parity] holds the solution
-  int64_t* dsz = nullptr;          // device: leaves, leaves before, hanging rows, groups, a balance pass's input
+  int64_t* dsz = nullptr;          // device: leaves, leaves before, hanging rows, a balance pass's input
   int64_t* hsz = nullptr;          // pinned mirror
   void* flag_host = nullptr;       // pinned flag-parameter table
   int64_t hang_rows = 0;
@@ -305,7 +305,7 @@ lt_status lt_cycle_create(lt_tree t, const lt_cycle_desc* d, void* stream, lt_cy
   c->tmpl[0].centre = c->tmpl_centres.data();
   c->d.flag_template = nullptr;
   lt_status st = LT_OK;
-  if (dev_malloc(t->A, reinterpret_cast<void**>(&c->dsz), 5 * sizeof(int64_t)) != hipSuccess ||
+  if (dev_malloc(t->A, reinterpret_cast<void**>(&c->dsz), 4 * sizeof(int64_t)) != hipSuccess ||
       hipHostMalloc(&c->hsz, 4 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(&c->flag_host, flag_args_size() * size_t(c->nmesh), hipHostMallocDefault) != hipSuccess)
     st = fail(LT_ERR_OOM, "cycle state");
@@ -336,7 +336,7 @@ lt_status lt_cycle_run(lt_cycle c, const lt_flag_params* fp, void* stream, int* 
                      s) != hipSuccess)
     return fail(LT_ERR_HIP, "flag table upload");
   if (hipGraphLaunch(c->exec[q], s) != hipSuccess) return fail(LT_ERR_HIP, "graph launch");
-  if (hipMemcpyAsync(c->hsz, c->dsz, 4 * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
+  if (hipMemcpyAsync(c->hsz, c->dsz, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
     return fail(LT_ERR_HIP, "size readback");
   LT_TRY_STATUS(read_ctr(t, s));
   unsigned err = t->hctr->err;

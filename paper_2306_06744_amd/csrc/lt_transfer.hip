@@ -315,54 +315,86 @@ __device__ inline void xy_pass(const double* Mx, const double* My, const double*
 }
 
 // Groups of 64 consecutive new elements that hold any refined or fused
-// element.  Groups with refined children only are listed in order by a
-// look-back scan (count 1 per such group); groups that hold a fused element
-// are appended to a second list (flist, count *nflist) in any order, since
-// every group is computed on its own.
-__global__ __launch_bounds__(kScanSmall) void k_group_list(const int8_t* __restrict__ kind, Count cn,
-                                                       int32_t* __restrict__ list, ScanState st,
-                                                       int32_t* __restrict__ flist,
-                                                       int64_t* __restrict__ nflist) {
-  const int64_t tile = take_ticket(st);
-  if (tile >= scan_tiles(st)) return;
+// element: those with refined children only go to list (count *nlist), those
+// that hold a fused element to flist (count *nflist).  A wave takes one group
+// a round, lane = element, so a group's case is two ballots of its kinds; a
+// workgroup appends its groups, in order, by one atomic per list (the blocks'
+// order is arbitrary: every group is computed on its own).
+// MIXED (an ensemble with a degree per mesh): entries (group << 2) | (N - 1)
+// for every degree N present among a group's refined / fused elements, listed
+// by whether its elements of that degree include a fused one.
+// Bound: latency.  One thread per group, with a look-back scan for the ordered
+// list, took 26 us at 37 000 leaves, and 181 us at 39 000 leaves of ten meshes
+// (a serial loop over a group's elements); in this form 5 and 7.
+constexpr int kGroupRounds = 8;
+constexpr int kGroupsPerBlock = kBlock / 64 * kGroupRounds;
+
+template <bool MIXED>
+__global__ __launch_bounds__(kBlock) void k_group_list(KeyGeom g, const uint64_t* __restrict__ keys,
+                                                       const uint8_t* __restrict__ np_of_mesh,
+                                                       const int8_t* __restrict__ kind, Count cn,
+                                                       int32_t* __restrict__ list, int64_t* nlist,
+                                                       int32_t* __restrict__ flist, int64_t* nflist) {
+  constexpr int kWaves = kBlock / 64;
+  constexpr int kPer = MIXED ? 3 : 1;  // entries a group can have
+  __shared__ int cr[kWaves], cf[kWaves];
+  __shared__ int64_t at[2];
   const int64_t n = cn.get();
-  const int64_t ngroups = st.items.get();
-  const int64_t base = tile * kTileMin + int64_t(threadIdx.x) * kItems;
-  bool ref[kItems];
-  int64_t local = 0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t g0 = int64_t(blockIdx.x) * kGroupsPerBlock + w * kGroupRounds;
+  if (int64_t(blockIdx.x) * kGroupsPerBlock * 64 >= n) return;  // launches sized for a capacity
+  int kd[kGroupRounds];
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t gidx = base + k;
-    ref[k] = false;
-    if (gidx >= ngroups) continue;
-    const int64_t j0 = gidx * 64;
-    bool any = false, fus = false;
-    if (j0 + 64 <= n) {
-      const uint64_t* w8 = reinterpret_cast<const uint64_t*>(kind + j0);
-      uint64_t acc = 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc |= w8[q];
-      any = acc != 0;
-      fus = (acc & 0x8080808080808080ull) != 0;  // a negative kind byte
-    } else {
-      for (int64_t j = j0; j < n; ++j) {
-        any = any || kind[j] != 0;
-        fus = fus || kind[j] < 0;
-      }
-    }
-    if (fus) {
-      const int64_t o = int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(nflist), 1ull));
-      flist[o] = int32_t(gidx);
-    }
-    ref[k] = any && !fus;
-    local += ref[k] ? 1 : 0;
+  for (int r = 0; r < kGroupRounds; ++r) {
+    const int64_t j = (g0 + r) * 64 + lane;
+    kd[r] = j < n ? int(kind[j]) : 0;
   }
-  int64_t blk;
-  const int64_t thr = block_exclusive<kScanSmall>(local, &blk);
-  int64_t o = tile_prefix(st, tile, blk) + thr;
+  unsigned ref = 0, fus = 0;  // bit kPer * round + (N - 2)
 #pragma unroll
-  for (int k = 0; k < kItems; ++k)
-    if (ref[k]) list[o++] = int32_t(base + k);
+  for (int r = 0; r < kGroupRounds; ++r) {
+    if constexpr (MIXED) {
+      if (__ballot(kd[r] != 0) == 0) continue;
+      const int np = kd[r] != 0 ? int(np_of_mesh[key_mesh(g, keys[(g0 + r) * 64 + lane])]) : 0;
+#pragma unroll
+      for (int N = 2; N <= 4; ++N) {
+        const bool f = __ballot(np == N * N * N && kd[r] < 0) != 0;
+        const bool any = __ballot(np == N * N * N) != 0;
+        fus |= unsigned(f) << (kPer * r + N - 2);
+        ref |= unsigned(any && !f) << (kPer * r + N - 2);
+      }
+    } else {
+      const bool f = __ballot(kd[r] < 0) != 0, any = __ballot(kd[r] != 0) != 0;
+      fus |= unsigned(f) << r;
+      ref |= unsigned(any && !f) << r;
+    }
+  }
+  if (lane == 0) {
+    cr[w] = __popc(ref);
+    cf[w] = __popc(fus);
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const int* c = threadIdx.x == 0 ? cr : cf;
+    int all = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) all += c[i];
+    unsigned long long* count = reinterpret_cast<unsigned long long*>(threadIdx.x == 0 ? nlist : nflist);
+    at[threadIdx.x] = all ? int64_t(atomicAdd(count, (unsigned long long)all)) : 0;
+  }
+  __syncthreads();
+  int64_t ro = at[0], fo = at[1];
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    ro += i < w ? cr[i] : 0;
+    fo += i < w ? cf[i] : 0;
+  }
+  if (lane < kPer * kGroupRounds) {
+    const unsigned below = (1u << lane) - 1u;
+    const int64_t grp = g0 + lane / kPer;
+    const int32_t entry = MIXED ? int32_t(grp * 4 + 1 + lane % kPer) : int32_t(grp);
+    if ((ref >> lane) & 1u) list[ro + __popc(ref & below)] = entry;
+    if ((fus >> lane) & 1u) flist[fo + __popc(fus & below)] = entry;
+  }
 }
 
 // Ensembles with a degree per mesh (lt_set_mesh_degree): the interpolation
@@ -953,73 +985,14 @@ __global__ __launch_bounds__(256) void k_copy3_mixed(const int32_t* __restrict__
   }
 }
 
-// Work entries of the interpolation passes: (group << 2) | (N - 1) for every
-// degree N present among a group's refined / fused elements.  Groups whose
-// elements of degree N are refined only go to the ordered list (look-back
-// scan, one entry per such (group, degree)); the others to flist (any order).
-__global__ __launch_bounds__(kScanSmall) void k_group_list_mixed(KeyGeom g, const uint64_t* __restrict__ keys,
-                                                                 const uint8_t* __restrict__ np_of_mesh,
-                                                                 const int8_t* __restrict__ kind, Count cn,
-                                                                 int32_t* __restrict__ list, ScanState st,
-                                                                 int32_t* __restrict__ flist,
-                                                                 int64_t* __restrict__ nflist) {
-  const int64_t tile = take_ticket(st);
-  if (tile >= scan_tiles(st)) return;
-  const int64_t n = cn.get();
-  const int64_t ngroups = st.items.get();
-  const int64_t base = tile * kTileMin + int64_t(threadIdx.x) * kItems;
-  unsigned refmask[kItems];  // bit N-1: a degree-N refined-only entry
-  int64_t local = 0;
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t gidx = base + k;
-    refmask[k] = 0;
-    if (gidx >= ngroups) continue;
-    unsigned any = 0, fus = 0;  // bit N-1 per degree
-    const int64_t j0 = gidx * 64;
-    if (j0 + 64 <= n) {  // a group of copies only (nearly all): eight words, no element loop
-      const uint64_t* w8 = reinterpret_cast<const uint64_t*>(kind + j0);
-      uint64_t acc = 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc |= w8[q];
-      if (acc == 0) continue;
-    }
-    for (int64_t j = j0; j < j0 + 64 && j < n; ++j) {
-      const int kd = kind[j];
-      if (kd == 0) continue;
-      const int np = elem_np(g, np_of_mesh, keys[j]);
-      const int N = np == 8 ? 2 : (np == 27 ? 3 : 4);
-      any |= 1u << (N - 1);
-      if (kd < 0) fus |= 1u << (N - 1);
-    }
-    for (int N = 2; N <= 4; ++N)
-      if (fus & (1u << (N - 1))) {
-        const int64_t o = int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(nflist), 1ull));
-        flist[o] = int32_t(gidx * 4 + (N - 1));
-      }
-    refmask[k] = any & ~fus;
-    local += __popc(refmask[k]);
-  }
-  int64_t blk;
-  const int64_t thr = block_exclusive<kScanSmall>(local, &blk);
-  int64_t o = tile_prefix(st, tile, blk) + thr;
-#pragma unroll
-  for (int k = 0; k < kItems; ++k)
-    for (int N = 2; N <= 4; ++N)
-      if (refmask[k] & (1u << (N - 1))) list[o++] = int32_t((base + k) * 4 + (N - 1));
-}
-
 // Scratch of one FP64 transfer, sized for n new leaves: per copy chunk the
 // source offset of a pure copy run (ceil(n / 256) entries at the finest
-// tuning), the interpolation-group lists (the ordered list of groups with a
-// refined element, then the groups holding a fused one: 2 ceil(n / 64)),
-// look-back words and counters.  From the tree's buffers (lt_transfer) or
+// tuning), the interpolation-group lists (the groups with refined elements
+// only, then those holding a fused one: 2 ceil(n / 64)) and counters.  From the tree's buffers (lt_transfer) or
 // from the library's static array (lt_transfer_noalloc).
 struct XferScratch {
   int64_t* copy_delta;
   int32_t* grp_list;
-  uint64_t* status;
-  int64_t status_cap;
   DevCtr* ctr;
   // a second stream for the interpolation passes, forked from and joined to
   // the caller's (null: everything on the caller's stream)
@@ -1033,7 +1006,7 @@ lt_status copy_pass(const TransferTune& tune, const int32_t* src, const int8_t* 
 
 template <int DIM, int N>
 hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* src, const int8_t* kind,
-                  Count n, const int64_t* ngroups_dev, int nvar, const double* uo, int64_t ldo,
+                  Count n, int nvar, const double* uo, int64_t ldo,
                   double* un, int64_t ldn, const XferScratch& X, hipStream_t s, lt_status* st_out) {
   *st_out = LT_OK;
   if constexpr (DIM == 3) {
@@ -1053,24 +1026,21 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     }
     *st_out = copy_pass(tune, src, kind, n, nvar * N * N * N, uo, ldo, un, ldn, X.copy_delta, true, s);
     if (X.side) e = hipStreamWaitEvent(X.side, X.fork, 0);
-    // grp_list holds the ordered list in [0, ngroups) and the list of
-    // groups with a fused element in [ngroups, 2 ngroups)
-    ScanState st;
-    if (*st_out == LT_OK && e == hipSuccess)
-      *st_out = prep_scan_fixed(X.status, X.status_cap, X.ctr, ngroups, kTileMin, si, 0, &st);
+    // grp_list holds the groups of refined elements in [0, ngroups) and those
+    // with a fused element in [ngroups, 2 ngroups)
+    if (*st_out == LT_OK && e == hipSuccess) *st_out = clear_counters(X.ctr, si);
     if (*st_out == LT_OK && e == hipSuccess) {
-      st.items.p = ngroups_dev;
       int32_t* flist = X.grp_list + ngroups;
-      k_group_list<<<grid_tiles(st), kScanSmall, 0, si>>>(kind, n, X.grp_list, st, flist,
-                                                      &X.ctr->nfgroups);
+      k_group_list<false><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, si>>>(
+          KeyGeom{}, nullptr, nullptr, kind, n, X.grp_list, &X.ctr->total, flist, &X.ctr->nfgroups);
       const dim3 gi{unsigned(std::max<int64_t>(1, std::min<int64_t>(ngroups, tune.interp_grid))),
                     unsigned(nvar), 1u};
       // the buffer form takes N*N rows of either array by a 32-bit offset
       constexpr int64_t kRowsMax = (int64_t(1) << 32) / (8 * N * N);
       if (ldo < kRowsMax && ldn < kRowsMax)
-        k_refine3<N><<<gi, 64 * N, 0, si>>>(ops, src, kind, n, X.grp_list, st.total, uo, ldo, un, ldn);
+        k_refine3<N><<<gi, 64 * N, 0, si>>>(ops, src, kind, n, X.grp_list, &X.ctr->total, uo, ldo, un, ldn);
       else
-        k_interp3_ref<N, false><<<gi, 64 * N, 0, si>>>(ops, src, kind, n, X.grp_list, st.total, uo,
+        k_interp3_ref<N, false><<<gi, 64 * N, 0, si>>>(ops, src, kind, n, X.grp_list, &X.ctr->total, uo,
                                                        ldo, un, ldn, MixedArgs{});
       k_interp3<N, false><<<gi, 64 * N, 0, si>>>(ops, src, kind, n, flist, &X.ctr->nfgroups, uo, ldo, un,
                                                  ldn, MixedArgs{});
@@ -1164,7 +1134,7 @@ lt_status launch_copy(lt_tree_s* t, int64_t rows, const double* uo, int64_t ldo,
 
 lt_status launch_transfer(lt_tree_s* t, int p, const double* ops, int nvar, const double* u_old,
                           int64_t ld_old, double* u_new, int64_t ld_new, hipStream_t s) {
-  return launch_transfer(t, Count{t->n_cur, nullptr}, nullptr, p, ops, nvar, u_old, ld_old, u_new,
+  return launch_transfer(t, Count{t->n_cur, nullptr}, p, ops, nvar, u_old, ld_old, u_new,
                          ld_new, s);
 }
 
@@ -1172,7 +1142,7 @@ namespace {
 // The FP64 transfer over n new leaves of a mapping (src, kind) with the given
 // scratch; no allocation.
 lt_status transfer_with(int dim, const TransferTune& tune, const int32_t* src, const int8_t* kind,
-                        Count n, const int64_t* ngroups_dev, int p, const double* ops, int nvar,
+                        Count n, int p, const double* ops, int nvar,
                         const double* u_old, int64_t ld_old, double* u_new, int64_t ld_new,
                         const XferScratch& X, hipStream_t s) {
   if (n.n == 0) return LT_OK;
@@ -1182,7 +1152,7 @@ lt_status transfer_with(int dim, const TransferTune& tune, const int32_t* src, c
     return fail(LT_ERR_ARG, "nvar * (p+1)^dim must be in [1, 65535]");
   hipError_t e = hipErrorInvalidValue;
   lt_status st = LT_OK;
-#define LT_L(D, NN) e = launch<D, NN>(tune, ops, src, kind, n, ngroups_dev, nvar, u_old, ld_old, u_new, ld_new, X, s, &st)
+#define LT_L(D, NN) e = launch<D, NN>(tune, ops, src, kind, n, nvar, u_old, ld_old, u_new, ld_new, X, s, &st)
   if (dim == 3) {
     switch (p) {
       case 1: LT_L(3, 2); break;
@@ -1232,8 +1202,7 @@ lt_status transfer_side(lt_tree_s* t, hipStream_t* side, hipEvent_t* fork, hipEv
   return LT_OK;
 }
 
-lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, const int64_t* ngroups_dev,
-                                int nvar, const double* uo, int64_t ldo, double* un, int64_t ldn,
+lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, int nvar, const double* uo, int64_t ldo, double* un, int64_t ldn,
                                 hipStream_t s) {
   if (n.n == 0) return LT_OK;
   if (!t->mesh_np || t->g.dim != 3) return fail(LT_ERR_STATE, "per-mesh degrees are not set");
@@ -1261,12 +1230,11 @@ lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, con
   // passes on the second stream need it.  Then the copy pass on the caller's
   // stream and, as in the single-degree form, the interpolation passes
   // (which here write no copies) on the second stream.
-  ScanState st;
-  LT_TRY_STATUS(prep_scan(t, ngroups, kTileMin, s, 0, &st));
-  st.items.p = ngroups_dev;
+  LT_TRY_STATUS(clear_counters(t->dctr, s));
   int32_t* flist = t->grp_list + 3 * ngroups;
-  k_group_list_mixed<<<grid_tiles(st), kScanSmall, 0, s>>>(t->g, keys, t->mesh_np, t->map_kind, n,
-                                                           t->grp_list, st, flist, &t->dctr->nfgroups);
+  const int64_t* nlist = &t->dctr->total;
+  k_group_list<true><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, s>>>(
+      t->g, keys, t->mesh_np, t->map_kind, n, t->grp_list, &t->dctr->total, flist, &t->dctr->nfgroups);
   hipError_t ef = hipEventRecord(fork, s);
   if (ef != hipSuccess) return fail(LT_ERR_HIP, std::string("transfer fork: ") + hipGetErrorString(ef));
   const dim3 grid{unsigned(nchunks), unsigned(nvar), 1u};
@@ -1302,10 +1270,10 @@ lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, con
   do {                                                                                                 \
     if (buffer_ok(NN))                                                                                 \
       k_refine3_mixed<NN><<<gi, 64 * NN, 0, side>>>(OPS, t->map_src, t->map_kind, n, t->grp_list,      \
-                                                    st.total, uo, ldo, un, ldn, mx, t->g.nmesh);       \
+                                                    nlist, uo, ldo, un, ldn, mx, t->g.nmesh);          \
     else                                                                                               \
       k_interp3_ref<NN, true><<<gi, 64 * NN, 0, side>>>(OPS, t->map_src, t->map_kind, n, t->grp_list,  \
-                                                        st.total, uo, ldo, un, ldn, mx);               \
+                                                        nlist, uo, ldo, un, ldn, mx);                  \
     k_interp3<NN, true><<<gi, 64 * NN, 0, side>>>(OPS, t->map_src, t->map_kind, n, flist,              \
                                                   &t->dctr->nfgroups, uo, ldo, un, ldn, mx);           \
   } while (0)
@@ -1324,7 +1292,7 @@ lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, con
   return LT_OK;
 }
 
-lt_status launch_transfer(lt_tree_s* t, Count n, const int64_t* ngroups_dev, int p,
+lt_status launch_transfer(lt_tree_s* t, Count n, int p,
                           const double* ops, int nvar, const double* u_old, int64_t ld_old,
                           double* u_new, int64_t ld_new, hipStream_t s) {
   if (n.n == 0) return LT_OK;
@@ -1334,12 +1302,10 @@ lt_status launch_transfer(lt_tree_s* t, Count n, const int64_t* ngroups_dev, int
     const int64_t CH = 256 * int64_t(t->tune.copy_epl);
     LT_TRY_STATUS(grow(t->A, &t->copy_delta, &t->copy_delta_cap, (n.n + CH - 1) / CH));
     LT_TRY_STATUS(grow(t->A, &t->grp_list, &t->grp_cap, 2 * ngroups));
-    LT_TRY_STATUS(grow(t->A, &t->status, &t->status_cap,
-                       std::max<int64_t>(1, (ngroups + kTileMin - 1) / kTileMin)));
-    X = XferScratch{t->copy_delta, t->grp_list, t->status, t->status_cap, t->dctr};
+    X = XferScratch{t->copy_delta, t->grp_list, t->dctr};
     LT_TRY_STATUS(transfer_side(t, &X.side, &X.fork, &X.join));
   }
-  return transfer_with(t->g.dim, t->tune, t->map_src, t->map_kind, n, ngroups_dev, p, ops, nvar,
+  return transfer_with(t->g.dim, t->tune, t->map_src, t->map_kind, n, p, ops, nvar,
                        u_old, ld_old, u_new, ld_new, X, s);
 }
 
@@ -1353,18 +1319,15 @@ namespace {
 // it until the process ends), laid out for up to kNoallocLeaves new leaves:
 //   [0, 4 KiB)       FP64 1D operators (4 (p+1)^2 + (p+1) doubles, p <= 7)
 //   [4 KiB, 8 KiB)   counters (DevCtr)
-//   [8 KiB, 16 KiB)  look-back words of the group scan
 //   then             copy-chunk source offsets, interpolation-group lists.
 constexpr int64_t kNoallocLeaves = int64_t(1) << 25;
-constexpr size_t kOffOps = 0, kOffCtr = 4096, kOffStatus = 8192, kOffDelta = 16384;
-constexpr int64_t kStatusWords = (kOffDelta - kOffStatus) / 8;
+constexpr size_t kOffOps = 0, kOffCtr = 4096, kOffDelta = 8192;
 constexpr int64_t kDeltaWords = kNoallocLeaves / 256 + 2;
 constexpr size_t kOffGroups = kOffDelta + size_t(kDeltaWords) * 8;
 constexpr int64_t kGroupWords = 2 * (kNoallocLeaves / 64 + 2);
 constexpr size_t kScratchBytes = (kOffGroups + size_t(kGroupWords) * 4 + 255) / 256 * 256;
 static_assert(sizeof(double) * (4 * 8 * 8 + 8) <= kOffCtr - kOffOps, "operators fit");
-static_assert(sizeof(DevCtr) <= kOffStatus - kOffCtr, "counters fit");
-static_assert((kNoallocLeaves / 64 + kTileMin - 1) / kTileMin <= kStatusWords, "look-back words fit");
+static_assert(sizeof(DevCtr) <= kOffDelta - kOffCtr, "counters fit");
 
 // In host code this name is only a stand-in for the symbol: the device
 // address comes from hipGetSymbolAddress, per device.
@@ -1420,10 +1383,9 @@ lt_status lt_transfer_noalloc(lt_tree t, int p, int nvar, const double* u_old, i
   if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "operator build launch");
   const XferScratch X{reinterpret_cast<int64_t*>(base + kOffDelta),
                       reinterpret_cast<int32_t*>(base + kOffGroups),
-                      reinterpret_cast<uint64_t*>(base + kOffStatus), kStatusWords,
                       reinterpret_cast<DevCtr*>(base + kOffCtr)};
-  return transfer_with(t->g.dim, t->tune, t->map_src, t->map_kind, Count{t->n_cur, nullptr}, nullptr,
-                       p, ops, nvar, u_old, ld_old, u_new, ld_new, X, s);
+  return transfer_with(t->g.dim, t->tune, t->map_src, t->map_kind, Count{t->n_cur, nullptr}, p, ops,
+                       nvar, u_old, ld_old, u_new, ld_new, X, s);
 }
 
 lt_status lt_set_mesh_degree(lt_tree t, const int* p, void* stream) {
@@ -1458,7 +1420,7 @@ lt_status lt_transfer_mixed(lt_tree t, int nvar, const double* u_old, int64_t ld
   if (!t->has_old) return fail(LT_ERR_STATE, "lt_transfer_mixed needs a prior lt_adapt");
   if (ld_old < t->n_old || ld_new < t->n_cur) return fail(LT_ERR_ARG, "leading dimension too small");
   if (!t->map_valid) LT_TRY_STATUS(lt_map(t, stream));
-  return launch_transfer_mixed(t, t->kbuf[t->cur], Count{t->n_cur, nullptr}, nullptr, nvar, u_old, ld_old,
+  return launch_transfer_mixed(t, t->kbuf[t->cur], Count{t->n_cur, nullptr}, nvar, u_old, ld_old,
                                u_new, ld_new, static_cast<hipStream_t>(stream));
 }
 

@@ -875,7 +875,11 @@ constexpr int kMapWin = 640;
 __global__ __launch_bounds__(kBlock) void k_map(KeyGeom g, const uint64_t* __restrict__ old_keys,
                                                 Count cn_old, const uint64_t* __restrict__ keys,
                                                 Count cn, int32_t* __restrict__ src,
-                                                int8_t* __restrict__ kind, unsigned* err) {
+                                                int8_t* __restrict__ kind, unsigned* err,
+                                                const unsigned long long* nmarked) {
+  // captured cycles: marks left by the last marking pass mean that the fixed
+  // balance passes did not reach the fixpoint
+  if (nmarked && blockIdx.x == 0 && threadIdx.x == 0 && *nmarked != 0) atomicOr(err, ERR_BALANCE_PASSES);
   __shared__ uint64_t win[kBlock / 64][kMapWin];
   const int64_t n_old = cn_old.get(), n = cn.get();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -996,6 +1000,12 @@ void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream) {
   if (n > 0) k_fill_u32<<<unsigned(ceil_div(n, 256)), 256, 0, stream>>>(p, n, v);
 }
 
+lt_status clear_counters(DevCtr* ctr, hipStream_t stream) {
+  k_clear_scan<<<1, 64, 0, stream>>>(nullptr, 0, ctr, 0, 0, 0, 0, nullptr, nullptr);
+  LT_HIP(hipGetLastError());
+  return LT_OK;
+}
+
 lt_status clear_err(lt_tree t, hipStream_t stream) {
   k_clear_scan<<<1, 64, 0, stream>>>(t->status, 0, t->dctr, 1, 0, 0, 0, nullptr, nullptr);
   LT_HIP(hipGetLastError());
@@ -1090,7 +1100,7 @@ lt_status do_map(lt_tree t, hipStream_t stream) {
   if (t->n_cur > 0)
     k_map<<<unsigned(ceil_div(t->n_cur, kBlock)), kBlock, 0, stream>>>(
         t->g, t->kbuf[t->old], Count{t->n_old, nullptr}, t->kbuf[t->cur], Count{t->n_cur, nullptr},
-        t->map_src, t->map_kind, &t->dctr->err);
+        t->map_src, t->map_kind, &t->dctr->err, nullptr);
   LT_HIP(hipGetLastError());
   LT_TRY(read_ctr(t, stream));
   if (t->hctr->err & ERR_MAP)
@@ -1102,18 +1112,6 @@ lt_status do_map(lt_tree t, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------- captured cycles
-// Single-thread bookkeeping kernels of a cycle whose counts stay on the device.
-
-// After the balance passes: marks left mean the fixed passes did not reach
-// the fixpoint; and the transfer's groups of 64 leaves, ceil(S[0] / 64), the
-// count being final here.
-__global__ void k_check_marks(DevCtr* ctr, int64_t* groups, const int64_t* n) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (ctr->nmarked != 0) atomicOr(&ctr->err, ERR_BALANCE_PASSES);
-    *groups = (*n + 63) / 64;
-  }
-}
-
 // Also folds connectivity's error word (its branch ran on a side stream)
 // into the cycle's.
 __global__ void k_copy_keys(const uint64_t* __restrict__ src, uint64_t* __restrict__ dst, Count cn,
@@ -1173,11 +1171,11 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
                                                  t->dctr, conv, t->elist, t->elist_cap);
     if (pass == r.passes) break;
     // the clear also records convergence, and copies the pass's input count
-    // to S[4], where the pass reads it: the last tile commits the new count
+    // to S[3], where the pass reads it: the last tile commits the new count
     // to S[0] while workgroups of the capacity-sized grid may still be taking
     // tickets, and each must see the count the scan started from
-    LT_TRY(prep_scan(t, C, tile_of(C), s, 2 | 4, &st, &S[4], &S[0]));
-    st.items.p = &S[4];
+    LT_TRY(prep_scan(t, C, tile_of(C), s, 2 | 4, &st, &S[3], &S[0]));
+    st.items.p = &S[3];
     st.commit = &S[0];
     st.commit_cap = C;
     launch_balance_refine(g, K[ki], t->mbuf[mi], K[1 - ki], t->mbuf[1 - mi], C, st, conv, t->elist,
@@ -1185,12 +1183,10 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
     ki = 1 - ki;
     mi = 1 - mi;
   }
-  k_check_marks<<<1, 64, 0, s>>>(t->dctr, &S[3], &S[0]);
-  LT_HIP(hipGetLastError());
   if (ki != 0) return fail(LT_ERR_ARG, "balance passes of a captured cycle must be even");
   // map
   k_map<<<nleaf, kBlock, 0, s>>>(g, K0, Count{C, &S[1]}, K[0], Count{C, &S[0]}, t->map_src,
-                                  t->map_kind, err);
+                                  t->map_kind, err, &t->dctr->nmarked);
   LT_HIP(hipGetLastError());
   // connect on the side stream (the directory of K[0] was built by the check
   // pass); it reads the new keys only, and its scan words and counters are its
@@ -1219,9 +1215,9 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
   if (r.precision == 1) {
     LT_TRY(launch_split_transfer(t, Count{C, &S[0]}, r.p, r.nvar, r.uo, r.ld, r.un, r.ld, s));
   } else if (r.p < 0) {  // per-mesh degrees
-    LT_TRY(launch_transfer_mixed(t, K[0], Count{C, &S[0]}, &S[3], r.nvar, r.uo, r.ld, r.un, r.ld, s));
+    LT_TRY(launch_transfer_mixed(t, K[0], Count{C, &S[0]}, r.nvar, r.uo, r.ld, r.un, r.ld, s));
   } else {
-    LT_TRY(launch_transfer(t, Count{C, &S[0], t->n_cur}, &S[3], r.p, r.ops, r.nvar, r.uo, r.ld, r.un, r.ld, s));
+    LT_TRY(launch_transfer(t, Count{C, &S[0], t->n_cur}, r.p, r.ops, r.nvar, r.uo, r.ld, r.un, r.ld, s));
   }
   // the new keys become the next cycle's input, once connectivity is done
   LT_HIP(hipStreamWaitEvent(s, r.join, 0));

@@ -55,8 +55,8 @@ lt_status launch_flag_table(const KeyGeom& g, const lt_flag_params* fps, int nme
 // kbuf[1], `passes` (even) balance passes between kbuf[1] and kbuf[2] and a
 // check pass, connect, map, transfer uo -> un, then the new keys copied back
 // to kbuf[0] (skipped when an error bit is set).  dsz[0] = leaves,
-// dsz[1] = leaves before the cycle, dsz[2] = hanging rows, dsz[3] = groups of
-// 64 leaves, dsz[4] = a balance pass's input count.  Every buffer must already hold `cap` leaves (no allocation).
+// dsz[1] = leaves before the cycle, dsz[2] = hanging rows, dsz[3] = a balance
+// pass's input count.  Every buffer must already hold `cap` leaves (no allocation).
 struct CycleRec {
   int64_t cap;        // leaves
   int64_t hang_rows;  // rows of the hanging-face table
@@ -157,6 +157,8 @@ lt_status create_tree(const lt_geom* geom, lt_tree_s** out);
 lt_status read_ctr(lt_tree_s* t, hipStream_t stream);
 // p[0, n) = v (a kernel: a captured graph must hold no memset node).
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream);
+// Zero the counters, but for the error word and the balance lists' lengths.
+lt_status clear_counters(DevCtr* ctr, hipStream_t stream);
 // Zero the counters and the error word.
 lt_status clear_err(lt_tree_s* t, hipStream_t stream);
 // Key-directory size for n leaves: 2^L buckets of 2^shift key values.
@@ -186,8 +188,7 @@ lt_status launch_transfer(lt_tree_s* t, int p, const double* ops, int nvar, cons
 // The tree's second stream for the interpolation passes of a 3D transfer and
 // its fork/join events, made on first use (default priority, non-blocking).
 lt_status transfer_side(lt_tree_s* t, hipStream_t* side, hipEvent_t* fork, hipEvent_t* join);
-lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, const int64_t* ngroups_dev,
-                                int nvar, const double* uo, int64_t ldo, double* un, int64_t ldn,
+lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, int nvar, const double* uo, int64_t ldo, double* un, int64_t ldn,
                                 hipStream_t s);
 
 // COPY elements of the current mapping, all `rows` point rows (nvar * n_p);
@@ -198,9 +199,8 @@ lt_status launch_copy(lt_tree_s* t, Count n, int64_t rows, const double* uo, int
                       double* un, int64_t ldn, hipStream_t s);
 
 // Transfer over n new leaves given as a Count (a device count with the
-// launch sized for its capacity n.n); ngroups_dev, when set, holds
-// ceil(count / 64) on the device.  Asynchronous; no host synchronisation.
-lt_status launch_transfer(lt_tree_s* t, Count n, const int64_t* ngroups_dev, int p,
+// launch sized for its capacity n.n).  Asynchronous; no host synchronisation.
+lt_status launch_transfer(lt_tree_s* t, Count n, int p,
                           const double* ops, int nvar, const double* u_old, int64_t ld_old,
                           double* u_new, int64_t ld_new, hipStream_t s);
 

@@ -342,3 +342,39 @@ def test_adapt_and_balance_at_tile_edges(dim, depth):
         o.balance()
         assert_same_tree(g, o, "balance")
         assert_same_map(g, o, "map")
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+def test_interpolation_groups_at_list_edges(depth, mixed):
+    """The list of interpolation groups at its edges: fewer leaves than one
+    group, one group, and just around the 2048 leaves that one workgroup
+    lists; all leaves refined, all families fused, and both with copies.
+    FP64 on both sides (dense operators against sum factorisation): 1e-13."""
+    import torch
+    import paper_2306_06744_amd as lt
+    from gpu_util import class_errors, dense_expected
+    degrees = [1, 3, 2] if mixed else [2]
+    for seed, (pr, pc) in enumerate([(1.0, 0.0), (0.0, 1.0), (0.3, 0.4)]):
+        if mixed:
+            t = lt.Tree.batch(3, 6, [0] * 3, [6] * 3, [depth, depth - 1, depth])
+            t.set_mesh_degree(degrees)
+        else:
+            t = lt.Tree.uniform(3, 0, 6, depth=depth)
+        n_old, offs_old = t.size(), t.mesh_offsets()
+        f = synth.random_flags(seed, n_old, pr, pc)
+        f[8 * (n_old // 16):8 * (n_old // 16) + 8] = -1 if pc else 1     # one complete family at least
+        t.adapt(torch.from_numpy(f).cuda())
+        npm = max((p + 1) ** 3 for p in degrees)
+        u = synth.random_solution(seed, 2, npm, n_old)
+        ud = torch.from_numpy(u).cuda()
+        got = (t.transfer_mixed(ud) if mixed else t.transfer(2, ud)).cpu().numpy()
+        src, kind = (v.cpu().numpy() for v in t.mapping())
+        offs = t.mesh_offsets()
+        for m, p in enumerate(degrees):
+            js = np.arange(offs[m], offs[m + 1])
+            npts = (p + 1) ** 3
+            exp = dense_expected(3, p, u[:, :npts], src, kind, js)
+            for name, (l2, mx, k) in class_errors(got[:, :npts, js], exp, kind[js]).items():
+                print("groups", depth, mixed, seed, p, name, k, l2, flush=True)
+                assert l2 <= 1e-13 and mx <= 1e-13
