@@ -14,7 +14,7 @@
 //     the integral).
 // Supported: 64 points per element (3D p = 3, 2D p = 7).  Copies are copies.
 // Work lists (first child of each refined family, each fused parent) are
-// built on the device by a look-back scan, so the call never synchronises.
+// built on the device, so the call never synchronises.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,7 +32,6 @@ constexpr int kNP = 64;        // points per element
 constexpr int kMT = kNP / 16;  // 16-row tiles of an operator
 constexpr int kKS = kNP / 32;  // 32-deep K steps
 constexpr int kTC = 16;        // columns (families / fused parents) per tile
-constexpr int64_t kLow31 = (int64_t(1) << 31) - 1;
 
 __device__ inline void split3(double x, __bf16& b0, __bf16& b1, __bf16& b2) {
   b0 = __bf16(float(x));
@@ -106,31 +105,57 @@ __global__ void k_build_split_vec(const double* __restrict__ ops1d, int n1, int 
 }
 
 // Work lists from the mapping: R = first child of each refined family (kind
-// 1), F = each fused parent (kind -1), in new-leaf order.  One scan carries
-// both counts packed as nR + (nF << 31).
-__global__ __launch_bounds__(kScanSmall) void k_split_lists(const int8_t* __restrict__ kind,
-                                                        int32_t* __restrict__ R,
-                                                        int32_t* __restrict__ F, ScanState st) {
-  const int64_t tile = take_ticket(st);
-  if (tile >= scan_tiles(st)) return;
-  const int64_t n = st.items.get();
-  const int64_t base = tile * kTileMin + int64_t(threadIdx.x) * kItems;
-  int8_t kd[kItems];
-  int64_t local = 0;
+// 1), F = each fused parent (kind -1).  Waves take rounds of 64 leaves and
+// count by ballots; a workgroup appends its entries, in leaf order, by one
+// atomic per list (the workgroups' order is arbitrary: every family and every
+// parent is computed on its own).
+__global__ __launch_bounds__(kBlock) void k_split_lists(const int8_t* __restrict__ kind, Count cn,
+                                                        int32_t* __restrict__ R, int64_t* nR,
+                                                        int32_t* __restrict__ F, int64_t* nF) {
+  constexpr int kWaves = kBlock / 64;
+  __shared__ int cr[kWaves], cf[kWaves];
+  __shared__ int64_t at[2];
+  const int64_t n = cn.get();
+  if (int64_t(blockIdx.x) * kTileMin >= n) return;  // launches sized for a capacity
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = int64_t(blockIdx.x) * kTileMin + w * (64 * kItems) + lane;
+  int kd[kItems];
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) kd[k] = base + 64 * k < n ? int(kind[base + 64 * k]) : 0;
+  int r = 0, f = 0;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    const int64_t j = base + k;
-    kd[k] = j < n ? kind[j] : 0;
-    local += (kd[k] == 1 ? 1 : 0) + (kd[k] == -1 ? (int64_t(1) << 31) : 0);
+    r += __popcll(__ballot(kd[k] == 1));
+    f += __popcll(__ballot(kd[k] == -1));
   }
-  int64_t blk;
-  const int64_t thr = block_exclusive<kScanSmall>(local, &blk);
-  const int64_t o = tile_prefix(st, tile, blk) + thr;
-  int64_t orr = o & kLow31, of = o >> 31;
+  if (lane == 0) {
+    cr[w] = r;
+    cf[w] = f;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const int* c = threadIdx.x == 0 ? cr : cf;
+    int all = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) all += c[i];
+    unsigned long long* count = reinterpret_cast<unsigned long long*>(threadIdx.x == 0 ? nR : nF);
+    at[threadIdx.x] = all ? int64_t(atomicAdd(count, (unsigned long long)all)) : 0;
+  }
+  __syncthreads();
+  int64_t ro = at[0], fo = at[1];
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    ro += i < w ? cr[i] : 0;
+    fo += i < w ? cf[i] : 0;
+  }
+  const uint64_t below = (uint64_t(1) << lane) - 1;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    if (kd[k] == 1) R[orr++] = int32_t(base + k);
-    if (kd[k] == -1) F[of++] = int32_t(base + k);
+    const uint64_t mr = __ballot(kd[k] == 1), mf = __ballot(kd[k] == -1);
+    if (kd[k] == 1) R[ro + __popcll(mr & below)] = int32_t(base + 64 * k);
+    if (kd[k] == -1) F[fo + __popcll(mf & below)] = int32_t(base + 64 * k);
+    ro += __popcll(mr);
+    fo += __popcll(mf);
   }
 }
 
@@ -145,25 +170,38 @@ __device__ inline f32x4 mma6(const bf16x8& a0, const bf16x8& a1, const bf16x8& a
   return acc;
 }
 
-// Refinement.  A block of NC waves takes tiles of 16 refined families; wave c
-// computes child c of all 16 (I_c in registers, the shared parent tile split
-// once into LDS).  The D fragment of lane l holds rows 4*(l/16) + r of a
-// 16-row tile, column l % 16.
+// Refinement.  A persistent block of NC waves takes (tile of 16 refined
+// families, variable) items; wave c computes child c of all 16, I_c staying in
+// its registers over all of the block's items (24 KB a wave: read for each
+// item, the operators were most of the bytes), the shared parent tile split
+// once into LDS.  The D fragment of lane l holds rows 4*(l/16) + r of a 16-row
+// tile, column l % 16.  The item list is read three items ahead, the sources
+// two and the parents' values one, so that no load is waited for where it is
+// issued.  Two barriers an item: the values' LDS is rewritten after the second
+// barrier, when every wave has read it, and the outputs' after the next first
+// one, when every wave has stored from it.  Bound where refined families lie
+// alone between copies: their 64-byte row segments reach memory as partial
+// lines (10 000 scattered families, 5 variables: 154 us alone, 87 with the same
+// bytes stored densely).  One item per block and five barriers took 276 us
+// beside the copy pass, this form 197.
 template <int NC>
 __global__ __launch_bounds__(64 * NC) void k_split_refine(
     const bf16x8* __restrict__ fragI, const double* __restrict__ vec, const int32_t* __restrict__ R,
-    const int64_t* __restrict__ packed, const int32_t* __restrict__ src,
+    const int64_t* __restrict__ count, int nvar, const int32_t* __restrict__ src,
     const double* __restrict__ uo, int64_t ldo, double* __restrict__ un, int64_t ldn) {
+  constexpr int kThreads = 64 * NC;
+  constexpr int kVals = kNP * kTC / kThreads;  // parent values a thread splits
   __shared__ double Bd[kNP][kTC];
-  __shared__ bf16x8 Bf[3][kKS][64];
+  __shared__ __attribute__((aligned(16))) __bf16 Bf[3][kKS][64][8];
   __shared__ double Out[kNP][kTC * NC];
-  __shared__ int32_t s_j0[kTC], s_src[kTC];
+  __shared__ int32_t s_j0[kTC];
   const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
-  const int v = blockIdx.y;
-  const int64_t nR = (*packed) & kLow31;
-  const int64_t ntile = (nR + kTC - 1) / kTC;
-  if (int64_t(blockIdx.x) >= ntile) return;
+  const int cc = threadIdx.x % kTC, k0 = threadIdx.x / kTC;  // this thread's column and first point
+  const int64_t nR = *count;
+  const uint32_t ntile = uint32_t((nR + kTC - 1) / kTC);
+  const uint32_t items = ntile * uint32_t(nvar);
+  if (blockIdx.x >= items) return;
   bf16x8 a[3][kMT][kKS];
 #pragma unroll
   for (int s = 0; s < 3; ++s)
@@ -173,48 +211,54 @@ __global__ __launch_bounds__(64 * NC) void k_split_refine(
       for (int ks = 0; ks < kKS; ++ks) a[s][mt][ks] = fragI[(((c * 3 + s) * kMT + mt) * kKS + ks) * 64 + lane];
   const double* Wn = vec;
   const double* g = vec + kNP + c * kNP;
-  const double* U = uo + int64_t(v) * kNP * ldo;
-  double* O = un + int64_t(v) * kNP * ldn;
-  for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-    if (threadIdx.x < kTC) {
-      const int64_t r = tile * kTC + threadIdx.x;
-      int32_t j0 = -1, sp = -1;
-      if (r < nR) {
-        j0 = R[r];
-        sp = src[j0];
-      }
-      s_j0[threadIdx.x] = j0;
-      s_src[threadIdx.x] = sp;
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < kNP * kTC; idx += blockDim.x) {
-      const int k = idx / kTC, cc = idx % kTC;
-      const int32_t sp = s_src[cc];
-      Bd[k][cc] = sp >= 0 ? U[int64_t(k) * ldo + sp] : 0.0;
-    }
-    __syncthreads();
-    if (threadIdx.x < kKS * 64) {
-      const int ks = threadIdx.x >> 6, l = threadIdx.x & 63;
-      bf16x8 b0, b1, b2;
+  // items run variable by variable, so that a variable's rows stay near each
+  // other; past the end the last item again (never used), and columns past the
+  // last family repeat it (same values, same address), so that every lane
+  // loads and stores
+  const uint32_t G = gridDim.x;
+  auto clamped = [&](uint32_t it) { return it < items ? it : items - 1; };
+  auto var_of = [&](uint32_t it) { return int64_t(clamped(it) / ntile); };
+  auto family = [&](uint32_t it) -> int32_t {  // first child of this thread's column
+    const int64_t r = int64_t(clamped(it) % ntile) * kTC + cc;
+    return R[r < nR ? r : nR - 1];
+  };
+  auto values = [&](uint32_t it, int32_t sp, double* x) {
+    const double* U = uo + var_of(it) * kNP * ldo + sp;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        __bf16 x0, x1, x2;
-        split3(Bd[ks * 32 + 8 * (l >> 4) + t][l & 15], x0, x1, x2);
-        b0[t] = x0;
-        b1[t] = x1;
-        b2[t] = x2;
-      }
-      Bf[0][ks][l] = b0;
-      Bf[1][ks][l] = b1;
-      Bf[2][ks][l] = b2;
+    for (int h = 0; h < kVals; ++h) x[h] = U[int64_t(k0 + h * (kThreads / kTC)) * ldo];
+  };
+  uint32_t it = blockIdx.x;
+  int32_t j_0 = family(it), j_1 = family(it + G), j_2 = family(it + 2 * G);
+  int32_t p_1 = src[j_1];
+  double x[kVals];
+  values(it, src[j_0], x);
+  for (; it < items; it += G) {
+    // this item's values, split, and its columns' first children
+#pragma unroll
+    for (int h = 0; h < kVals; ++h) {
+      const int k = k0 + h * (kThreads / kTC);
+      Bd[k][cc] = x[h];
+      __bf16 x0, x1, x2;
+      split3(x[h], x0, x1, x2);
+      const int ks = k >> 5, l = ((k & 31) >> 3) * 16 + cc, t = k & 7;
+      Bf[0][ks][l][t] = x0;
+      Bf[1][ks][l][t] = x1;
+      Bf[2][ks][l][t] = x2;
     }
+    if (threadIdx.x < kTC) s_j0[threadIdx.x] = j_0;
+    // the next items' loads, in flight over this item's products
+    values(it + G, p_1, x);
+    const int32_t p_2 = src[j_2];
+    const int32_t j_3 = family(it + 3 * G);
     __syncthreads();
     f32x4 acc[kMT];
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
-      const bf16x8 b0 = Bf[0][ks][lane], b1 = Bf[1][ks][lane], b2 = Bf[2][ks][lane];
+      const bf16x8 b0 = *reinterpret_cast<const bf16x8*>(Bf[0][ks][lane]);
+      const bf16x8 b1 = *reinterpret_cast<const bf16x8*>(Bf[1][ks][lane]);
+      const bf16x8 b2 = *reinterpret_cast<const bf16x8*>(Bf[2][ks][lane]);
 #pragma unroll
       for (int mt = 0; mt < kMT; ++mt)
         acc[mt] = mma6(a[0][mt][ks], a[1][mt][ks], a[2][mt][ks], b0, b1, b2, acc[mt]);
@@ -236,35 +280,40 @@ __global__ __launch_bounds__(64 * NC) void k_split_refine(
     for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) Out[mt * 16 + 4 * grp + r][col * NC + c] = double(acc[mt][r]) + delta;
+    const int32_t jo = s_j0[(threadIdx.x % (kTC * NC)) / NC];  // read before the next item's are written
     __syncthreads();
-    for (int idx = threadIdx.x; idx < kNP * kTC * NC; idx += blockDim.x) {
-      const int row = idx / (kTC * NC), q = idx % (kTC * NC);
-      const int32_t j0 = s_j0[q / NC];
-      if (j0 >= 0) O[int64_t(row) * ldn + j0 + (q % NC)] = Out[row][q];
-    }
-    __syncthreads();
+    const int q = threadIdx.x % (kTC * NC), r0 = threadIdx.x / (kTC * NC);
+    double* O = un + var_of(it) * kNP * ldn + jo + (q % NC);
+    constexpr int kStep = kThreads / (kTC * NC);  // rows a block stores at once
+#pragma unroll
+    for (int i = 0; i < kNP / kStep; ++i) O[int64_t(r0 + i * kStep) * ldn] = Out[r0 + i * kStep][q];
+    j_0 = j_1;
+    j_1 = j_2;
+    j_2 = j_3;
+    p_1 = p_2;
   }
 }
 
-// Coarsening.  A block of NC waves takes tiles of 16 fused parents; wave c
-// multiplies P_c by the values of child c (split in registers); the partial
-// results are summed over the children through LDS.
+// Coarsening.  A persistent block of NC waves takes (tile of 16 fused parents,
+// variable) items; wave c multiplies P_c by the values of child c (split in
+// registers); the partial results are summed over the children through LDS.
+// Lists, sources and values are read ahead as in the refinement.
 template <int NC>
 __global__ __launch_bounds__(64 * NC) void k_split_fuse(
     const bf16x8* __restrict__ fragP, const double* __restrict__ vec, const int32_t* __restrict__ F,
-    const int64_t* __restrict__ packed, const int32_t* __restrict__ src,
+    const int64_t* __restrict__ count, int nvar, const int32_t* __restrict__ src,
     const double* __restrict__ uo, int64_t ldo, double* __restrict__ un, int64_t ldn) {
+  constexpr int kThreads = 64 * NC;
+  constexpr int kVals = kNP * kTC / kThreads;
   __shared__ float Part[NC][kNP][kTC];
   __shared__ double Mc[NC][kTC];
-  __shared__ double Osum[kNP][kTC];
-  __shared__ double Shift[kTC];
-  __shared__ int32_t s_j[kTC], s_src[kTC];
+  __shared__ double Ms[NC][kTC];
   const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
-  const int v = blockIdx.y;
-  const int64_t nF = (*packed) >> 31;
-  const int64_t ntile = (nF + kTC - 1) / kTC;
-  if (int64_t(blockIdx.x) >= ntile) return;
+  const int64_t nF = *count;
+  const uint32_t ntile = uint32_t((nF + kTC - 1) / kTC);
+  const uint32_t items = ntile * uint32_t(nvar);
+  if (blockIdx.x >= items) return;
   bf16x8 a[3][kMT][kKS];
 #pragma unroll
   for (int s = 0; s < 3; ++s)
@@ -273,28 +322,27 @@ __global__ __launch_bounds__(64 * NC) void k_split_fuse(
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks) a[s][mt][ks] = fragP[(((c * 3 + s) * kMT + mt) * kKS + ks) * 64 + lane];
   const double* Wn = vec;
-  const double* U = uo + int64_t(v) * kNP * ldo;
-  double* O = un + int64_t(v) * kNP * ldn;
-  for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-    if (threadIdx.x < kTC) {
-      const int64_t r = tile * kTC + threadIdx.x;
-      int32_t j = -1, sp = -1;
-      if (r < nF) {
-        j = F[r];
-        sp = src[j];
-      }
-      s_j[threadIdx.x] = j;
-      s_src[threadIdx.x] = sp;
-    }
-    __syncthreads();
-    const int32_t sp = s_src[col];
-    const bool live = sp >= 0;
-    // Rows 8*grp + 32*ks + t of child c.  A padding column (sp < 0) reads
-    // column c instead and discards it: a tile exists only when some parent
-    // fuses, so the old mesh holds at least 2^d elements.  The per-row offsets
-    // are wave-uniform, and one lane address per tile keeps the split
-    // operator (96 registers) and the values in registers without scratch.
-    const double* Ucol = U + int64_t(8 * grp) * ldo + (live ? sp : 0) + c;
+  const uint32_t G = gridDim.x;
+  auto clamped = [&](uint32_t it) { return it < items ? it : items - 1; };
+  auto var_of = [&](uint32_t it) { return int64_t(clamped(it) / ntile); };
+  auto parent = [&](uint32_t it) -> int32_t {  // the lane's column; past the last parent that one again
+    const int64_t r = int64_t(clamped(it) % ntile) * kTC + col;
+    return F[r < nF ? r : nF - 1];
+  };
+  // rows 32*ks + 8*grp + t of child c
+  auto values = [&](uint32_t it, int32_t sp, double* x) {
+    const double* U = uo + (var_of(it) * kNP + 8 * grp) * ldo + sp + c;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[8 * ks + t] = U[int64_t(ks * 32 + t) * ldo];
+  };
+  uint32_t it = blockIdx.x;
+  int32_t j_0 = parent(it), j_1 = parent(it + G), j_2 = parent(it + 2 * G);
+  int32_t p_1 = src[j_1];
+  double x[8 * kKS];
+  values(it, src[j_0], x);
+  for (; it < items; it += G) {
     double mpart = 0.0;
     f32x4 acc[kMT];
 #pragma unroll
@@ -304,12 +352,10 @@ __global__ __launch_bounds__(64 * NC) void k_split_fuse(
       bf16x8 b0, b1, b2;
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
-        const int k = ks * 32 + 8 * grp + t;
-        const double xr = Ucol[int64_t(ks * 32 + t) * ldo];
-        const double x = live ? xr : 0.0;
-        mpart += Wn[k] * x;
+        const double xr = x[8 * ks + t];
+        mpart += Wn[ks * 32 + 8 * grp + t] * xr;
         __bf16 x0, x1, x2;
-        split3(x, x0, x1, x2);
+        split3(xr, x0, x1, x2);
         b0[t] = x0;
         b1[t] = x1;
         b2[t] = x2;
@@ -319,6 +365,10 @@ __global__ __launch_bounds__(64 * NC) void k_split_fuse(
         acc[mt] = mma6(a[0][mt][ks], a[1][mt][ks], a[2][mt][ks], b0, b1, b2, acc[mt]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    // the next items' loads, in flight over the sums below
+    values(it + G, p_1, x);
+    const int32_t p_2 = src[j_2];
+    const int32_t j_3 = parent(it + 3 * G);
     mpart += __shfl_xor(mpart, 16, 64);
     mpart += __shfl_xor(mpart, 32, 64);
     if (grp == 0) Mc[c][col] = mpart;
@@ -327,27 +377,39 @@ __global__ __launch_bounds__(64 * NC) void k_split_fuse(
 #pragma unroll
       for (int r = 0; r < 4; ++r) Part[c][mt * 16 + 4 * grp + r][col] = acc[mt][r];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < kNP * kTC; idx += blockDim.x) {
-      const int row = idx / kTC, cc = idx % kTC;
-      double sum = 0.0;
+    // sums over the children, one column and kVals rows a thread, and their
+    // means: over the wave's rows, then over the waves
+    const int cc = threadIdx.x % kTC;
+    double sum[kVals], ms = 0.0;
 #pragma unroll
-      for (int ch = 0; ch < NC; ++ch) sum += double(Part[ch][row][cc]);
-      Osum[row][cc] = sum;
+    for (int h = 0; h < kVals; ++h) {
+      const int row = threadIdx.x / kTC + h * (kThreads / kTC);
+      sum[h] = 0.0;
+#pragma unroll
+      for (int ch = 0; ch < NC; ++ch) sum[h] += double(Part[ch][row][cc]);
+      ms += Wn[row] * sum[h];
     }
+    ms += __shfl_xor(ms, 16, 64);
+    ms += __shfl_xor(ms, 32, 64);
+    if (grp == 0) Ms[c][col] = ms;
     __syncthreads();
-    if (threadIdx.x < kTC) {
-      double ms = 0.0, mf = 0.0;
-      for (int row = 0; row < kNP; ++row) ms += Wn[row] * Osum[row][threadIdx.x];
-      for (int ch = 0; ch < NC; ++ch) mf += Mc[ch][threadIdx.x];
-      Shift[threadIdx.x] = mf / NC - ms;
+    double mf = 0.0, mt = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < NC; ++ch) {
+      mf += Mc[ch][cc];
+      mt += Ms[ch][cc];
     }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < kNP * kTC; idx += blockDim.x) {
-      const int row = idx / kTC, cc = idx % kTC;
-      const int32_t j = s_j[cc];
-      if (j >= 0) O[int64_t(row) * ldn + j] = Osum[row][cc] + Shift[cc];
-    }
-    __syncthreads();
+    const double shift = mf / NC - mt;
+    // this thread's column is its lane's: its parent is j_0
+    double* O = un + var_of(it) * kNP * ldn + j_0;
+#pragma unroll
+    for (int h = 0; h < kVals; ++h)
+      O[int64_t(threadIdx.x / kTC + h * (kThreads / kTC)) * ldn] = sum[h] + shift;
+    __syncthreads();  // the sums' LDS is read before the next item writes it
+    j_0 = j_1;
+    j_1 = j_2;
+    j_2 = j_3;
+    p_1 = p_2;
   }
 }
 
@@ -402,32 +464,42 @@ lt_status launch_split_transfer(lt_tree_s* t, Count cn, int p, int nvar, const d
   const bf16x8* fP = fr + size_t(nc) * 3 * kMT * kKS * 64;
   // The copy pass writes only copies and the refinement and fusion passes
   // only refined and fused elements: the latter run on the tree's second
-  // stream beside the copy pass, forked after it is enqueued and joined back.
+  // stream beside the copy pass, forked before it is enqueued and joined back;
+  // the work lists before the fork or after it (lists_first).
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
   LT_TRY_STATUS(transfer_side(t, &side, &fork, &join));
+  int64_t *nR = &t->dctr->total, *nF = &t->dctr->nfgroups;
+  auto lists = [&](hipStream_t q) -> lt_status {
+    LT_TRY_STATUS(clear_counters(t->dctr, q));
+    k_split_lists<<<unsigned((n + kTileMin - 1) / kTileMin), kBlock, 0, q>>>(t->map_kind, cn, t->split_R, nR,
+                                                                           t->split_F, nF);
+    return LT_OK;
+  };
+  if (lists_first(n)) LT_TRY_STATUS(lists(s));
   hipError_t ef = hipEventRecord(fork, s);
   if (ef != hipSuccess) return fail(LT_ERR_HIP, std::string("split transfer fork: ") + hipGetErrorString(ef));
   lt_status r = launch_copy(t, cn, int64_t(nvar) * kNP, u_old, ld_old, u_new, ld_new, s);
   ef = hipStreamWaitEvent(side, fork, 0);
-  ScanState st;
-  if (r == LT_OK && ef == hipSuccess) r = prep_scan(t, n, kTileMin, side, 0, &st);
+  if (r == LT_OK && ef == hipSuccess && !lists_first(n)) r = lists(side);
   if (r == LT_OK && ef == hipSuccess) {
-    st.items.p = cn.p;
-    k_split_lists<<<grid_tiles(st), kScanSmall, 0, side>>>(t->map_kind, t->split_R, t->split_F, st);
-    const int64_t max_ref_tiles = (n / nc + kTC - 1) / kTC + 1;
-    const int64_t max_fuse_tiles = (n + kTC - 1) / kTC + 1;
-    const dim3 gr(unsigned(std::min<int64_t>(max_ref_tiles, 2048)), unsigned(nvar));
-    const dim3 gf(unsigned(std::min<int64_t>(max_fuse_tiles, 512)), unsigned(nvar));
+    const int64_t max_ref = ((n / nc + kTC - 1) / kTC + 1) * nvar;
+    const int64_t max_fuse = ((n + kTC - 1) / kTC + 1) * nvar;
+    // persistent: one workgroup of 8 waves per compute unit (the operator
+    // takes 96 registers a wave), or two of 4
+    const int64_t slots = nc == 8 ? 256 : 512;
+    const unsigned gr = unsigned(std::min(max_ref, slots)), gf = unsigned(std::min(max_fuse, slots));
+    // a short copy pass ends before the refinement: the fusion follows it
+    hipStream_t fs = lists_first(n) ? s : side;
     if (nc == 8) {
-      k_split_refine<8><<<gr, 512, 0, side>>>(fI, t->split_vec, t->split_R, st.total, t->map_src, u_old,
+      k_split_refine<8><<<gr, 512, 0, side>>>(fI, t->split_vec, t->split_R, nR, nvar, t->map_src, u_old,
                                               ld_old, u_new, ld_new);
-      k_split_fuse<8><<<gf, 512, 0, side>>>(fP, t->split_vec, t->split_F, st.total, t->map_src, u_old,
+      k_split_fuse<8><<<gf, 512, 0, fs>>>(fP, t->split_vec, t->split_F, nF, nvar, t->map_src, u_old,
                                             ld_old, u_new, ld_new);
     } else {
-      k_split_refine<4><<<gr, 256, 0, side>>>(fI, t->split_vec, t->split_R, st.total, t->map_src, u_old,
+      k_split_refine<4><<<gr, 256, 0, side>>>(fI, t->split_vec, t->split_R, nR, nvar, t->map_src, u_old,
                                               ld_old, u_new, ld_new);
-      k_split_fuse<4><<<gf, 256, 0, side>>>(fP, t->split_vec, t->split_F, st.total, t->map_src, u_old,
+      k_split_fuse<4><<<gf, 256, 0, fs>>>(fP, t->split_vec, t->split_F, nF, nvar, t->map_src, u_old,
                                             ld_old, u_new, ld_new);
     }
   }

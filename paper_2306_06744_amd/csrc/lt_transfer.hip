@@ -240,7 +240,9 @@ __global__ __launch_bounds__(256) void k_copy_chunks(const int32_t* __restrict__
 // Copy pass (COPY elements).  One block moves one point row (variable v,
 // point i) of one chunk: 256 lanes x EPL elements.  Pure chunks read one
 // offset and move the row like a plain copy (16-byte pairs for EPL >= 2);
-// impure chunks read the map per element and move only the copy elements.
+// impure chunks read the map per element and move only the copy elements, one
+// block in IR taking IR rows: the map is read once for them and their loads
+// are in flight together.
 // SKIP: a wave leaves out its 64 elements (one interpolation group) when any
 // of them is refined or fused -- the interpolation passes then write the
 // group's copies too, so that every row segment of a group is written whole
@@ -248,7 +250,16 @@ __global__ __launch_bounds__(256) void k_copy_chunks(const int32_t* __restrict__
 // Source loads and output stores are streaming (non-temporal): every copied
 // value is touched once, and keeping it out of the caches was measured ~2.5%
 // faster for the whole transfer.
-template <int EPL, bool SKIP>
+// IR: eight rows up to 2^18 new leaves, where changed leaves make many chunks
+// impure and the arrays are mostly cached (320 rows of 117 000 leaves, two
+// thirds of them refined, nearly every chunk impure: 150 -> 119 us beside the
+// refinement); one row beyond, where nearly all chunks are pure and blocks that
+// walk distant rows disturb the streaming ones (1.9M leaves, p = 3: the cycle
+// 2034 us with one row, 2073, 2095 and 2149 with 2, 4 and 8).
+constexpr int kImpureRows = 8;
+constexpr int64_t kImpureLeaves = int64_t(1) << 18;
+
+template <int EPL, bool SKIP, int IR>
 __global__ __launch_bounds__(256) void k_copy3(const int32_t* __restrict__ src,
                                                const int8_t* __restrict__ kind, Count cn,
                                                const int64_t* __restrict__ cdelta,
@@ -280,12 +291,22 @@ __global__ __launch_bounds__(256) void k_copy3(const int32_t* __restrict__ src,
       }
       continue;
     }
+    if (blockIdx.y % IR) continue;
+    const int rows = std::min<int>(IR, int(gridDim.y - blockIdx.y));
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
       const int64_t jj = c * CH + int64_t(e) * 256 + threadIdx.x;
-      const int kd = jj < n ? int(kind[jj]) : 0;
-      if (SKIP && __ballot(kd != 0) != 0) continue;  // an interpolation group
-      if (jj < n && kd == 0) __builtin_nontemporal_store(__builtin_nontemporal_load(U + src[jj]), O + jj);
+      const int kd = jj < n ? int(kind[jj]) : 1;
+      if (SKIP && __ballot(jj < n && kd != 0) != 0) continue;  // an interpolation group
+      if (kd != 0) continue;
+      const double* p = U + src[jj];
+      double x[IR];
+#pragma unroll
+      for (int r = 0; r < IR; ++r)
+        if (r < rows) x[r] = __builtin_nontemporal_load(p + int64_t(r) * ldo);
+#pragma unroll
+      for (int r = 0; r < IR; ++r)
+        if (r < rows) __builtin_nontemporal_store(x[r], O + int64_t(r) * ldn + jj);
     }
   }
 }
@@ -988,8 +1009,9 @@ __global__ __launch_bounds__(256) void k_copy3_mixed(const int32_t* __restrict__
 // Scratch of one FP64 transfer, sized for n new leaves: per copy chunk the
 // source offset of a pure copy run (ceil(n / 256) entries at the finest
 // tuning), the interpolation-group lists (the groups with refined elements
-// only, then those holding a fused one: 2 ceil(n / 64)) and counters.  From the tree's buffers (lt_transfer) or
-// from the library's static array (lt_transfer_noalloc).
+// only, then those holding a fused one: 2 ceil(n / 64)) and counters.  From
+// the tree's buffers (lt_transfer) or from the library's static array
+// (lt_transfer_noalloc).
 struct XferScratch {
   int64_t* copy_delta;
   int32_t* grp_list;
@@ -1019,6 +1041,20 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     // copy is enqueued first, so that its start waits on no host call of
     // the fork.
     hipStream_t si = s;
+    // grp_list holds the groups of refined elements in [0, ngroups) and those
+    // with a fused element in [ngroups, 2 ngroups)
+    int32_t* flist = X.grp_list + ngroups;
+    auto lists = [&](hipStream_t q) -> lt_status {
+      LT_TRY_STATUS(clear_counters(X.ctr, q));
+      k_group_list<false><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, q>>>(
+          KeyGeom{}, nullptr, nullptr, kind, n, X.grp_list, &X.ctr->total, flist, &X.ctr->nfgroups);
+      return LT_OK;
+    };
+    const bool first = X.side && lists_first(n.n);
+    if (first) {
+      *st_out = lists(s);
+      if (*st_out != LT_OK) return e;
+    }
     if (X.side) {
       e = hipEventRecord(X.fork, s);
       if (e != hipSuccess) return e;
@@ -1026,13 +1062,8 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     }
     *st_out = copy_pass(tune, src, kind, n, nvar * N * N * N, uo, ldo, un, ldn, X.copy_delta, true, s);
     if (X.side) e = hipStreamWaitEvent(X.side, X.fork, 0);
-    // grp_list holds the groups of refined elements in [0, ngroups) and those
-    // with a fused element in [ngroups, 2 ngroups)
-    if (*st_out == LT_OK && e == hipSuccess) *st_out = clear_counters(X.ctr, si);
+    if (*st_out == LT_OK && e == hipSuccess && !first) *st_out = lists(si);
     if (*st_out == LT_OK && e == hipSuccess) {
-      int32_t* flist = X.grp_list + ngroups;
-      k_group_list<false><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, si>>>(
-          KeyGeom{}, nullptr, nullptr, kind, n, X.grp_list, &X.ctr->total, flist, &X.ctr->nfgroups);
       const dim3 gi{unsigned(std::max<int64_t>(1, std::min<int64_t>(ngroups, tune.interp_grid))),
                     unsigned(nvar), 1u};
       // the buffer form takes N*N rows of either array by a 32-bit offset
@@ -1082,13 +1113,21 @@ lt_status copy_pass(const TransferTune& tune, const int32_t* src, const int8_t* 
   const int64_t nlaunch =
       n.hint > 0 ? std::max<int64_t>(1, std::min(nchunks, (n.hint + n.hint / 32 + CH - 1) / CH)) : nchunks;
   const dim3 grid{unsigned(nlaunch), unsigned(rows), 1u};
+#define LT_COPY_IR(E, SKIP)                                                                       \
+  do {                                                                                          \
+    if (n.n <= kImpureLeaves)                                                                   \
+      k_copy3<E, SKIP, kImpureRows>                                                             \
+          <<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);                    \
+    else                                                                                        \
+      k_copy3<E, SKIP, 1><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);     \
+  } while (0)
 #define LT_COPY(E)                                                                              \
   do {                                                                                          \
     k_copy_chunks<E><<<unsigned(nchunks), 256, 0, s>>>(src, kind, n, copy_delta);               \
     if (skip_groups)                                                                            \
-      k_copy3<E, true><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);        \
+      LT_COPY_IR(E, true);                                                                      \
     else                                                                                        \
-      k_copy3<E, false><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);       \
+      LT_COPY_IR(E, false);                                                                     \
   } while (0)
   if (epl == 1)
     LT_COPY(1);
@@ -1097,6 +1136,7 @@ lt_status copy_pass(const TransferTune& tune, const int32_t* src, const int8_t* 
   else
     LT_COPY(2);
 #undef LT_COPY
+#undef LT_COPY_IR
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LT_ERR_HIP, std::string("copy pass launch: ") + hipGetErrorString(e));
   return LT_OK;
