@@ -371,6 +371,13 @@ __global__ __launch_bounds__(kScanBig) void k_adapt(KeyGeom g, const uint64_t* _
   if (err) atomicOr(st.err, err);
 }
 
+// Orders one wave's LDS writes before its later reads by other lanes.
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 2:1 balance, marking pass.  For a leaf L of depth D with parent P, the
 // leaves that touch L and are two or more levels coarser are exactly the
 // leaves strictly containing one of the 2^dim - 1 depth-(D-1) neighbours of P
@@ -378,41 +385,87 @@ __global__ __launch_bounds__(kScanBig) void k_adapt(KeyGeom g, const uint64_t* _
 // restricted to face / face+edge neighbours for the weaker balance kinds.
 // Such a leaf gets bit 0 (split); L gets bit 1 (check again next pass).
 // Only leaves with bit 2 (new or re-checked) are examined unless check_all.
-template <int DIM>
+//
+// Not every searching key is searched:
+//  - a neighbour of P with P's own parent is a sibling of P, so no leaf
+//    strictly contains it;
+//  - siblings of L that share the face (edge) of P ask for the same neighbour;
+//    the first of them in Morton order asks for all (child index within the
+//    key's axes).  Where that sibling is itself subdivided, its leaf at the
+//    same corner asks for a smaller octant inside that neighbour, which the
+//    same coarse leaf contains.
+// That leaves 19 of 56 searches per family in 3D on average.  A wave lists its
+// PER leaves' searches in LDS and takes them 64 at a time, so that lanes
+// without one cost nothing: 64 leaves where every leaf is examined (about three
+// rounds of searches), 16 of a list, which is short enough that one round each
+// on more waves ends sooner.
+// Bound: latency of the directory and key reads.  The passes of a tree built
+// from 1M points (five, the first over every leaf): 340 us (155 the first)
+// against 552 with a lane per leaf and key, searched or not.
+template <int DIM, int PER>
 __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64_t* __restrict__ keys,
                                                          Count cn, KeyDir D, uint32_t* mark,
                                                          int check_all, DevCtr* ctr,
                                                          const unsigned* conv,
                                                          const int32_t* __restrict__ elist,
                                                          int64_t ecap) {
-  // 2^DIM lanes per leaf, lane `sub` (1 .. 2^DIM - 1) probes one searching key;
-  // waves stride over the (leaf, sub) pairs: every leaf (check_all), or the
-  // listed leaves (elist: ctr->nexam entries, the leaves holding bit 2).
-  // `conv` (captured cycles): the fixpoint was already reached, nothing to
-  // examine.
+  // waves stride over the leaves: every one (check_all), or the listed ones
+  // (elist: ctr->nexam entries, the leaves holding bit 2).  `conv` (captured
+  // cycles): the fixpoint was already reached, nothing to examine.
   if (conv && *conv) return;
-  constexpr int SL = 1 << DIM;
+  constexpr int NC = 1 << DIM, kWaves = kBlock / 64;
+  __shared__ uint64_t s_key[kWaves][PER];
+  __shared__ int32_t s_idx[kWaves][PER];
+  __shared__ uint16_t s_task[kWaves][PER * (NC - 1)];
   const int64_t n = cn.get();
   const int64_t items = elist ? min(ctr->nexam, ecap) : n;
-  const int64_t lanes = items * SL;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
   unsigned long long nfresh = 0;
-  for (int64_t wb = int64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63); wb < lanes;
-       wb += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t tid = wb + lane;
-    const int64_t it = tid / SL;
-    const int64_t i = elist ? (it < items ? int64_t(elist[it]) : -1) : it;
-    const int sub = int(tid % SL);
-    bool viol = false, fresh = false;
-    if (i >= 0 && i < n && sub != 0 && __popc(unsigned(sub)) <= limit &&
-        (check_all || (mark[i] & 4u))) {
-      const uint64_t key = keys[i];
+  for (int64_t wb = (int64_t(blockIdx.x) * kWaves + wv) * PER; wb < items; wb += int64_t(gridDim.x) * kWaves * PER) {
+    const int64_t it = lane < PER ? wb + lane : items;
+    const int64_t i = it < items ? (elist ? int64_t(elist[it]) : it) : -1;
+    unsigned need = 0;  // bit sub: the neighbour across the axes of `sub` is searched
+    uint64_t key = 0;
+    if (i >= 0 && i < n && (check_all || (mark[i] & 4u))) {
+      key = keys[i];
       const int d = key_depth(g, key);
       if (d >= 2) {
+        const uint64_t m = key_m(g, key);
+        const unsigned c = child_index(g, m, d), cp = child_index(g, m, d - 1);
+        const unsigned cross = ~(c ^ cp);  // axes on which P's neighbour leaves P's parent
+#pragma unroll
+        for (unsigned sub = 1; sub < unsigned(NC); ++sub)
+          if (__popc(sub) <= limit && (c & sub) == c && (sub & cross) != 0) need |= 1u << sub;
+      }
+    }
+    if (lane < PER) {
+      s_key[wv][lane] = key;
+      s_idx[wv][lane] = int32_t(i);
+    }
+    // the wave's searches, listed by lane
+    int at = __popc(need), total = at;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(total, o, 64);
+      if (lane >= o) total += y;
+    }
+    at = total - at;
+    total = __shfl(total, 63);
+#pragma unroll
+    for (unsigned sub = 1; sub < unsigned(NC); ++sub)
+      if ((need >> sub) & 1u) s_task[wv][at++] = uint16_t(lane * NC + sub);
+    wave_lds_fence();
+    for (int t = lane; t < ((total + 63) & ~63); t += 64) {
+      bool fresh = false;
+      if (t < total) {
+        const int w = s_task[wv][t];
+        const int l = w / NC, sub = w % NC;
+        const uint64_t k = s_key[wv][l];
+        const int d = key_depth(g, k);
         uint64_t x[3];
-        demorton(g, key_morton(g, key), x);
-        const uint64_t mhi = key_mesh_bits(g, key) >> g.mb;
+        demorton(g, key_morton(g, k), x);
+        const uint64_t mhi = key_mesh_bits(g, k) >> g.mb;
         const uint64_t S = uint64_t(1) << (g.dmax - d + 1);  // parent size
         uint64_t q[3] = {0, 0, 0};
         bool ok = true;
@@ -428,35 +481,53 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
         if (ok) {
           const int64_t j = dir_last_le(keys, n, D, point_key(g, morton(g, q) | mhi));
           if (j >= 0 && key_depth(g, keys[j]) < d - 1) {
-            const uint32_t was = atomicOr(&mark[j], 1u);
-            fresh = !(was & 1u);
-            viol = true;
+            fresh = !(atomicOr(&mark[j], 1u) & 1u);
+            atomicOr(&mark[s_idx[wv][l]], 2u);
           }
         }
       }
+      nfresh += __popcll(__ballot(fresh));
     }
-    const uint64_t vb = __ballot(viol);
-    const uint64_t fb = __ballot(fresh);
-    if (sub == 0 && i >= 0 && i < n && ((vb >> lane) & ((uint64_t(1) << SL) - 1)))
-      atomicOr(&mark[i], 2u);
-    nfresh += __popcll(fb);
+    wave_lds_fence();  // the lists are read before the next leaves overwrite them
   }
   if (lane == 0 && nfresh) atomicAdd(&ctr->nmarked, nfresh);
 }
 
+constexpr int kMarkList = 16;  // listed leaves a wave takes at a time
+
+// A marking pass over every leaf (elist null) or the listed ones; `leaves`
+// bounds their number.
+void launch_balance_mark(const KeyGeom& g, const uint64_t* keys, Count cn, int64_t leaves, const KeyDir& D,
+                         uint32_t* mark, DevCtr* ctr, const unsigned* conv, const int32_t* elist,
+                         int64_t ecap, hipStream_t s) {
+  const int per = (elist ? kMarkList : 64) * (kBlock / 64);  // leaves a block takes at a time
+  const int64_t full = ceil_div(leaves, per);
+  const unsigned blocks = unsigned(elist ? std::min<int64_t>(full, kMarkGrid) : full);
+#define LT_MARK(DIM, PER, ALL) \
+  k_balance_mark<DIM, PER><<<blocks, kBlock, 0, s>>>(g, keys, cn, D, mark, ALL, ctr, conv, elist, ecap)
+  if (g.dim == 3) {
+    if (elist) LT_MARK(3, kMarkList, 0); else LT_MARK(3, 64, 1);
+  } else {
+    if (elist) LT_MARK(2, kMarkList, 0); else LT_MARK(2, 64, 1);
+  }
+#undef LT_MARK
+}
+
 // 2:1 balance after adaptation, fused parents.  A parent P (depth D) that
 // replaced 2^dim balanced leaves can touch leaves of depth D+2 (never deeper,
-// never coarser than D-1 -- the leaves it replaced were balanced); those sit
-// in the shell of depth-(D+2) cells around P.  Adapt lists the fused parents
-// (any order, count ctr->nfused); one lane per (parent, shell cell) -- per the
-// balance kind, cells across faces only, or also edges, or also corners --
-// probes its cell and marks P for splitting on a depth-(D+2) leaf.
+// never coarser than D-1 -- the leaves it replaced were balanced).  Such a leaf
+// sits in a depth-(D+1) octant touching P, and any such octant that is
+// subdivided has a child touching P: one lane per (parent, depth-(D+1) cell of
+// the shell around it) -- per the balance kind, cells across faces only, or
+// also edges, or also corners -- looks whether its cell is subdivided, and marks
+// P for splitting then.  Adapt lists the fused parents (any order, count
+// ctr->nfused).
 template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_fused_probe(KeyGeom g, const uint64_t* __restrict__ keys,
                                                         Count cn, KeyDir D,
                                                         const int32_t* __restrict__ list, uint32_t* mark,
                                                         DevCtr* ctr) {
-  constexpr int W = 6;  // cells per axis around P: -1 .. 4 in units of a depth-(D+2) cell
+  constexpr int W = 4;  // cells per axis around P: -1 .. 2 in units of a depth-(D+1) cell
   constexpr int NCELL = DIM == 3 ? W * W * W : W * W;
   const int64_t n = cn.get();
   const int64_t work = int64_t(ctr->nfused) * NCELL;
@@ -467,7 +538,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_probe(KeyGeom g, const uint64_
     const int cidx = int(t % NCELL);
     const int off[3] = {cidx % W - 1, (cidx / W) % W - 1, DIM == 3 ? cidx / (W * W) - 1 : 0};
     int outside = 0;
-    for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 3) ? 1 : 0;
+    for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
     if (outside == 0 || outside > limit || i < 0 || i >= n) continue;
     const uint64_t key = keys[i];
     const int d = key_depth(g, key);
@@ -475,10 +546,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_probe(KeyGeom g, const uint64_
     uint64_t x[3];
     demorton(g, key_morton(g, key), x);
     const uint64_t mhi = key_mesh_bits(g, key) >> g.mb;
-    const int64_t q4 = int64_t(1) << (g.dmax - d - 2);
+    const int64_t half = int64_t(1) << (g.dmax - d - 1);
     uint64_t q[3] = {x[0], x[1], x[2]};
     bool ok = true;
-    for (int a = 0; a < DIM && ok; ++a) ok = shift_coord(g, a, x[a], int64_t(off[a]) * q4, &q[a]);
+    for (int a = 0; a < DIM && ok; ++a) ok = shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
     if (!ok) continue;
     const int64_t j = dir_last_le(keys, n, D, point_key(g, morton(g, q) | mhi));
     if (j >= 0 && key_depth(g, keys[j]) >= d + 2) {
@@ -860,12 +931,6 @@ __device__ inline void wave_lower_bound2(const uint64_t* __restrict__ keys, int6
   *rb = __shfl(r, 32);
 }
 
-__device__ inline void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // A wave maps 64 consecutive new keys.  Their lower bounds lie between those
 // of the wave's first and last key, found by one cooperative search; the
 // old keys around that range (the case checks read B - 1 and B + 2^d - 1) go
@@ -1162,13 +1227,8 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
     k_build_dir<<<nleaf, 256, 0, s>>>(K[ki], Count{C, &S[0]}, r.dir_shift, r.dir_nb, t->dir, conv);
     if (pass == 0)
       LT_HIP(launch_fused_check(g, K[ki], Count{C, &S[0]}, D, t->mbuf[mi], t->fused, t->dctr, s));
-    const unsigned mgrid = unsigned(std::min<int64_t>(nlanes, kMarkGrid));
-    if (g.dim == 3)
-      k_balance_mark<3><<<mgrid, kBlock, 0, s>>>(g, K[ki], Count{C, &S[0]}, D, t->mbuf[mi], 0,
-                                                 t->dctr, conv, t->elist, t->elist_cap);
-    else
-      k_balance_mark<2><<<mgrid, kBlock, 0, s>>>(g, K[ki], Count{C, &S[0]}, D, t->mbuf[mi], 0,
-                                                 t->dctr, conv, t->elist, t->elist_cap);
+    launch_balance_mark(g, K[ki], Count{C, &S[0]}, C, D, t->mbuf[mi], t->dctr, conv, t->elist, t->elist_cap, s);
+    LT_HIP(hipGetLastError());
     if (pass == r.passes) break;
     // the clear also records convergence, and copies the pass's input count
     // to S[3], where the pass reads it: the last tile commits the new count
@@ -1496,21 +1556,13 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
     KeyDir D;
     LT_TRY(ensure_dir(t, s, &D));
     if (t->n_cur > 0) {
-      const int all = pass == 0 && !restricted ? 1 : 0;
-      // every leaf: one lane per (leaf, searching key); listed leaves: a
-      // bounded grid striding over the device-side list
-      const int64_t full = ceil_div(t->n_cur * t->g.nchild(), kBlock);
-      const unsigned blocks = unsigned(all ? full : std::min<int64_t>(full, kMarkGrid));
+      const bool all = pass == 0 && !restricted;
       const int32_t* el = all ? nullptr : t->elist;
       const Count cn{t->n_cur, nullptr};
       if (pass == 0 && restricted)  // adapt listed the fused parents (the list is sized for its output)
         LT_HIP(launch_fused_check(t->g, t->kbuf[t->cur], cn, D, t->mbuf[mi], t->fused, t->dctr, s));
-      if (t->g.dim == 3)
-        k_balance_mark<3><<<blocks, kBlock, 0, s>>>(t->g, t->kbuf[t->cur], cn, D, t->mbuf[mi], all,
-                                                    t->dctr, nullptr, el, t->elist_cap);
-      else
-        k_balance_mark<2><<<blocks, kBlock, 0, s>>>(t->g, t->kbuf[t->cur], cn, D, t->mbuf[mi], all,
-                                                    t->dctr, nullptr, el, t->elist_cap);
+      launch_balance_mark(t->g, t->kbuf[t->cur], cn, t->n_cur, D, t->mbuf[mi], t->dctr, nullptr, el,
+                          t->elist_cap, s);
       LT_HIP(hipGetLastError());
     }
     LT_TRY(read_ctr(t, s));

@@ -344,6 +344,28 @@ def test_adapt_and_balance_at_tile_edges(dim, depth):
         assert_same_map(g, o, "map")
 
 
+@pytest.mark.parametrize("dim,depth,kind", [(2, 1, 0), (2, 1, 2), (2, 2, 2), (2, 3, 0), (2, 3, 2), (2, 6, 0), (2, 6, 2),
+                                            (3, 1, 0), (3, 1, 1), (3, 1, 2), (3, 2, 0), (3, 2, 1), (3, 2, 2),
+                                            (3, 4, 0), (3, 4, 1), (3, 4, 2)])
+def test_balance_marking_at_list_edges(dim, depth, kind):
+    """The marking passes, whose waves list the searches of 64 leaves (every
+    leaf examined) or 16 (the leaves that adapt and refinement list), from
+    fewer leaves than that to many blocks, with each balance kind: after
+    adaptations of a balanced tree (listed leaves and fused parents) and,
+    three adaptations on without balance, of every leaf."""
+    for periodic in (0, (1 << dim) - 1):
+        g, o = both(dim, 0, depth + 5, depth=depth, periodic_mask=periodic, balance=kind)
+        for c in range(6):
+            print("marking", dim, depth, kind, periodic, c, "leaves", o.size(), flush=True)
+            grow = 0.3 if o.size() < 20000 else 0.02
+            adapt_both(g, o, synth.random_flags(300 + c, o.size(), grow, 0.6))
+            if c == 3 or c == 4:
+                continue
+            g.balance()
+            o.balance()
+            assert_same_tree(g, o, "balance")
+
+
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("depth", [1, 2, 3, 4])
 def test_interpolation_groups_at_list_edges(depth, mixed):
