@@ -371,6 +371,51 @@ __global__ __launch_bounds__(kScanBig) void k_adapt(KeyGeom g, const uint64_t* _
   if (err) atomicOr(st.err, err);
 }
 
+// Radix directory of a sorted key array (see KeyDir): leaf i owns the
+// buckets c with keys[i] <= c << shift < keys[i + 1].  A wave fills those of 64
+// consecutive leaves (lane = leaf i with its key and the next leaf's; every
+// lane calls): spans of up to 64 buckets each by its own lane, longer ones (very
+// coarse leaves) by the whole wave in turn.
+__device__ inline void dir_fill(int64_t i, int64_t n, uint64_t key, uint64_t next, int shift, int64_t nb,
+                                int32_t* __restrict__ d) {
+  const int lane = threadIdx.x & 63;
+  auto ceil_sh = [shift](uint64_t k) -> int64_t {
+    const uint64_t mask = (uint64_t(1) << shift) - 1;
+    return int64_t(k >> shift) + ((k & mask) ? 1 : 0);
+  };
+  int c0 = 0, c1 = 0;
+  if (i < n) {
+    const int64_t b = i + 1 < n ? ceil_sh(next) : nb + 1;
+    c1 = int(b < nb + 1 ? b : nb + 1);
+    const int64_t a = ceil_sh(key);
+    c0 = int(a < c1 ? a : c1);
+    if (i == 0)
+      for (int c = 0; c < c0; ++c) d[c] = -1;
+  }
+  const bool big = c1 - c0 > 64;
+  if (!big)
+    for (int c = c0; c < c1; ++c) d[c] = int32_t(i);
+  for (uint64_t bm = __ballot(big); bm; bm &= bm - 1) {
+    const int l = __ffsll((unsigned long long)bm) - 1;
+    const int a = __builtin_amdgcn_readlane(c0, l), b = __builtin_amdgcn_readlane(c1, l);
+    const int32_t v = int32_t(i) - lane + l;
+    for (int c = a + lane; c < b; c += 64) d[c] = v;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_build_dir(const uint64_t* __restrict__ keys, Count cn,
+                                                   int shift, int64_t nb, int32_t* __restrict__ d,
+                                                   const unsigned* conv) {
+  if (conv && *conv) return;  // captured cycles: keys unchanged since the last build
+  const int64_t n = cn.get();
+  const int lane = threadIdx.x & 63;
+  for (int64_t wb = int64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63); wb < n;
+       wb += int64_t(gridDim.x) * blockDim.x) {
+    const int64_t i = wb + lane;
+    dir_fill(i, n, i < n ? keys[i] : 0, i + 1 < n ? keys[i + 1] : 0, shift, nb, d);
+  }
+}
+
 // Orders one wave's LDS writes before its later reads by other lanes.
 __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -402,6 +447,46 @@ __device__ inline void wave_lds_fence() {
 // Bound: latency of the directory and key reads.  The passes of a tree built
 // from 1M points (five, the first over every leaf): 340 us (155 the first)
 // against 552 with a lane per leaf and key, searched or not.
+
+// Bit sub set: the neighbour of the key's parent across the axes of `sub` is
+// searched (see above); limit: the most axes (balance kind).
+template <int DIM>
+__device__ inline unsigned balance_searches(const KeyGeom& g, uint64_t key, int limit) {
+  constexpr int NC = 1 << DIM;
+  const int d = key_depth(g, key);
+  if (d < 2) return 0;
+  const uint64_t m = key_m(g, key);
+  const unsigned c = child_index(g, m, d), cp = child_index(g, m, d - 1);
+  const unsigned cross = ~(c ^ cp);  // axes on which P's neighbour leaves P's parent
+  unsigned need = 0;
+#pragma unroll
+  for (unsigned sub = 1; sub < unsigned(NC); ++sub)
+    if (__popc(sub) <= limit && (c & sub) == c && (sub & cross) != 0) need |= 1u << sub;
+  return need;
+}
+
+// Search key of that neighbour; false outside a non-periodic domain.
+template <int DIM>
+__device__ inline bool balance_probe(const KeyGeom& g, uint64_t key, int sub, uint64_t* probe) {
+  const int d = key_depth(g, key);
+  uint64_t x[3];
+  demorton(g, key_morton(g, key), x);
+  const uint64_t S = uint64_t(1) << (g.dmax - d + 1);  // parent size
+  uint64_t q[3] = {0, 0, 0};
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) {
+    const uint64_t pa = x[a] & ~(S - 1);
+    q[a] = pa;
+    if ((sub >> a) & 1) {
+      const bool up = (x[a] >> (g.dmax - d)) & 1;
+      ok = ok && shift_coord(g, a, pa, up ? int64_t(S) : -int64_t(S), &q[a]);
+    }
+  }
+  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
+  return ok;
+}
+
 template <int DIM, int PER>
 __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64_t* __restrict__ keys,
                                                          Count cn, KeyDir D, uint32_t* mark,
@@ -425,19 +510,11 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
   for (int64_t wb = (int64_t(blockIdx.x) * kWaves + wv) * PER; wb < items; wb += int64_t(gridDim.x) * kWaves * PER) {
     const int64_t it = lane < PER ? wb + lane : items;
     const int64_t i = it < items ? (elist ? int64_t(elist[it]) : it) : -1;
-    unsigned need = 0;  // bit sub: the neighbour across the axes of `sub` is searched
+    unsigned need = 0;
     uint64_t key = 0;
     if (i >= 0 && i < n && (check_all || (mark[i] & 4u))) {
       key = keys[i];
-      const int d = key_depth(g, key);
-      if (d >= 2) {
-        const uint64_t m = key_m(g, key);
-        const unsigned c = child_index(g, m, d), cp = child_index(g, m, d - 1);
-        const unsigned cross = ~(c ^ cp);  // axes on which P's neighbour leaves P's parent
-#pragma unroll
-        for (unsigned sub = 1; sub < unsigned(NC); ++sub)
-          if (__popc(sub) <= limit && (c & sub) == c && (sub & cross) != 0) need |= 1u << sub;
-      }
+      need = balance_searches<DIM>(g, key, limit);
     }
     if (lane < PER) {
       s_key[wv][lane] = key;
@@ -462,25 +539,10 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
         const int w = s_task[wv][t];
         const int l = w / NC, sub = w % NC;
         const uint64_t k = s_key[wv][l];
-        const int d = key_depth(g, k);
-        uint64_t x[3];
-        demorton(g, key_morton(g, k), x);
-        const uint64_t mhi = key_mesh_bits(g, k) >> g.mb;
-        const uint64_t S = uint64_t(1) << (g.dmax - d + 1);  // parent size
-        uint64_t q[3] = {0, 0, 0};
-        bool ok = true;
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-          const uint64_t pa = x[a] & ~(S - 1);
-          q[a] = pa;
-          if ((sub >> a) & 1) {
-            const bool up = (x[a] >> (g.dmax - d)) & 1;
-            ok = ok && shift_coord(g, a, pa, up ? int64_t(S) : -int64_t(S), &q[a]);
-          }
-        }
-        if (ok) {
-          const int64_t j = dir_last_le(keys, n, D, point_key(g, morton(g, q) | mhi));
-          if (j >= 0 && key_depth(g, keys[j]) < d - 1) {
+        uint64_t probe;
+        if (balance_probe<DIM>(g, k, sub, &probe)) {
+          const int64_t j = dir_last_le(keys, n, D, probe);
+          if (j >= 0 && key_depth(g, keys[j]) < key_depth(g, k) - 1) {
             fresh = !(atomicOr(&mark[j], 1u) & 1u);
             atomicOr(&mark[s_idx[wv][l]], 2u);
           }
@@ -522,47 +584,226 @@ void launch_balance_mark(const KeyGeom& g, const uint64_t* keys, Count cn, int64
 // also edges, or also corners -- looks whether its cell is subdivided, and marks
 // P for splitting then.  Adapt lists the fused parents (any order, count
 // ctr->nfused).
+constexpr int kShellW = 4;  // cells per axis around P: -1 .. 2 in units of a depth-(D+1) cell
+
+// Search key of shell cell cidx around the fused parent; false for a cell the
+// balance kind leaves out, outside a non-periodic domain, or of a parent too
+// deep to touch a leaf two levels finer.
+template <int DIM>
+__device__ inline bool shell_probe(const KeyGeom& g, uint64_t key, int cidx, int limit, uint64_t* probe) {
+  constexpr int W = kShellW;
+  const int off[3] = {cidx % W - 1, (cidx / W) % W - 1, DIM == 3 ? cidx / (W * W) - 1 : 0};
+  int outside = 0;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
+  const int d = key_depth(g, key);
+  if (outside == 0 || outside > limit || d + 2 > g.dmax) return false;
+  uint64_t x[3];
+  demorton(g, key_morton(g, key), x);
+  const int64_t half = int64_t(1) << (g.dmax - d - 1);
+  uint64_t q[3] = {x[0], x[1], x[2]};
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) ok = ok && shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
+  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
+  return ok;
+}
+
 template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_fused_probe(KeyGeom g, const uint64_t* __restrict__ keys,
                                                         Count cn, KeyDir D,
                                                         const int32_t* __restrict__ list, uint32_t* mark,
                                                         DevCtr* ctr) {
-  constexpr int W = 4;  // cells per axis around P: -1 .. 2 in units of a depth-(D+1) cell
-  constexpr int NCELL = DIM == 3 ? W * W * W : W * W;
+  constexpr int NCELL = DIM == 3 ? kShellW * kShellW * kShellW : kShellW * kShellW;
   const int64_t n = cn.get();
   const int64_t work = int64_t(ctr->nfused) * NCELL;
   const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
   for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < work;
        t += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = list[t / NCELL];
-    const int cidx = int(t % NCELL);
-    const int off[3] = {cidx % W - 1, (cidx / W) % W - 1, DIM == 3 ? cidx / (W * W) - 1 : 0};
-    int outside = 0;
-    for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
-    if (outside == 0 || outside > limit || i < 0 || i >= n) continue;
+    if (i < 0 || i >= n) continue;
     const uint64_t key = keys[i];
-    const int d = key_depth(g, key);
-    if (d + 2 > g.dmax) continue;
-    uint64_t x[3];
-    demorton(g, key_morton(g, key), x);
-    const uint64_t mhi = key_mesh_bits(g, key) >> g.mb;
-    const int64_t half = int64_t(1) << (g.dmax - d - 1);
-    uint64_t q[3] = {x[0], x[1], x[2]};
-    bool ok = true;
-    for (int a = 0; a < DIM && ok; ++a) ok = shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
-    if (!ok) continue;
-    const int64_t j = dir_last_le(keys, n, D, point_key(g, morton(g, q) | mhi));
-    if (j >= 0 && key_depth(g, keys[j]) >= d + 2) {
+    uint64_t probe;
+    if (!shell_probe<DIM>(g, key, int(t % NCELL), limit, &probe)) continue;
+    const int64_t j = dir_last_le(keys, n, D, probe);
+    if (j >= 0 && key_depth(g, keys[j]) >= key_depth(g, key) + 2) {
       const uint32_t was = atomicOr(&mark[i], 1u);
       if (!(was & 1u)) atomicAdd(&ctr->nmarked, 1ull);
     }
   }
 }
 
+// Balance of a small tree in one workgroup: keys and marks in LDS, where
+// neighbours are found by bisection, all passes in one launch.  Up to
+// kSmallLeaves leaves (a wave holds kSmallRounds rounds of 64), the result
+// included.  marks: adapt's, or null to examine every leaf.  Writes the error
+// word, the number of balanced leaves to ctr->total, their keys if any leaf was
+// split, and their directory.  Keys that do not fit `out` raise ERR_CAPACITY
+// with their number, a tree that outgrows the workgroup with 0, and leave
+// everything else as it was.
+// Bound: one CU's issue rate and the latency of the LDS searches: 11 000 leaves
+// of a 2D tree, six passes: 85 us (22 the first marking pass, about 6 us of
+// counting, refinement and marking each later one); 800 leaves, three passes:
+// 21 us.  The multi-workgroup passes take 15 to 20 us of kernels and 25 us of
+// host readback each; with them a cycle of those trees took 328 and 254 us, with
+// this 269 and 212.  The limit is the LDS (8 bytes a leaf and its mark).
+constexpr int kSmallRounds = 14;
+constexpr int kSmallLeaves = kScanBig * kSmallRounds;
+
+template <int DIM>
+__global__ __launch_bounds__(kScanBig) void k_balance_small(KeyGeom g, const uint64_t* in, int n,
+                                                          const uint32_t* __restrict__ marks,
+                                                          uint64_t* out, int64_t cap, int shift, int64_t nb,
+                                                          int32_t* __restrict__ dir, DevCtr* ctr) {
+  constexpr int NC = 1 << DIM, kWaves = kScanBig / 64, R = kSmallRounds;
+  constexpr int NCELL = DIM == 3 ? kShellW * kShellW * kShellW : kShellW * kShellW;
+  constexpr int kTasks = 64 + 64 * (NC - 1);  // a wave's pending searches
+  __shared__ uint64_t K[kSmallLeaves];
+  __shared__ uint32_t M[kSmallLeaves / 4];  // a byte per leaf, bits as the marks'
+  __shared__ uint32_t s_task[kWaves][kTasks];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // rounds: as few as the leaves take, so that small trees use every wave
+  int rounds = (n + kScanBig - 1) / kScanBig, first = wv * (64 * rounds) + lane;
+  const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
+  uint8_t* Mb = reinterpret_cast<uint8_t*>(M);
+  auto mark_bits = [&](int i, unsigned bits) { atomicOr(&M[i >> 2], bits << (8 * (i & 3))); };
+  for (int r = 0; r < rounds; ++r) {
+    const int i = first + 64 * r;
+    if (i < n) K[i] = in[i];
+    Mb[i] = i < n ? uint8_t(marks ? marks[i] : 4u) : 0;
+  }
+  __syncthreads();
+  auto find = [&](uint64_t probe) {  // last key <= probe
+    // four ways a step: three reads at once instead of two in a row
+    int lo = 0;
+    for (int step = 1 << ((31 - __clz(n)) & ~1); step > 0; step >>= 2) {
+      const int t1 = lo + step, t2 = t1 + step, t3 = t2 + step;
+      const uint64_t k1 = K[min(t1, n) - 1], k2 = K[min(t2, n) - 1], k3 = K[min(t3, n) - 1];
+      lo += (t1 <= n && k1 <= probe) ? step : 0;
+      lo += (t2 <= n && k2 <= probe) ? step : 0;
+      lo += (t3 <= n && k3 <= probe) ? step : 0;
+    }
+    return lo - 1;
+  };
+  auto search = [&](uint32_t task) {
+    const int i = int(task >> 3);
+    const uint64_t k = K[i];
+    uint64_t probe;
+    if (!balance_probe<DIM>(g, k, int(task & 7u), &probe)) return;
+    const int j = find(probe);
+    if (j >= 0 && key_depth(g, K[j]) < key_depth(g, k) - 1) {
+      mark_bits(j, 1u);
+      mark_bits(i, 2u);
+    }
+  };
+  bool grown = false, full = false;
+  for (;;) {
+    // marking: the waves take 64 leaves in turn (leaves to examine come in
+    // runs), and their searches 64 at a time
+    int pend = 0;
+    for (int w = wv * 64; w < n; w += kScanBig) {
+      const int i = w + lane;
+      const unsigned m = i < n ? Mb[i] : 0;
+      unsigned need = (m & 4u) ? balance_searches<DIM>(g, K[i], limit) : 0;
+      if (__ballot(need != 0)) {
+        int at = __popc(need), upto = at;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(upto, o, 64);
+          if (lane >= o) upto += y;
+        }
+        at = pend + upto - at;
+        pend += __shfl(upto, 63);
+        for (; need; need &= need - 1) s_task[wv][at++] = uint32_t(i) << 3 | uint32_t(__ffs(need) - 1);
+        wave_lds_fence();
+        for (; pend >= 64; pend -= 64) search(s_task[wv][pend - 64 + lane]);
+        wave_lds_fence();
+      }
+      // fused parents (first pass): NCELL lanes each, lane = shell cell
+      for (uint64_t fm = __ballot(m & kMarkFused); fm;) {
+        int f = -1;
+#pragma unroll
+        for (int q = 0; q < 64 / NCELL; ++q) {
+          if (fm && lane / NCELL == q) f = i - lane + __ffsll((unsigned long long)fm) - 1;
+          fm &= fm - 1;
+        }
+        uint64_t probe;
+        if (f >= 0 && shell_probe<DIM>(g, K[f], lane % NCELL, limit, &probe)) {
+          const int j = find(probe);
+          if (j >= 0 && key_depth(g, K[j]) >= key_depth(g, K[f]) + 2) mark_bits(f, 1u);
+        }
+      }
+    }
+    if (lane < pend) search(s_task[wv][lane]);
+    __syncthreads();
+    // refinement, in place: every leaf to registers before any is written
+    uint64_t key[R], one[R], ref[R], chk[R];
+    int n_one = 0, n_ref = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      key[r] = ref[r] = one[r] = chk[r] = 0;
+      if (r >= rounds) continue;
+      const int i = first + 64 * r;
+      const unsigned m = i < n ? Mb[i] : 0;
+      key[r] = i < n ? K[i] : 0;
+      ref[r] = __ballot(m & 1u);
+      one[r] = __ballot(i < n && !(m & 1u));
+      chk[r] = __ballot((m & 3u) == 2u);
+      n_one += __popcll(one[r]);
+      n_ref += __popcll(ref[r]);
+    }
+    WaveOut wo, wr;
+    block_waves(n_ref * NC + n_one, n_ref, &wo, &wr);
+    if (wr.all == 0) break;
+    grown = true;
+    if (wo.all > kSmallLeaves) {
+      n = wo.all;
+      full = true;
+      break;
+    }
+    int o = wo.base;
+    const uint64_t below = lanes_below();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r >= rounds) continue;
+      const int q = o + __popcll(ref[r] & below) * NC + __popcll(one[r] & below);
+      o += __popcll(ref[r]) * NC + __popcll(one[r]);
+      if ((ref[r] >> lane) & 1) {
+        const uint64_t m = key_m(g, key[r]);
+        const int d = key_depth(g, key[r]);
+        for (int c = 0; c < NC; ++c) {
+          K[q + c] = child_key(g, m, d, c);
+          Mb[q + c] = 4;
+        }
+      } else if ((one[r] >> lane) & 1) {
+        K[q] = key[r];
+        Mb[q] = (chk[r] >> lane) & 1 ? 4 : 0;
+      }
+    }
+    n = wo.all;
+    rounds = (n + kScanBig - 1) / kScanBig;
+    first = wv * (64 * rounds) + lane;
+    __syncthreads();
+  }
+  full = full || (grown && n > cap);
+  if (threadIdx.x == 0) {
+    ctr->err = full ? ERR_CAPACITY : 0;
+    ctr->total = n <= kSmallLeaves ? n : 0;
+  }
+  if (full) return;
+  for (int r = 0; r < rounds; ++r) {
+    const int i = first + 64 * r;
+    const uint64_t k = i < n ? K[i] : 0;
+    if (grown && i < n) out[i] = k;
+    dir_fill(i, n, k, i + 1 < n ? K[i + 1] : 0, shift, nb, dir);
+  }
+}
+
 // The fused-parent check of the first balance pass after adaptation.
 hipError_t launch_fused_check(const KeyGeom& g, const uint64_t* keys, Count cn, const KeyDir& D,
                               uint32_t* mark, const int32_t* list, DevCtr* ctr, hipStream_t s) {
-  constexpr int64_t kGrid = 2048;
+  // the list's length is on the device: up to a block per 64 leaves, striding
+  const int64_t kGrid = std::max<int64_t>(1, std::min<int64_t>(1024, cn.n / 64));
   if (g.dim == 3)
     k_fused_probe<3><<<unsigned(kGrid), kBlock, 0, s>>>(g, keys, cn, D, list, mark, ctr);
   else
@@ -570,42 +811,12 @@ hipError_t launch_fused_check(const KeyGeom& g, const uint64_t* keys, Count cn, 
   return hipGetLastError();
 }
 
-// Radix directory of a sorted key array (see KeyDir): leaf i owns the
-// buckets c with keys[i] <= c << shift < keys[i + 1].  Short spans are
-// written by their own lane, long ones (coarse leaves) by the whole wave.
-__global__ __launch_bounds__(256) void k_build_dir(const uint64_t* __restrict__ keys, Count cn,
-                                                   int shift, int64_t nb, int32_t* __restrict__ d,
-                                                   const unsigned* conv) {
-  if (conv && *conv) return;  // captured cycles: keys unchanged since the last build
-  const int64_t n = cn.get();
-  const int lane = threadIdx.x & 63;
-  auto ceil_sh = [shift](uint64_t k) -> int64_t {
-    const uint64_t mask = (uint64_t(1) << shift) - 1;
-    return int64_t(k >> shift) + ((k & mask) ? 1 : 0);
-  };
-  for (int64_t wb = int64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63); wb < n;
-       wb += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = wb + lane;
-    int64_t c0 = 0, c1 = 0;
-    if (i < n) {
-      c0 = ceil_sh(keys[i]);
-      c1 = i + 1 < n ? ceil_sh(keys[i + 1]) : nb + 1;
-      c1 = c1 < nb + 1 ? c1 : nb + 1;
-      c0 = c0 < c1 ? c0 : c1;
-      if (i == 0)
-        for (int64_t c = 0, e = c0; c < e; ++c) d[c] = -1;
-    }
-    const bool big = c1 - c0 > 8;
-    if (!big)
-      for (int64_t c = c0; c < c1; ++c) d[c] = int32_t(i);
-    uint64_t bm = __ballot(big);
-    while (bm) {
-      const int l = __ffsll((unsigned long long)bm) - 1;
-      bm &= bm - 1;
-      const int64_t a = __shfl(c0, l), b = __shfl(c1, l), v = __shfl(i, l);
-      for (int64_t c = a + lane; c < b; c += 64) d[c] = int32_t(v);
-    }
-  }
+void launch_balance_small(const KeyGeom& g, const uint64_t* in, int n, const uint32_t* marks, uint64_t* out,
+                          int64_t cap, int shift, int64_t nb, int32_t* dir, DevCtr* ctr, hipStream_t s) {
+  if (g.dim == 3)
+    k_balance_small<3><<<1, kScanBig, 0, s>>>(g, in, n, marks, out, cap, shift, nb, dir, ctr);
+  else
+    k_balance_small<2><<<1, kScanBig, 0, s>>>(g, in, n, marks, out, cap, shift, nb, dir, ctr);
 }
 
 // 2:1 balance, refinement pass: split bit-0 leaves one level, in order.  The
@@ -1539,6 +1750,36 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
   int mi = 0;
   const bool restricted = t->adapt_marks && t->mcap[0] >= t->n_cur;
   t->adapt_marks = false;
+  // A tree that fits one workgroup with room to grow: every pass in one launch
+  // and one readback (another launch where the output buffer is too small).  One
+  // that outgrows it goes through the passes below, which find everything as it
+  // was.
+  if (t->n_cur > 0 && t->n_cur <= kSmallLeaves - kScanBig) {
+    const int out = t->cur == t->tmp ? t->aux : t->tmp;
+    if (!t->dir_valid) {
+      dir_params(t->g, t->n_cur, &t->dir_shift, &t->dir_nb);
+      LT_TRY(grow(t->A, &t->dir, &t->dir_cap, t->dir_nb + 1));
+    }
+    t->dir_valid = false;
+    for (;;) {
+      launch_balance_small(t->g, t->kbuf[t->cur], int(t->n_cur), restricted ? t->mbuf[0] : nullptr, t->kbuf[out],
+                           t->kcap[out], t->dir_shift, t->dir_nb, t->dir, t->dctr, s);
+      LT_HIP(hipGetLastError());
+      LT_TRY(read_ctr(t, s));
+      if (!t->hctr->err || !t->hctr->total) break;
+      LT_TRY(grow(t->A, &t->kbuf[out], &t->kcap[out], t->hctr->total));
+    }
+    if (!t->hctr->err) {
+      if (t->hctr->total != t->n_cur) {
+        t->cur = out;
+        t->n_cur = t->hctr->total;
+        invalidate(t);
+      }
+      t->dir_valid = true;
+      return LT_OK;
+    }
+    LT_TRY(clear_err(t, s));
+  }
   if (!restricted) {
     LT_TRY(grow(t->A, &t->mbuf[mi], &t->mcap[mi], t->n_cur));
     k_fill_u32<<<unsigned(ceil_div(t->n_cur, 256)), 256, 0, s>>>(t->mbuf[mi], t->n_cur, 0u);

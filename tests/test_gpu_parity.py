@@ -366,6 +366,45 @@ def test_balance_marking_at_list_edges(dim, depth, kind):
             assert_same_tree(g, o, "balance")
 
 
+@pytest.mark.parametrize("dim,depth,n,deep", [(2, 0, 1, 0), (2, 3, 64, 0), (2, 4, 1024, 12), (2, 4, 1027, 40),
+                                              (2, 6, 13309, 1), (2, 6, 13312, 12), (2, 6, 13312, 1000), (2, 6, 13315, 12),
+                                              (3, 4, 13308, 2), (3, 4, 13308, 300), (3, 4, 13315, 2)])
+def test_balance_of_one_workgroup_at_its_edges(dim, depth, n, deep):
+    """Balance of a tree that fits one workgroup, around the 1024 leaves of one
+    round and the 13312 above which the passes take over, with results that
+    fit it, that outgrow it and that change nothing: a tree refined at random
+    to n leaves, the last `deep` splits among the children of the others, as
+    it is adapted and as it is built from its keys (no buffer to spare)."""
+    import torch
+    import oracle
+    import paper_2306_06744_amd as lt
+    nc = 1 << dim
+    rng = np.random.default_rng(n + deep)
+    g, o = both(dim, 0, depth + 6, depth=depth, periodic_mask=0)
+    while o.size() < n:
+        splits = (n - o.size()) // (nc - 1) - deep
+        splits, last = (splits, False) if splits > 0 else (deep, True)
+        splits = min(splits, o.size() // 2) if not last else splits
+        f = np.zeros(o.size(), np.int8)
+        pick = rng.permutation(o.size())[:splits]
+        if last:    # the deepest leaves, so that their neighbours must follow
+            d = o.keys() & np.uint64((1 << int(depth + 6).bit_length()) - 1)
+            pick = np.argsort(-d.astype(np.int64), kind="stable")[rng.permutation(min(4 * deep, o.size()))[:splits]]
+        f[pick] = 1
+        adapt_both(g, o, f)
+        assert_same_tree(g, o, "adapt")
+    print("one workgroup", dim, depth, n, deep, "leaves", o.size(), flush=True)
+    k = o.keys()
+    g2 = lt.Tree.from_keys(torch.from_numpy(k.view(np.int64).copy()), dim, 0, depth + 6, periodic_mask=0)
+    for t in (g, g2):
+        t.balance()
+    o.balance()
+    print("balanced", o.size(), flush=True)
+    for t in (g, g2):
+        assert_same_tree(t, o, "balance")
+        assert_same_connectivity(t, o, "connect")
+
+
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("depth", [1, 2, 3, 4])
 def test_interpolation_groups_at_list_edges(depth, mixed):
