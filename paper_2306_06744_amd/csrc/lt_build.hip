@@ -366,9 +366,9 @@ lt_status build_points(lt_tree t, const double* pts, int64_t n, const double* lo
     k_unique<<<grid_tiles(st), kScanSmall, 0, s>>>(a, b, st);
     if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "unique launch");
     LT_TRY_STATUS(read_ctr(t, s));
-    if (t->hctr->err & ERR_POINT) return fail(LT_ERR_ARG, "a point lies outside the domain");
-    if (t->hctr->err) return fail(LT_ERR_INTERNAL, "device check failed while sorting the points");
-    m = t->hctr->total;
+    if (t->hctr->c.err & ERR_POINT) return fail(LT_ERR_ARG, "a point lies outside the domain");
+    if (t->hctr->c.err) return fail(LT_ERR_INTERNAL, "device check failed while sorting the points");
+    m = t->hctr->c.total;
   }
   const uint64_t* S = b;
   const uint64_t end = uint64_t(1) << (dim * g.dmax);
@@ -379,8 +379,8 @@ lt_status build_points(lt_tree t, const double* pts, int64_t n, const double* lo
   k_gap_count<<<grid_tiles(st), kScanSmall, 0, s>>>(S, m, end, dim, K, goff, st);
   if (hipGetLastError() != hipSuccess) return fail(LT_ERR_HIP, "gap count launch");
   LT_TRY_STATUS(read_ctr(t, s));
-  if (t->hctr->err) return fail(LT_ERR_INTERNAL, "device check failed while counting the tiling");
-  const int64_t total = t->hctr->total;
+  if (t->hctr->c.err) return fail(LT_ERR_INTERNAL, "device check failed while counting the tiling");
+  const int64_t total = t->hctr->c.total;
   if (total > (int64_t(1) << 31) - 1) return fail(LT_ERR_ARG, "the tree would hold 2^31 leaves or more");
   LT_TRY_STATUS(grow(t->A, &t->kbuf[t->cur], &t->kcap[t->cur], total));
   const int64_t threads = m + 1;  // one lane per gap
@@ -406,7 +406,7 @@ lt_status lt_build_points(const lt_geom* geom, const double* pts, int64_t n, con
   if (n > (int64_t(1) << 31) - 1) return fail(LT_ERR_ARG, "at most 2^31 - 1 points");
   if (!(len > 0.0)) return fail(LT_ERR_ARG, "the domain length must be positive");
   lt_tree t = nullptr;
-  LT_TRY_STATUS(create_tree(geom, &t));
+  LT_TRY_STATUS(create_tree(geom, static_cast<hipStream_t>(stream), &t));
   if (geom->dim == 3 && geom->d_max > 21) {
     lt_destroy(t);
     return fail(LT_ERR_DEPTH, "3D d_max above 21");

@@ -2,9 +2,10 @@
 //
 // record_cycle (lt_tree.hip) enqueues every step with the leaf counts kept on
 // the device and every launch sized for a fixed capacity, so the sequence
-// needs no host readback and can be captured once.  A run uploads the cycle's
-// flag parameters, replays the graph for the current solution parity and
-// reads the sizes and the error word back in one synchronisation.
+// needs no host readback and can be captured once.  A run writes the cycle's
+// flag parameters to pinned memory, where the graph fetches them, replays the
+// graph for the current solution parity and waits for the sizes and the error
+// word that the graph's last node writes to pinned memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -163,6 +164,8 @@ lt_status capture(lt_cycle c) {
     r.tmpl = c->tmpl.data();
     r.nmesh = c->nmesh;
     r.dsz = c->dsz;
+    r.hsz = c->hsz;
+    r.flag_host = c->flag_host;
     r.ops = c->d.p > 0 ? t->ops[c->d.p] : nullptr;
     r.precision = c->d.precision;
     r.mlp = c->d.mlp;
@@ -332,14 +335,10 @@ lt_status lt_cycle_run(lt_cycle c, const lt_flag_params* fp, void* stream, int* 
     if (fp[m].p != c->tmpl[m].p) return fail(LT_ERR_ARG, "flag parameters need each mesh's template p");
   LT_TRY_STATUS(fill_flag_table(t->g, fp, c->nmesh, c->flag_host));
   const int q = c->parity;
-  if (hipMemcpyAsync(t->flag_tab, c->flag_host, flag_args_size() * size_t(c->nmesh), hipMemcpyHostToDevice,
-                     s) != hipSuccess)
-    return fail(LT_ERR_HIP, "flag table upload");
+  const uint64_t seen = __atomic_load_n(&t->hctr->seq, __ATOMIC_ACQUIRE);
   if (hipGraphLaunch(c->exec[q], s) != hipSuccess) return fail(LT_ERR_HIP, "graph launch");
-  if (hipMemcpyAsync(c->hsz, c->dsz, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-    return fail(LT_ERR_HIP, "size readback");
-  LT_TRY_STATUS(read_ctr(t, s));
-  unsigned err = t->hctr->err;
+  LT_TRY_STATUS(await_read(t->hctr, seen, s));
+  unsigned err = t->hctr->c.err;
   // an unfinished balance also shows as missing fine leaves at hanging faces
   if (err & ERR_BALANCE_PASSES) err &= ~ERR_UNBALANCED;
   c->runs++;

@@ -22,6 +22,14 @@ struct DevCtr {
   int64_t nfused;             // fused parents listed for the first balance pass
   int64_t nfgroups;           // transfer groups holding a fused element (second list)
   int64_t nexam;              // balance: leaves listed for the next marking pass
+  uint64_t reads;             // readbacks so far (see k_publish)
+};
+
+// Pinned mirror of a DevCtr and, behind it, the number of the readback it came
+// with (see k_publish).
+struct HostCtr {
+  DevCtr c;
+  uint64_t seq;
 };
 
 void set_error(const std::string& msg);
@@ -69,6 +77,8 @@ struct CycleRec {
   const lt_flag_params* tmpl;  // every mesh's template (only the degrees are read here)
   int nmesh;
   int64_t* dsz;
+  int64_t* hsz;            // pinned: dsz as the cycle leaves it
+  const void* flag_host;   // pinned: the flag parameters the cycle starts from
   const double* ops;
   int precision;       // transfer: 0 FP64, 1 split
   lt_mlp mlp;          // learned flags (null: geometric only)
@@ -152,9 +162,15 @@ lt_status prep_scan_fixed(uint64_t* status, int64_t status_cap, DevCtr* ctr, int
 lt_status prep_scan_conn(lt_tree_s* t, int64_t n_items, hipStream_t stream, int flags,
                          ScanState* st);
 // A new tree with no leaves yet (geometry checked, counters allocated).
-lt_status create_tree(const lt_geom* geom, lt_tree_s** out);
+lt_status create_tree(const lt_geom* geom, hipStream_t s, lt_tree_s** out);
 // Copy the device counters to the pinned mirror and wait for the stream.
 lt_status read_ctr(lt_tree_s* t, hipStream_t stream);
+// Enqueues the readback of the counters `dev` and, if given, of `words` further
+// ones to pinned memory; await_read waits for the one after readback number
+// `seen` and for all work before it on the stream.
+lt_status publish(DevCtr* dev, HostCtr* host, hipStream_t stream, const int64_t* more = nullptr,
+                  int64_t* more_host = nullptr, int words = 0);
+lt_status await_read(const HostCtr* host, uint64_t seen, hipStream_t stream);
 // p[0, n) = v (a kernel: a captured graph must hold no memset node).
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream);
 // Zero the counters, but for the error word and the balance lists' lengths.
@@ -268,13 +284,13 @@ struct lt_tree_s {
   uint64_t* status = nullptr;  // look-back tile words
   int64_t status_cap = 0;
   lt::DevCtr* dctr = nullptr;
-  lt::DevCtr* hctr = nullptr;  // pinned mirror
+  lt::HostCtr* hctr = nullptr;  // pinned mirror
   int32_t* elist = nullptr;     // balance: leaves to examine in the next marking pass
   int64_t elist_cap = 0;
   uint64_t* cstatus = nullptr;  // connectivity's own look-back words and counters
   int64_t cstatus_cap = 0;
   lt::DevCtr* cctr = nullptr;
-  lt::DevCtr* hcctr = nullptr;  // pinned mirror
+  lt::HostCtr* hcctr = nullptr;  // pinned mirror
 
   double* ops[LT_MAX_DEGREE + 1] = {};  // 1D factors A_0, A_1, P_0, P_1 and weights
 

@@ -405,6 +405,52 @@ def test_balance_of_one_workgroup_at_its_edges(dim, depth, n, deep):
         assert_same_connectivity(t, o, "connect")
 
 
+def test_readbacks_behind_a_long_queue_and_in_threads():
+    """Counters read back to pinned memory: behind work that keeps the stream
+    busy for longer than the host watches the mirror (1 ms), from several
+    threads with a tree and a stream each, and for more trees alive at once
+    than the blocks that are kept, made twice from the same blocks."""
+    import threading
+    import torch
+    import oracle
+    import paper_2306_06744_amd as lt
+
+    def run(seed, busy, out):
+        torch.cuda.set_device(0)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            x = torch.ones(1 << 27, device="cuda")
+            g, o = both(2, 1, 7, depth=3)
+            for c in range(3):
+                if busy:
+                    for _ in range(20):     # 1 GiB of traffic each: about 4 ms
+                        x.mul_(1.0)
+                adapt_both(g, o, synth.random_flags(seed + c, o.size(), 0.4, 0.3))
+                g.balance()
+                o.balance()
+                assert_same_tree(g, o, "balance")
+                assert_same_connectivity(g, o, "connect")
+                assert_same_map(g, o, "map")
+            out.append(seed)
+
+    done = []
+    run(1, True, done)
+    ths = [threading.Thread(target=run, args=(10 * i, i % 2 == 0, done)) for i in range(1, 5)]
+    for t in ths:
+        t.start()
+    for t in ths:
+        t.join()
+    assert sorted(done) == [1, 10, 20, 30, 40]
+    for _ in range(2):
+        trees = [lt.Tree.uniform(2, 0, 6, depth=2 + i % 3) for i in range(40)]
+        for i, t in enumerate(trees):
+            o = oracle.Tree(2, 0, 6, start_depth=2 + i % 3)
+            adapt_both(t, o, synth.random_flags(i, o.size(), 0.4, 0.3))
+            t.balance()
+            o.balance()
+            assert_same_tree(t, o, "balance")
+        del trees, t
+
+
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("depth", [1, 2, 3, 4])
 def test_interpolation_groups_at_list_edges(depth, mixed):
