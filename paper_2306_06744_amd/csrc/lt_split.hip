@@ -471,7 +471,7 @@ lt_status launch_split_transfer(lt_tree_s* t, Count cn, int p, int nvar, const d
   LT_TRY_STATUS(transfer_side(t, &side, &fork, &join));
   int64_t *nR = &t->dctr->total, *nF = &t->dctr->nfgroups;
   auto lists = [&](hipStream_t q) -> lt_status {
-    LT_TRY_STATUS(clear_counters(t->dctr, q));
+    if (!cn.p) LT_TRY_STATUS(clear_counters(t->dctr, q));  // a captured cycle's mapping cleared them
     k_split_lists<<<unsigned((n + kTileMin - 1) / kTileMin), kBlock, 0, q>>>(t->map_kind, cn, t->split_R, nR,
                                                                            t->split_F, nF);
     return LT_OK;

@@ -1045,7 +1045,7 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     // with a fused element in [ngroups, 2 ngroups)
     int32_t* flist = X.grp_list + ngroups;
     auto lists = [&](hipStream_t q) -> lt_status {
-      LT_TRY_STATUS(clear_counters(X.ctr, q));
+      if (!n.p) LT_TRY_STATUS(clear_counters(X.ctr, q));  // a captured cycle's mapping cleared them
       k_group_list<false><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, q>>>(
           KeyGeom{}, nullptr, nullptr, kind, n, X.grp_list, &X.ctr->total, flist, &X.ctr->nfgroups);
       return LT_OK;
@@ -1270,7 +1270,7 @@ lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, int
   // passes on the second stream need it.  Then the copy pass on the caller's
   // stream and, as in the single-degree form, the interpolation passes
   // (which here write no copies) on the second stream.
-  LT_TRY_STATUS(clear_counters(t->dctr, s));
+  if (!n.p) LT_TRY_STATUS(clear_counters(t->dctr, s));  // a captured cycle's mapping cleared them
   int32_t* flist = t->grp_list + 3 * ngroups;
   const int64_t* nlist = &t->dctr->total;
   k_group_list<true><<<unsigned((ngroups + kGroupsPerBlock - 1) / kGroupsPerBlock), kBlock, 0, s>>>(

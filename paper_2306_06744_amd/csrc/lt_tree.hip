@@ -85,24 +85,15 @@ namespace {
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------------ kernels
-// Zero the look-back words and counters before a scan.  converge (captured
-// cycles, after a balance marking pass): no fresh marks means the fixpoint.
-// Captured cycles also fold their count bookkeeping in here (one launch fewer
-// each): *cnt_dst = *cnt_src when both are set, and reset_conv clears the
-// fixpoint flag at the start of a cycle.
-__global__ void k_clear_scan(uint64_t* status, int64_t ntiles, DevCtr* ctr, int clear_err,
-                             int converge, int clear_list, int reset_conv, int64_t* cnt_dst,
-                             const int64_t* cnt_src) {
+// Zero the look-back words and counters before a scan.
+__global__ void k_clear_scan(uint64_t* status, int64_t ntiles, DevCtr* ctr, int clear_err, int clear_list) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < ntiles) status[i] = 0;
   if (i == 0) {
     if (clear_list) {  // the lists adapt and balance refinement build for the next pass
-      ctr->nexam = 0;
+      ctr->nexam[0] = 0;
       ctr->nfused = 0;
     }
-    if (converge && ctr->nmarked == 0) ctr->conv = 1;
-    if (reset_conv) ctr->conv = 0;
-    if (cnt_dst && cnt_src) *cnt_dst = *cnt_src;
     ctr->ticket = 0;
     ctr->total = 0;
     ctr->nmarked = 0;
@@ -111,10 +102,44 @@ __global__ void k_clear_scan(uint64_t* status, int64_t ntiles, DevCtr* ctr, int 
   }
 }
 
-// Words from pinned host memory.
-__global__ void k_fetch(const uint32_t* __restrict__ host, uint32_t* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// The same done by a kernel that runs ahead of the scan anyway (a launch less:
+// in a captured cycle 5 us each, of which it had eight).  ctr null: nothing.
+struct ScanClear {
+  uint64_t* status;
+  int64_t ntiles;
+  DevCtr* ctr;
+  int64_t* nexam;  // the examine list the scan appends to
+  int64_t* cnt_dst;
+  const int64_t* cnt_src;
+};
+
+// Every thread of a launch of `threads` calls; tid: its index there.
+__device__ inline void scan_clear(const ScanClear& c, int64_t tid, int64_t threads) {
+  if (!c.ctr) return;
+  for (int64_t i = tid; i < c.ntiles; i += threads) c.status[i] = 0;
+  if (tid == 0) {
+    if (c.nexam) *c.nexam = 0;
+    if (c.cnt_dst) *c.cnt_dst = *c.cnt_src;
+    c.ctr->ticket = 0;
+    c.ctr->total = 0;
+    c.ctr->nmarked = 0;
+    c.ctr->nfgroups = 0;
+  }
+}
+
+// Start of a captured cycle: words from pinned host memory, everything cleared
+// for adapt's scan, the count before the cycle kept.
+__global__ void k_cycle_start(const uint32_t* __restrict__ host, uint32_t* __restrict__ p, int n, ScanClear c) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) p[i] = host[i];
+  scan_clear(c, i, int64_t(gridDim.x) * blockDim.x);
+  if (i == 0) {
+    c.ctr->err = 0;
+    c.ctr->conv = 0;
+    c.ctr->nfused = 0;
+    c.ctr->nexam[0] = 0;
+    c.ctr->nexam[1] = 0;
+  }
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -424,7 +449,8 @@ __device__ inline void dir_fill(int64_t i, int64_t n, uint64_t key, uint64_t nex
 
 __global__ __launch_bounds__(256) void k_build_dir(const uint64_t* __restrict__ keys, Count cn,
                                                    int shift, int64_t nb, int32_t* __restrict__ d,
-                                                   const unsigned* conv) {
+                                                   const unsigned* conv, ScanClear clear) {
+  scan_clear(clear, int64_t(blockIdx.x) * blockDim.x + threadIdx.x, int64_t(gridDim.x) * blockDim.x);
   if (conv && *conv) return;  // captured cycles: keys unchanged since the last build
   const int64_t n = cn.get();
   const int lane = threadIdx.x & 63;
@@ -512,9 +538,9 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
                                                          int check_all, DevCtr* ctr,
                                                          const unsigned* conv,
                                                          const int32_t* __restrict__ elist,
-                                                         int64_t ecap) {
+                                                         const int64_t* nexam, int64_t ecap) {
   // waves stride over the leaves: every one (check_all), or the listed ones
-  // (elist: ctr->nexam entries, the leaves holding bit 2).  `conv` (captured
+  // (elist: *nexam entries, the leaves holding bit 2).  `conv` (captured
   // cycles): the fixpoint was already reached, nothing to examine.
   if (conv && *conv) return;
   constexpr int NC = 1 << DIM, kWaves = kBlock / 64;
@@ -522,7 +548,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
   __shared__ int32_t s_idx[kWaves][PER];
   __shared__ uint16_t s_task[kWaves][PER * (NC - 1)];
   const int64_t n = cn.get();
-  const int64_t items = elist ? min(ctr->nexam, ecap) : n;
+  const int64_t items = elist ? min(*nexam, ecap) : n;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
   unsigned long long nfresh = 0;
@@ -580,12 +606,12 @@ constexpr int kMarkList = 16;  // listed leaves a wave takes at a time
 // bounds their number.
 void launch_balance_mark(const KeyGeom& g, const uint64_t* keys, Count cn, int64_t leaves, const KeyDir& D,
                          uint32_t* mark, DevCtr* ctr, const unsigned* conv, const int32_t* elist,
-                         int64_t ecap, hipStream_t s) {
+                         const int64_t* nexam, int64_t ecap, hipStream_t s) {
   const int per = (elist ? kMarkList : 64) * (kBlock / 64);  // leaves a block takes at a time
   const int64_t full = ceil_div(leaves, per);
   const unsigned blocks = unsigned(elist ? std::min<int64_t>(full, kMarkGrid) : full);
 #define LT_MARK(DIM, PER, ALL) \
-  k_balance_mark<DIM, PER><<<blocks, kBlock, 0, s>>>(g, keys, cn, D, mark, ALL, ctr, conv, elist, ecap)
+  k_balance_mark<DIM, PER><<<blocks, kBlock, 0, s>>>(g, keys, cn, D, mark, ALL, ctr, conv, elist, nexam, ecap)
   if (g.dim == 3) {
     if (elist) LT_MARK(3, kMarkList, 0); else LT_MARK(3, 64, 1);
   } else {
@@ -846,12 +872,14 @@ __global__ __launch_bounds__(kScanBig) void k_balance_refine(KeyGeom g, const ui
                                                            const uint32_t* __restrict__ mark,
                                                            uint64_t* __restrict__ out,
                                                            uint32_t* __restrict__ mark_out, int64_t cap,
-                                                           ScanState st, const unsigned* conv,
+                                                           ScanState st, DevCtr* cyc,
                                                            int32_t* __restrict__ elist, int64_t* nexam,
                                                            int64_t ecap) {
   constexpr int64_t kTile = int64_t(kScanBig) * R;
-  if (conv && *conv) {
-    // captured cycles past the fixpoint: the pass is the identity, a plain copy
+  if (cyc && (cyc->conv || cyc->nmarked == 0)) {
+    // captured cycles at the fixpoint (no marks: noted for the passes after
+    // this one) or past it: the pass is the identity, a plain copy
+    if (blockIdx.x == 0 && threadIdx.x == 0) cyc->conv = 1;
     const int64_t n = st.items.get();
 #pragma unroll
     for (int k = 0; k < R; ++k) {
@@ -943,13 +971,13 @@ void launch_adapt(const KeyGeom& g, const uint64_t* in, const int8_t* flags, uin
 }
 
 void launch_balance_refine(const KeyGeom& g, const uint64_t* in, const uint32_t* mark, uint64_t* out,
-                           uint32_t* mark_out, int64_t cap, const ScanState& st, const unsigned* conv,
+                           uint32_t* mark_out, int64_t cap, const ScanState& st, DevCtr* cyc,
                            int32_t* elist, int64_t* nexam, int64_t ecap, hipStream_t s) {
   if (st.tile == kScanBig)
-    k_balance_refine<1><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, conv, elist,
+    k_balance_refine<1><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, cyc, elist,
                                                             nexam, ecap);
   else
-    k_balance_refine<kRounds><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, conv,
+    k_balance_refine<kRounds><<<grid_tiles(st), kScanBig, 0, s>>>(g, in, mark, out, mark_out, cap, st, cyc,
                                                                   elist, nexam, ecap);
 }
 
@@ -965,7 +993,11 @@ void launch_balance_refine(const KeyGeom& g, const uint64_t* in, const uint32_t*
 template <int DIM>
 __global__ __launch_bounds__(256) void k_connect_faces(KeyGeom g, const uint64_t* __restrict__ keys,
                                                        Count cn, KeyDir D, int32_t* __restrict__ nbr,
-                                                       uint8_t* __restrict__ hmask) {
+                                                       uint8_t* __restrict__ hmask, ScanClear clear) {
+  // for the scan of the rows, which follows
+  const int64_t gt = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  scan_clear(clear, gt, int64_t(gridDim.x) * blockDim.x);
+  if (clear.ctr && gt == 0) clear.ctr->err = 0;
   constexpr int SL = 1 << DIM, NF = 2 * DIM;
   const int64_t n = cn.get();
   const int64_t lanes = n * SL;
@@ -1170,11 +1202,13 @@ constexpr int kMapWin = 640;
 __global__ __launch_bounds__(kBlock) void k_map(KeyGeom g, const uint64_t* __restrict__ old_keys,
                                                 Count cn_old, const uint64_t* __restrict__ keys,
                                                 Count cn, int32_t* __restrict__ src,
-                                                int8_t* __restrict__ kind, unsigned* err,
-                                                const unsigned long long* nmarked) {
+                                                int8_t* __restrict__ kind, unsigned* err, DevCtr* cyc) {
   // captured cycles: marks left by the last marking pass mean that the fixed
-  // balance passes did not reach the fixpoint
-  if (nmarked && blockIdx.x == 0 && threadIdx.x == 0 && *nmarked != 0) atomicOr(err, ERR_BALANCE_PASSES);
+  // balance passes did not reach the fixpoint; the transfer's lists count from 0
+  if (cyc && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (cyc->nmarked != 0) atomicOr(err, ERR_BALANCE_PASSES);
+    scan_clear(ScanClear{nullptr, 0, cyc, nullptr, nullptr, nullptr}, 0, 1);
+  }
   __shared__ uint64_t win[kBlock / 64][kMapWin];
   const int64_t n_old = cn_old.get(), n = cn.get();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1244,40 +1278,30 @@ void dir_params(const KeyGeom& g, int64_t n, int* shift, int64_t* nb) {
     *nb = (nm + (int64_t(1) << (*shift - ms)) - 1) >> (*shift - ms);
 }
 
-lt_status prep_scan_fixed(uint64_t* status, int64_t status_cap, DevCtr* ctr, int64_t n_items,
-                          int64_t tile, hipStream_t stream, int flags, ScanState* st, int64_t* cnt_dst,
-                          const int64_t* cnt_src) {
+// A scan over n_items whose words and counters an earlier kernel clears (clear).
+lt_status plan_scan(const Alloc& A, uint64_t** status, int64_t* status_cap, DevCtr* ctr, int64_t n_items,
+                    int64_t tile, ScanState* st, ScanClear* clear) {
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(n_items, tile));
-  if (ntiles > status_cap) return fail(LT_ERR_ARG, "scan needs more look-back words than provided");
-  k_clear_scan<<<unsigned(ceil_div(ntiles, 256)), 256, 0, stream>>>(
-      status, ntiles, ctr, flags & 1, (flags >> 1) & 1, (flags >> 2) & 1, (flags >> 3) & 1, cnt_dst,
-      cnt_src);
-  LT_HIP(hipGetLastError());
-  st->status = status;
-  st->ticket = &ctr->ticket;
-  st->err = &ctr->err;
-  st->total = &ctr->total;
-  st->items = Count{n_items, nullptr};
-  st->tile = tile;
-  st->commit = nullptr;
-  st->commit_cap = 0;
+  LT_TRY(grow(A, status, status_cap, ntiles));
+  *st = ScanState{*status, &ctr->ticket, &ctr->err, &ctr->total, Count{n_items, nullptr}, tile, nullptr, 0};
+  *clear = ScanClear{*status, ntiles, ctr, nullptr, nullptr, nullptr};
   return LT_OK;
 }
 
 namespace {
 lt_status prep_scan_on(const Alloc& A, uint64_t** status, int64_t* status_cap, DevCtr* ctr,
-                       int64_t n_items, int64_t tile, hipStream_t stream, int flags, ScanState* st,
-                       int64_t* cnt_dst = nullptr, const int64_t* cnt_src = nullptr) {
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(n_items, tile));
-  LT_TRY(grow(A, status, status_cap, ntiles));
-  return prep_scan_fixed(*status, *status_cap, ctr, n_items, tile, stream, flags, st, cnt_dst, cnt_src);
+                       int64_t n_items, int64_t tile, hipStream_t stream, int flags, ScanState* st) {
+  ScanClear c;
+  LT_TRY(plan_scan(A, status, status_cap, ctr, n_items, tile, st, &c));
+  k_clear_scan<<<unsigned(ceil_div(c.ntiles, 256)), 256, 0, stream>>>(c.status, c.ntiles, ctr, flags & 1,
+                                                                     (flags >> 1) & 1);
+  LT_HIP(hipGetLastError());
+  return LT_OK;
 }
 }  // namespace
 
-lt_status prep_scan(lt_tree t, int64_t n_items, int64_t tile, hipStream_t stream, int flags,
-                    ScanState* st, int64_t* cnt_dst, const int64_t* cnt_src) {
-  return prep_scan_on(t->A, &t->status, &t->status_cap, t->dctr, n_items, tile, stream, flags, st,
-                      cnt_dst, cnt_src);
+lt_status prep_scan(lt_tree t, int64_t n_items, int64_t tile, hipStream_t stream, int flags, ScanState* st) {
+  return prep_scan_on(t->A, &t->status, &t->status_cap, t->dctr, n_items, tile, stream, flags, st);
 }
 
 lt_status prep_scan_conn(lt_tree t, int64_t n_items, hipStream_t stream, int flags, ScanState* st) {
@@ -1392,13 +1416,13 @@ void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream) {
 }
 
 lt_status clear_counters(DevCtr* ctr, hipStream_t stream) {
-  k_clear_scan<<<1, 64, 0, stream>>>(nullptr, 0, ctr, 0, 0, 0, 0, nullptr, nullptr);
+  k_clear_scan<<<1, 64, 0, stream>>>(nullptr, 0, ctr, 0, 0);
   LT_HIP(hipGetLastError());
   return LT_OK;
 }
 
 lt_status clear_err(lt_tree t, hipStream_t stream) {
-  k_clear_scan<<<1, 64, 0, stream>>>(t->status, 0, t->dctr, 1, 0, 0, 0, nullptr, nullptr);
+  k_clear_scan<<<1, 64, 0, stream>>>(t->status, 0, t->dctr, 1, 0);
   LT_HIP(hipGetLastError());
   return LT_OK;
 }
@@ -1471,7 +1495,7 @@ lt_status ensure_dir(lt_tree t, hipStream_t s, KeyDir* D) {
     LT_TRY(grow(t->A, &t->dir, &t->dir_cap, t->dir_nb + 1));
     if (n > 0) {
       k_build_dir<<<unsigned(ceil_div(n, 256)), 256, 0, s>>>(t->kbuf[t->cur], Count{n, nullptr},
-                                                             t->dir_shift, t->dir_nb, t->dir, nullptr);
+                                                             t->dir_shift, t->dir_nb, t->dir, nullptr, ScanClear{});
       LT_HIP(hipGetLastError());
     }
     t->dir_valid = true;
@@ -1530,21 +1554,23 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
   unsigned* err = &t->dctr->err;
   int8_t* F = t->map_kind;  // the flags live in the kind array until the mapping overwrites it
   // flags (parameters from the device table, fetched from the host's)
+  ScanState st;
+  ScanClear sc;
+  LT_TRY(plan_scan(t->A, &t->status, &t->status_cap, t->dctr, C, tile_of(C), &st, &sc));
+  sc.cnt_dst = &S[1];  // leaves before the cycle
+  sc.cnt_src = &S[0];
   const int fw = int(flag_args_size() * size_t(r.nmesh) / 4);
-  k_fetch<<<unsigned(ceil_div(fw, 256)), 256, 0, s>>>(static_cast<const uint32_t*>(r.flag_host),
-                                                    static_cast<uint32_t*>(t->flag_tab), fw);
+  k_cycle_start<<<unsigned(ceil_div(fw, 256)), 256, 0, s>>>(static_cast<const uint32_t*>(r.flag_host),
+                                                          static_cast<uint32_t*>(t->flag_tab), fw, sc);
   LT_HIP(hipGetLastError());
   LT_TRY(launch_flag_table(g, r.tmpl, r.nmesh, t->flag_tab, K0, Count{C, &S[0]}, F, s));
   if (r.mlp)  // learned flags, the geometric ones as the fallback below conf_min
     LT_TRY(launch_mlp_flag(t, r.mlp, Count{C, &S[0]}, r.uo, r.ld, r.conf_min, F, nullptr, s));
-  // adapt K0 -> K[0]; its scan's clear also starts the cycle: leaves before
-  // the cycle S[1] <- S[0], the fixpoint flag cleared
-  ScanState st;
-  LT_TRY(prep_scan(t, C, tile_of(C), s, 1 | 4 | 8, &st, &S[1], &S[0]));
+  // adapt K0 -> K[0]
   st.items.p = &S[1];
   st.commit = &S[0];
   st.commit_cap = C;
-  launch_adapt(g, K0, F, K[0], C, st, t->mbuf[0], t->elist, &t->dctr->nexam, t->elist_cap, t->fused,
+  launch_adapt(g, K0, F, K[0], C, st, t->mbuf[0], t->elist, &t->dctr->nexam[0], t->elist_cap, t->fused,
                &t->dctr->nfused, t->fused_cap, s);
   LT_HIP(hipGetLastError());
   // balance: fixed passes, then a check
@@ -1553,29 +1579,34 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
   const KeyDir D{t->dir, r.dir_shift, r.dir_nb};
   int ki = 0, mi = 0;
   for (int pass = 0; pass <= r.passes; ++pass) {
-    k_build_dir<<<nleaf, 256, 0, s>>>(K[ki], Count{C, &S[0]}, r.dir_shift, r.dir_nb, t->dir, conv);
+    // The directory build also clears for the pass's refinement and copies its
+    // input count to S[3], where it reads it: the last tile commits the new count
+    // to S[0] while workgroups of the capacity-sized grid may still be taking
+    // tickets, and each must see the count the scan started from.
+    LT_TRY(plan_scan(t->A, &t->status, &t->status_cap, t->dctr, C, tile_of(C), &st, &sc));
+    sc.nexam = &t->dctr->nexam[1 - (pass & 1)];
+    sc.cnt_dst = &S[3];
+    sc.cnt_src = &S[0];
+    k_build_dir<<<nleaf, 256, 0, s>>>(K[ki], Count{C, &S[0]}, r.dir_shift, r.dir_nb, t->dir, conv, sc);
     if (pass == 0)
       LT_HIP(launch_fused_check(g, K[ki], Count{C, &S[0]}, D, t->mbuf[mi], t->fused, t->dctr, s));
-    launch_balance_mark(g, K[ki], Count{C, &S[0]}, C, D, t->mbuf[mi], t->dctr, conv, t->elist, t->elist_cap, s);
+    launch_balance_mark(g, K[ki], Count{C, &S[0]}, C, D, t->mbuf[mi], t->dctr, conv, t->elist,
+                        &t->dctr->nexam[pass & 1], t->elist_cap, s);
     LT_HIP(hipGetLastError());
     if (pass == r.passes) break;
-    // the clear also records convergence, and copies the pass's input count
-    // to S[3], where the pass reads it: the last tile commits the new count
-    // to S[0] while workgroups of the capacity-sized grid may still be taking
-    // tickets, and each must see the count the scan started from
-    LT_TRY(prep_scan(t, C, tile_of(C), s, 2 | 4, &st, &S[3], &S[0]));
     st.items.p = &S[3];
     st.commit = &S[0];
     st.commit_cap = C;
-    launch_balance_refine(g, K[ki], t->mbuf[mi], K[1 - ki], t->mbuf[1 - mi], C, st, conv, t->elist,
-                          &t->dctr->nexam, t->elist_cap, s);
+    launch_balance_refine(g, K[ki], t->mbuf[mi], K[1 - ki], t->mbuf[1 - mi], C, st, t->dctr, t->elist, sc.nexam,
+                          t->elist_cap, s);
+    LT_HIP(hipGetLastError());
     ki = 1 - ki;
     mi = 1 - mi;
   }
   if (ki != 0) return fail(LT_ERR_ARG, "balance passes of a captured cycle must be even");
   // map
   k_map<<<nleaf, kBlock, 0, s>>>(g, K0, Count{C, &S[1]}, K[0], Count{C, &S[0]}, t->map_src,
-                                  t->map_kind, err, &t->dctr->nmarked);
+                                  t->map_kind, err, t->dctr);
   LT_HIP(hipGetLastError());
   // connect on the side stream (the directory of K[0] was built by the check
   // pass); it reads the new keys only, and its scan words and counters are its
@@ -1584,13 +1615,14 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
   hipStream_t cs = r.side;
   LT_HIP(hipEventRecord(r.fork, s));
   LT_HIP(hipStreamWaitEvent(cs, r.fork, 0));
+  ScanState cst;
+  ScanClear cc;
+  LT_TRY(plan_scan(t->A, &t->cstatus, &t->cstatus_cap, t->cctr, C, kTileMin, &cst, &cc));
   const unsigned cgrid = t->conn_grid > 0 ? std::min<unsigned>(nlanes, unsigned(t->conn_grid)) : nlanes;
   if (g.dim == 3)
-    k_connect_faces<3><<<cgrid, 256, 0, cs>>>(g, K[0], Count{C, &S[0]}, D, t->nbr, t->hmask);
+    k_connect_faces<3><<<cgrid, 256, 0, cs>>>(g, K[0], Count{C, &S[0]}, D, t->nbr, t->hmask, cc);
   else
-    k_connect_faces<2><<<cgrid, 256, 0, cs>>>(g, K[0], Count{C, &S[0]}, D, t->nbr, t->hmask);
-  ScanState cst;
-  LT_TRY(prep_scan_conn(t, C, cs, 1, &cst));
+    k_connect_faces<2><<<cgrid, 256, 0, cs>>>(g, K[0], Count{C, &S[0]}, D, t->nbr, t->hmask, cc);
   cst.items.p = &S[0];
   cst.commit = &S[2];  // rows past the table's capacity raise ERR_CAPACITY
   cst.commit_cap = r.hang_rows;
@@ -1828,9 +1860,9 @@ lt_status lt_adapt(lt_tree t, const int8_t* flags, void* stream) {
     cap = std::min(cap, std::min(t->mcap[0], std::min(t->elist_cap, t->fused_cap)));
   }
   ScanState st;
-  LT_TRY(prep_scan(t, n, tile_of(n), s, 1 | 4, &st));
+  LT_TRY(prep_scan(t, n, tile_of(n), s, 1 | 2, &st));
   launch_adapt(t->g, t->kbuf[t->cur], flags, t->kbuf[out], cap, st, marks ? t->mbuf[0] : nullptr,
-               marks ? t->elist : nullptr, &t->dctr->nexam, t->elist_cap, marks ? t->fused : nullptr,
+               marks ? t->elist : nullptr, &t->dctr->nexam[0], t->elist_cap, marks ? t->fused : nullptr,
                &t->dctr->nfused, t->fused_cap, s);
   LT_HIP(hipGetLastError());
   LT_TRY(read_ctr(t, s));
@@ -1921,7 +1953,7 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
       if (pass == 0 && restricted)  // adapt listed the fused parents (the list is sized for its output)
         LT_HIP(launch_fused_check(t->g, t->kbuf[t->cur], cn, D, t->mbuf[mi], t->fused, t->dctr, s));
       launch_balance_mark(t->g, t->kbuf[t->cur], cn, t->n_cur, D, t->mbuf[mi], t->dctr, nullptr, el,
-                          t->elist_cap, s);
+                          &t->dctr->nexam[0], t->elist_cap, s);
       LT_HIP(hipGetLastError());
     }
     LT_TRY(read_ctr(t, s));
@@ -1937,10 +1969,10 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
     LT_TRY(grow(t->A, &t->elist, &t->elist_cap, n_new));
     ScanState st;
     // also zeroes the mark count and the examine list for the next pass
-    LT_TRY(prep_scan(t, t->n_cur, tile_of(t->n_cur), s, 4, &st));
+    LT_TRY(prep_scan(t, t->n_cur, tile_of(t->n_cur), s, 2, &st));
     const int64_t cap = std::min(std::min(t->kcap[out], t->mcap[1 - mi]), t->elist_cap);
     launch_balance_refine(t->g, t->kbuf[t->cur], t->mbuf[mi], t->kbuf[out], t->mbuf[1 - mi], cap, st,
-                          nullptr, t->elist, &t->dctr->nexam, t->elist_cap, s);
+                          nullptr, t->elist, &t->dctr->nexam[0], t->elist_cap, s);
     LT_HIP(hipGetLastError());
     expect_total = n_new;
     t->cur = out;
@@ -1999,23 +2031,25 @@ lt_status lt_connect(lt_tree t, void* stream) {
   LT_TRY(grow(t->A, &t->hang, &t->hang_cap, std::max<int64_t>(1024, n / 16) * width));
   KeyDir D;
   LT_TRY(ensure_dir(t, s, &D));
+  ScanState st;
+  ScanClear clear;
+  LT_TRY(plan_scan(t->A, &t->cstatus, &t->cstatus_cap, t->cctr, n, kTileMin, &st, &clear));
   if (n > 0) {
     const int64_t lanes = ceil_div(n * t->g.nchild(), 256);
     const unsigned blocks = unsigned(t->conn_grid > 0 ? std::min<int64_t>(lanes, t->conn_grid) : lanes);
     if (t->g.dim == 3)
       k_connect_faces<3><<<blocks, 256, 0, s>>>(t->g, t->kbuf[t->cur], Count{n, nullptr}, D, t->nbr,
-                                                t->hmask);
+                                                t->hmask, clear);
     else
       k_connect_faces<2><<<blocks, 256, 0, s>>>(t->g, t->kbuf[t->cur], Count{n, nullptr}, D, t->nbr,
-                                                t->hmask);
+                                                t->hmask, clear);
     LT_HIP(hipGetLastError());
   }
   const int nh = 1 << (t->g.dim - 1);
   int64_t rows = -1;
   for (int attempt = 0; attempt < 2 && rows < 0; ++attempt) {
     const int64_t cap_rows = t->hang_cap / width;
-    ScanState st;
-    LT_TRY(prep_scan_conn(t, n, s, 1, &st));
+    if (attempt > 0 || n == 0) LT_TRY(prep_scan_conn(t, n, s, 1, &st));
     k_connect_rows<<<grid_tiles(st), kScanSmall, 0, s>>>(t->hmask, t->g.dim, t->hang, cap_rows, st);
     LT_HIP(hipGetLastError());
     // fine leaves of the rows the table holds (the row count stays on the device)
