@@ -468,6 +468,64 @@ __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 2:1 balance after adaptation, fused parents.  A parent P (depth D) that
+// replaced 2^dim balanced leaves can touch leaves of depth D+2 (never deeper,
+// never coarser than D-1 -- the leaves it replaced were balanced).  Such a leaf
+// sits in a depth-(D+1) octant touching P, and any such octant that is
+// subdivided has a child touching P: one lane per (parent, depth-(D+1) cell of
+// the shell around it) -- per the balance kind, cells across faces only, or
+// also edges, or also corners -- looks whether its cell is subdivided, and marks
+// P for splitting then.  Adapt lists the fused parents (any order, count
+// ctr->nfused).  The check runs beside the marking in one launch: both wait for
+// reads, and one after the other they took 8 to 10 us more of a captured cycle
+// (333 -> 325 us at 37 000 leaves, 635 -> 622 for the mixed-degree ensemble).
+constexpr int kShellW = 4;  // cells per axis around P: -1 .. 2 in units of a depth-(D+1) cell
+
+// Search key of shell cell cidx around the fused parent; false for a cell the
+// balance kind leaves out, outside a non-periodic domain, or of a parent too
+// deep to touch a leaf two levels finer.
+template <int DIM>
+__device__ inline bool shell_probe(const KeyGeom& g, uint64_t key, int cidx, int limit, uint64_t* probe) {
+  constexpr int W = kShellW;
+  const int off[3] = {cidx % W - 1, (cidx / W) % W - 1, DIM == 3 ? cidx / (W * W) - 1 : 0};
+  int outside = 0;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
+  const int d = key_depth(g, key);
+  if (outside == 0 || outside > limit || d + 2 > g.dmax) return false;
+  uint64_t x[3];
+  demorton(g, key_morton(g, key), x);
+  const int64_t half = int64_t(1) << (g.dmax - d - 1);
+  uint64_t q[3] = {x[0], x[1], x[2]};
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) ok = ok && shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
+  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
+  return ok;
+}
+
+// Thread tid of `threads` that share the listed parents' cells.
+template <int DIM>
+__device__ inline void fused_probe(const KeyGeom& g, const uint64_t* __restrict__ keys, int64_t n, const KeyDir& D,
+                                   const int32_t* __restrict__ list, uint32_t* mark, DevCtr* ctr, int64_t tid,
+                                   int64_t threads) {
+  constexpr int NCELL = DIM == 3 ? kShellW * kShellW * kShellW : kShellW * kShellW;
+  const int64_t work = int64_t(ctr->nfused) * NCELL;
+  const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
+  for (int64_t t = tid; t < work; t += threads) {
+    const int64_t i = list[t / NCELL];
+    if (i < 0 || i >= n) continue;
+    const uint64_t key = keys[i];
+    uint64_t probe;
+    if (!shell_probe<DIM>(g, key, int(t % NCELL), limit, &probe)) continue;
+    const int64_t j = dir_last_le(keys, n, D, probe);
+    if (j >= 0 && key_depth(g, keys[j]) >= key_depth(g, key) + 2) {
+      const uint32_t was = atomicOr(&mark[i], 1u);
+      if (!(was & 1u)) atomicAdd(&ctr->nmarked, 1ull);
+    }
+  }
+}
+
 // 2:1 balance, marking pass.  For a leaf L of depth D with parent P, the
 // leaves that touch L and are two or more levels coarser are exactly the
 // leaves strictly containing one of the 2^dim - 1 depth-(D-1) neighbours of P
@@ -532,17 +590,26 @@ __device__ inline bool balance_probe(const KeyGeom& g, uint64_t key, int sub, ui
   return ok;
 }
 
-template <int DIM, int PER>
+template <int DIM, int PER, bool PROBE>
 __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64_t* __restrict__ keys,
                                                          Count cn, KeyDir D, uint32_t* mark,
                                                          int check_all, DevCtr* ctr,
                                                          const unsigned* conv,
                                                          const int32_t* __restrict__ elist,
-                                                         const int64_t* nexam, int64_t ecap) {
+                                                         const int64_t* nexam, int64_t ecap,
+                                                         const int32_t* __restrict__ flist, unsigned mblocks) {
   // waves stride over the leaves: every one (check_all), or the listed ones
   // (elist: *nexam entries, the leaves holding bit 2).  `conv` (captured
   // cycles): the fixpoint was already reached, nothing to examine.
   if (conv && *conv) return;
+  // PROBE (the first pass after an adaptation): the workgroups from mblocks on
+  // take the fused parents beside the marking
+  if constexpr (PROBE)
+    if (blockIdx.x >= mblocks) {
+      fused_probe<DIM>(g, keys, cn.get(), D, flist, mark, ctr,
+                       int64_t(blockIdx.x - mblocks) * kBlock + threadIdx.x, int64_t(gridDim.x - mblocks) * kBlock);
+      return;
+    }
   constexpr int NC = 1 << DIM, kWaves = kBlock / 64;
   __shared__ uint64_t s_key[kWaves][PER];
   __shared__ int32_t s_idx[kWaves][PER];
@@ -552,7 +619,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
   unsigned long long nfresh = 0;
-  for (int64_t wb = (int64_t(blockIdx.x) * kWaves + wv) * PER; wb < items; wb += int64_t(gridDim.x) * kWaves * PER) {
+  for (int64_t wb = (int64_t(blockIdx.x) * kWaves + wv) * PER; wb < items; wb += int64_t(mblocks) * kWaves * PER) {
     const int64_t it = lane < PER ? wb + lane : items;
     const int64_t i = it < items ? (elist ? int64_t(elist[it]) : it) : -1;
     unsigned need = 0;
@@ -602,80 +669,31 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
 
 constexpr int kMarkList = 16;  // listed leaves a wave takes at a time
 
-// A marking pass over every leaf (elist null) or the listed ones; `leaves`
-// bounds their number.
+// A marking pass over every leaf (elist null) or the listed ones, and with flist
+// the fused parents' check; `leaves` bounds their number.
 void launch_balance_mark(const KeyGeom& g, const uint64_t* keys, Count cn, int64_t leaves, const KeyDir& D,
                          uint32_t* mark, DevCtr* ctr, const unsigned* conv, const int32_t* elist,
-                         const int64_t* nexam, int64_t ecap, hipStream_t s) {
+                         const int64_t* nexam, int64_t ecap, const int32_t* flist, hipStream_t s) {
   const int per = (elist ? kMarkList : 64) * (kBlock / 64);  // leaves a block takes at a time
   const int64_t full = ceil_div(leaves, per);
   const unsigned blocks = unsigned(elist ? std::min<int64_t>(full, kMarkGrid) : full);
-#define LT_MARK(DIM, PER, ALL) \
-  k_balance_mark<DIM, PER><<<blocks, kBlock, 0, s>>>(g, keys, cn, D, mark, ALL, ctr, conv, elist, nexam, ecap)
-  if (g.dim == 3) {
-    if (elist) LT_MARK(3, kMarkList, 0); else LT_MARK(3, 64, 1);
-  } else {
-    if (elist) LT_MARK(2, kMarkList, 0); else LT_MARK(2, 64, 1);
-  }
+  // the fused parents' number is on the device: up to a workgroup per 64 leaves
+  const unsigned probes = elist && flist ? unsigned(std::max<int64_t>(1, std::min<int64_t>(1024, leaves / 64))) : 0;
+#define LT_MARK(DIM, PER, PROBE, ALL)                                                                    \
+  k_balance_mark<DIM, PER, PROBE><<<blocks + probes, kBlock, 0, s>>>(g, keys, cn, D, mark, ALL, ctr, conv, \
+                                                                   elist, nexam, ecap, flist, blocks)
+#define LT_MARK_DIM(DIM)                          \
+  do {                                            \
+    if (!elist) LT_MARK(DIM, 64, false, 1);       \
+    else if (flist) LT_MARK(DIM, kMarkList, true, 0); \
+    else LT_MARK(DIM, kMarkList, false, 0);       \
+  } while (0)
+  if (g.dim == 3)
+    LT_MARK_DIM(3);
+  else
+    LT_MARK_DIM(2);
+#undef LT_MARK_DIM
 #undef LT_MARK
-}
-
-// 2:1 balance after adaptation, fused parents.  A parent P (depth D) that
-// replaced 2^dim balanced leaves can touch leaves of depth D+2 (never deeper,
-// never coarser than D-1 -- the leaves it replaced were balanced).  Such a leaf
-// sits in a depth-(D+1) octant touching P, and any such octant that is
-// subdivided has a child touching P: one lane per (parent, depth-(D+1) cell of
-// the shell around it) -- per the balance kind, cells across faces only, or
-// also edges, or also corners -- looks whether its cell is subdivided, and marks
-// P for splitting then.  Adapt lists the fused parents (any order, count
-// ctr->nfused).
-constexpr int kShellW = 4;  // cells per axis around P: -1 .. 2 in units of a depth-(D+1) cell
-
-// Search key of shell cell cidx around the fused parent; false for a cell the
-// balance kind leaves out, outside a non-periodic domain, or of a parent too
-// deep to touch a leaf two levels finer.
-template <int DIM>
-__device__ inline bool shell_probe(const KeyGeom& g, uint64_t key, int cidx, int limit, uint64_t* probe) {
-  constexpr int W = kShellW;
-  const int off[3] = {cidx % W - 1, (cidx / W) % W - 1, DIM == 3 ? cidx / (W * W) - 1 : 0};
-  int outside = 0;
-#pragma unroll
-  for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
-  const int d = key_depth(g, key);
-  if (outside == 0 || outside > limit || d + 2 > g.dmax) return false;
-  uint64_t x[3];
-  demorton(g, key_morton(g, key), x);
-  const int64_t half = int64_t(1) << (g.dmax - d - 1);
-  uint64_t q[3] = {x[0], x[1], x[2]};
-  bool ok = true;
-#pragma unroll
-  for (int a = 0; a < DIM; ++a) ok = ok && shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
-  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
-  return ok;
-}
-
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_fused_probe(KeyGeom g, const uint64_t* __restrict__ keys,
-                                                        Count cn, KeyDir D,
-                                                        const int32_t* __restrict__ list, uint32_t* mark,
-                                                        DevCtr* ctr) {
-  constexpr int NCELL = DIM == 3 ? kShellW * kShellW * kShellW : kShellW * kShellW;
-  const int64_t n = cn.get();
-  const int64_t work = int64_t(ctr->nfused) * NCELL;
-  const int limit = g.balance == 0 ? 1 : (g.balance == 1 ? 2 : 3);
-  for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < work;
-       t += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = list[t / NCELL];
-    if (i < 0 || i >= n) continue;
-    const uint64_t key = keys[i];
-    uint64_t probe;
-    if (!shell_probe<DIM>(g, key, int(t % NCELL), limit, &probe)) continue;
-    const int64_t j = dir_last_le(keys, n, D, probe);
-    if (j >= 0 && key_depth(g, keys[j]) >= key_depth(g, key) + 2) {
-      const uint32_t was = atomicOr(&mark[i], 1u);
-      if (!(was & 1u)) atomicAdd(&ctr->nmarked, 1ull);
-    }
-  }
 }
 
 // Balance of a small tree in one workgroup: keys and marks in LDS, where
@@ -842,18 +860,6 @@ __global__ __launch_bounds__(kScanBig) void k_balance_small(KeyGeom g, const uin
     if (grown && i < n) out[i] = k;
     dir_fill(i, n, k, i + 1 < n ? K[i + 1] : 0, shift, nb, dir);
   }
-}
-
-// The fused-parent check of the first balance pass after adaptation.
-hipError_t launch_fused_check(const KeyGeom& g, const uint64_t* keys, Count cn, const KeyDir& D,
-                              uint32_t* mark, const int32_t* list, DevCtr* ctr, hipStream_t s) {
-  // the list's length is on the device: up to a block per 64 leaves, striding
-  const int64_t kGrid = std::max<int64_t>(1, std::min<int64_t>(1024, cn.n / 64));
-  if (g.dim == 3)
-    k_fused_probe<3><<<unsigned(kGrid), kBlock, 0, s>>>(g, keys, cn, D, list, mark, ctr);
-  else
-    k_fused_probe<2><<<unsigned(kGrid), kBlock, 0, s>>>(g, keys, cn, D, list, mark, ctr);
-  return hipGetLastError();
 }
 
 void launch_balance_small(const KeyGeom& g, const uint64_t* in, int n, const uint32_t* marks, uint64_t* out,
@@ -1588,10 +1594,8 @@ lt_status record_cycle(lt_tree_s* t, const CycleRec& r, hipStream_t s) {
     sc.cnt_dst = &S[3];
     sc.cnt_src = &S[0];
     k_build_dir<<<nleaf, 256, 0, s>>>(K[ki], Count{C, &S[0]}, r.dir_shift, r.dir_nb, t->dir, conv, sc);
-    if (pass == 0)
-      LT_HIP(launch_fused_check(g, K[ki], Count{C, &S[0]}, D, t->mbuf[mi], t->fused, t->dctr, s));
     launch_balance_mark(g, K[ki], Count{C, &S[0]}, C, D, t->mbuf[mi], t->dctr, conv, t->elist,
-                        &t->dctr->nexam[pass & 1], t->elist_cap, s);
+                        &t->dctr->nexam[pass & 1], t->elist_cap, pass == 0 ? t->fused : nullptr, s);
     LT_HIP(hipGetLastError());
     if (pass == r.passes) break;
     st.items.p = &S[3];
@@ -1950,10 +1954,10 @@ lt_status balance_passes(lt_tree t, hipStream_t s) {
       const bool all = pass == 0 && !restricted;
       const int32_t* el = all ? nullptr : t->elist;
       const Count cn{t->n_cur, nullptr};
-      if (pass == 0 && restricted)  // adapt listed the fused parents (the list is sized for its output)
-        LT_HIP(launch_fused_check(t->g, t->kbuf[t->cur], cn, D, t->mbuf[mi], t->fused, t->dctr, s));
+      // adapt listed the fused parents (the list is sized for its output)
+      const int32_t* fl = pass == 0 && restricted ? t->fused : nullptr;
       launch_balance_mark(t->g, t->kbuf[t->cur], cn, t->n_cur, D, t->mbuf[mi], t->dctr, nullptr, el,
-                          &t->dctr->nexam[0], t->elist_cap, s);
+                          &t->dctr->nexam[0], t->elist_cap, fl, s);
       LT_HIP(hipGetLastError());
     }
     LT_TRY(read_ctr(t, s));
