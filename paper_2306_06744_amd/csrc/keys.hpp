@@ -145,17 +145,22 @@ __host__ __device__ inline uint64_t point_key(const KeyGeom& g, uint64_t m) {
   return make_key(g, m, g.dmax);
 }
 
-// Shift coordinate x by delta along axis a; false outside a non-periodic domain.
-__host__ __device__ inline bool shift_coord(const KeyGeom& g, int a, uint64_t x, int64_t delta,
-                                            uint64_t* out) {
-  const int64_t W = int64_t(g.width());
-  int64_t y = int64_t(x) + delta;
-  if ((g.periodic >> a) & 1u) {
-    y = ((y % W) + W) % W;
-  } else if (y < 0 || y >= W) {
-    return false;
-  }
-  *out = uint64_t(y);
+// Moves the Morton index m (no mesh bits) along axis a by 2^s finest units, up or
+// down, bits = dim * s; false outside a non-periodic domain, m unchanged then.  The
+// axis's bits are added to with the others' gaps filled, and subtracted from
+// with them empty, so that carries and borrows pass over them; a sum past the
+// axis's top bit is the wrapped coordinate.  (By way of coordinates, two
+// interleavings and two 64-bit remainders per axis, the searches of balance and
+// connectivity were bound by that arithmetic: at 1.9M 3D leaves the face search
+// took 120 us beside the copy pass, with this 93; a captured 3D cycle of 37 000
+// leaves 320 us, with this 308.)
+__host__ __device__ inline bool shift_morton(const KeyGeom& g, uint64_t* m, int a, bool up, int bits) {
+  const uint64_t axis = ((g.dim == 2 ? 0x5555555555555555ull : 0x1249249249249249ull) << a) &
+                        ((uint64_t(1) << (g.dim * g.dmax)) - 1);
+  const uint64_t x = *m & axis, by = uint64_t(1) << (bits + a);
+  const uint64_t y = (up ? (x | ~axis) + by : x - by) & axis;
+  if ((up ? y <= x : y >= x) && !((g.periodic >> a) & 1u)) return false;
+  *m = (*m & ~axis) | y;
   return true;
 }
 

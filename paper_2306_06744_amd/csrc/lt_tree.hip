@@ -493,14 +493,13 @@ __device__ inline bool shell_probe(const KeyGeom& g, uint64_t key, int cidx, int
   for (int a = 0; a < DIM; ++a) outside += (off[a] < 0 || off[a] > 1) ? 1 : 0;
   const int d = key_depth(g, key);
   if (outside == 0 || outside > limit || d + 2 > g.dmax) return false;
-  uint64_t x[3];
-  demorton(g, key_morton(g, key), x);
-  const int64_t half = int64_t(1) << (g.dmax - d - 1);
-  uint64_t q[3] = {x[0], x[1], x[2]};
+  uint64_t m = key_morton(g, key);
+  const int half = DIM * (g.dmax - d - 1);  // a cell is 2^(dmax - d - 1) wide
   bool ok = true;
 #pragma unroll
-  for (int a = 0; a < DIM; ++a) ok = ok && shift_coord(g, a, x[a], int64_t(off[a]) * half, &q[a]);
-  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
+  for (int a = 0; a < DIM; ++a)
+    if (off[a] != 0) ok = ok && shift_morton(g, &m, a, off[a] > 0, half + (off[a] == 2 ? DIM : 0));
+  *probe = point_key(g, m | (key_mesh_bits(g, key) >> g.mb));
   return ok;
 }
 
@@ -571,22 +570,15 @@ __device__ inline unsigned balance_searches(const KeyGeom& g, uint64_t key, int 
 // Search key of that neighbour; false outside a non-periodic domain.
 template <int DIM>
 __device__ inline bool balance_probe(const KeyGeom& g, uint64_t key, int sub, uint64_t* probe) {
-  const int d = key_depth(g, key);
-  uint64_t x[3];
-  demorton(g, key_morton(g, key), x);
-  const uint64_t S = uint64_t(1) << (g.dmax - d + 1);  // parent size
-  uint64_t q[3] = {0, 0, 0};
+  const int child = DIM * (g.dmax - key_depth(g, key)), parent = child + DIM;
+  uint64_t m = key_morton(g, key);
+  const unsigned c = unsigned(m >> child);  // low bits: the child index
+  m = (m >> parent) << parent;              // the parent's anchor
   bool ok = true;
 #pragma unroll
-  for (int a = 0; a < DIM; ++a) {
-    const uint64_t pa = x[a] & ~(S - 1);
-    q[a] = pa;
-    if ((sub >> a) & 1) {
-      const bool up = (x[a] >> (g.dmax - d)) & 1;
-      ok = ok && shift_coord(g, a, pa, up ? int64_t(S) : -int64_t(S), &q[a]);
-    }
-  }
-  *probe = point_key(g, morton(g, q) | (key_mesh_bits(g, key) >> g.mb));
+  for (int a = 0; a < DIM; ++a)
+    if ((sub >> a) & 1) ok = ok && shift_morton(g, &m, a, (c >> a) & 1u, parent);
+  *probe = point_key(g, m | (key_mesh_bits(g, key) >> g.mb));
   return ok;
 }
 
@@ -1017,17 +1009,12 @@ __global__ __launch_bounds__(256) void k_connect_faces(KeyGeom g, const uint64_t
     if (e < n && f < NF) {
       const uint64_t key = keys[e];
       const int d = key_depth(g, key);
-      uint64_t x[3];
-      demorton(g, key_morton(g, key), x);
-      const uint64_t mhi = key_mesh_bits(g, key) >> g.mb;
-      const int64_t sz = int64_t(1) << (g.dmax - d);
-      const int a = f >> 1;
-      uint64_t q[3] = {x[0], x[1], x[2]};
+      uint64_t m = key_morton(g, key);
       int32_t v;
-      if (!shift_coord(g, a, x[a], (f & 1) ? sz : -sz, &q[a])) {
+      if (!shift_morton(g, &m, f >> 1, f & 1, DIM * (g.dmax - d))) {
         v = -2;
       } else {
-        const int64_t j = dir_last_le(keys, n, D, point_key(g, morton(g, q) | mhi));
+        const int64_t j = dir_last_le(keys, n, D, point_key(g, m | (key_mesh_bits(g, key) >> g.mb)));
         if (j < 0) {
           v = -2;  // unreachable for a complete tree (keys[0] has anchor 0)
         } else if (key_depth(g, keys[j]) <= d) {
@@ -1103,20 +1090,16 @@ __global__ __launch_bounds__(256) void k_connect_fine(KeyGeom g, const uint64_t*
   }
   const uint64_t key = keys[e];
   const int d = key_depth(g, key);
-  uint64_t x[3];
-  demorton(g, key_morton(g, key), x);
-  const uint64_t mhi = key_mesh_bits(g, key) >> g.mb;
-  const int64_t sz = int64_t(1) << (g.dmax - d);
+  uint64_t m = key_morton(g, key);
   const int a = f >> 1, side = f & 1;
-  uint64_t q[3] = {x[0], x[1], x[2]};
-  shift_coord(g, a, x[a], side ? sz : -sz, &q[a]);
+  shift_morton(g, &m, a, side, g.dim * (g.dmax - d));  // a hanging face has a neighbour
   int c = (1 - side) << a, j = 0;
   for (int t = 0; t < g.dim; ++t) {
     if (t == a) continue;
     c |= ((slot >> j) & 1) << t;
     ++j;
   }
-  const uint64_t ck = child_key(g, morton(g, q) | mhi, d, c);
+  const uint64_t ck = child_key(g, m | (key_mesh_bits(g, key) >> g.mb), d, c);
   const int64_t idx = dir_last_le(keys, n, D, ck);
   if (idx < 0 || keys[idx] != ck) {
     atomicOr(err, ERR_UNBALANCED);
