@@ -547,8 +547,12 @@ __device__ inline void fused_probe(const KeyGeom& g, const uint64_t* __restrict_
 // rounds of searches), 16 of a list, which is short enough that one round each
 // on more waves ends sooner.
 // Bound: latency of the directory and key reads.  The passes of a tree built
-// from 1M points (five, the first over every leaf): 340 us (155 the first)
-// against 552 with a lane per leaf and key, searched or not.
+// from 1M points (five, the first over every leaf) take 200 us (75 the first)
+// against 552 with a lane per leaf and key, searched or not.  340 of them were
+// left while every wave added its marks to the counter and every search marked
+// for itself: atomics to one address queue up, so a workgroup adds once, runs of
+// lanes that found the same leaf mark it once, and a leaf's violations are
+// gathered in LDS.
 
 // Bit sub set: the neighbour of the key's parent across the axes of `sub` is
 // searched (see above); limit: the most axes (balance kind).
@@ -604,8 +608,9 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
     }
   constexpr int NC = 1 << DIM, kWaves = kBlock / 64;
   __shared__ uint64_t s_key[kWaves][PER];
-  __shared__ int32_t s_idx[kWaves][PER];
   __shared__ uint16_t s_task[kWaves][PER * (NC - 1)];
+  __shared__ uint8_t s_viol[kWaves][PER];
+  __shared__ unsigned long long s_fresh[kWaves];
   const int64_t n = cn.get();
   const int64_t items = elist ? min(*nexam, ecap) : n;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -622,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
     }
     if (lane < PER) {
       s_key[wv][lane] = key;
-      s_idx[wv][lane] = int32_t(i);
+      s_viol[wv][lane] = 0;
     }
     // the wave's searches, listed by lane
     int at = __popc(need), total = at;
@@ -638,7 +643,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
       if ((need >> sub) & 1u) s_task[wv][at++] = uint16_t(lane * NC + sub);
     wave_lds_fence();
     for (int t = lane; t < ((total + 63) & ~63); t += 64) {
-      bool fresh = false;
+      int32_t hit = -1;  // the leaf to split
       if (t < total) {
         const int w = s_task[wv][t];
         const int l = w / NC, sub = w % NC;
@@ -647,16 +652,28 @@ __global__ __launch_bounds__(kBlock) void k_balance_mark(KeyGeom g, const uint64
         if (balance_probe<DIM>(g, k, sub, &probe)) {
           const int64_t j = dir_last_le(keys, n, D, probe);
           if (j >= 0 && key_depth(g, keys[j]) < key_depth(g, k) - 1) {
-            fresh = !(atomicOr(&mark[j], 1u) & 1u);
-            atomicOr(&mark[s_idx[wv][l]], 2u);
+            hit = int32_t(j);
+            s_viol[wv][l] = 1;
           }
         }
       }
+      // runs of lanes that found the same leaf mark it once
+      const int32_t before = __shfl_up(hit, 1, 64);
+      bool fresh = hit >= 0 && (lane == 0 || before != hit);
+      if (fresh) fresh = !(atomicOr(&mark[hit], 1u) & 1u);
       nfresh += __popcll(__ballot(fresh));
     }
     wave_lds_fence();  // the lists are read before the next leaves overwrite them
+    if (lane < PER && s_viol[wv][lane]) atomicOr(&mark[i], 2u);
   }
-  if (lane == 0 && nfresh) atomicAdd(&ctr->nmarked, nfresh);
+  // one addition for the workgroup: thousands to one address queue up
+  if (lane == 0) s_fresh[wv] = nfresh;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long all = 0;
+    for (int w = 0; w < kWaves; ++w) all += s_fresh[w];
+    if (all) atomicAdd(&ctr->nmarked, all);
+  }
 }
 
 constexpr int kMarkList = 16;  // listed leaves a wave takes at a time
