@@ -144,8 +144,16 @@ __device__ inline void tensor_apply(const double* __restrict__ Mx, const double*
 // One thread per (new element, variable) -- used for 2D.  Consecutive
 // threads handle consecutive new elements, so every load and store of one
 // point index is a contiguous run across the wave in the element-fastest layout.
+// Bound: the latency of a wave's rounds of loads, one per kind that its elements
+// have and one per child of a fused family, with few waves per SIMD (a thread
+// holds its element).  Every kind's first values come in one round, and a fused
+// family's next child is read while the last is worked on; one wave to a
+// workgroup, so that a wave of copies frees its place at once and the registers
+// of p = 6 and 7 fit.  Most leaves changed, whole call: p = 5, 16 000 leaves 50.3
+// -> 45.4 us; p = 3, 65 000 leaves 59 -> 51; p = 6 533 -> 209; p = 7, 4000 leaves
+// 214 -> 133.
 template <int DIM, int N>
-__global__ __launch_bounds__(256) void k_transfer(const double* __restrict__ ops,
+__global__ __launch_bounds__(64) void k_transfer(const double* __restrict__ ops,
                                                   const int32_t* __restrict__ src,
                                                   const int8_t* __restrict__ kind, Count cn,
                                                   const double* __restrict__ uo, int64_t ldo,
@@ -160,18 +168,20 @@ __global__ __launch_bounds__(256) void k_transfer(const double* __restrict__ ops
   double* O = un + int64_t(v) * NP * ldn;
   const int kd = kind[j];
   const int64_t s = src[j];
+  // One round of loads for every kind (the element copied or refined, the first
+  // child of a fused family): lanes of a wave differ in kind.
+  double in[NP], out[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) in[i] = U[i * ldo + s];
   if (kd == 0) {
 #pragma unroll
-    for (int i = 0; i < NP; ++i) O[i * ldn + j] = U[i * ldo + s];
+    for (int i = 0; i < NP; ++i) O[i * ldn + j] = in[i];
     return;
   }
   const double* A = ops;
   const double* P = ops + 2 * N * N;
-  double in[NP], out[NP];
   if (kd > 0) {
     const int c = kd - 1;
-#pragma unroll
-    for (int i = 0; i < NP; ++i) in[i] = U[i * ldo + s];
     tensor_apply<DIM, N>(A + (c & 1) * N * N, A + ((c >> 1) & 1) * N * N, A + ((c >> 2) & 1) * N * N,
                          in, out);
 #pragma unroll
@@ -182,12 +192,16 @@ __global__ __launch_bounds__(256) void k_transfer(const double* __restrict__ ops
 #pragma unroll
   for (int i = 0; i < NP; ++i) acc[i] = 0.0;
   for (int c = 0; c < NC; ++c) {
+    double next[NP];  // the next child's values, while this one's are worked on
+    const int cn = c + 1 < NC ? c + 1 : c;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) in[i] = U[i * ldo + s + c];
+    for (int i = 0; i < NP; ++i) next[i] = U[i * ldo + s + cn];
     tensor_apply<DIM, N>(P + (c & 1) * N * N, P + ((c >> 1) & 1) * N * N, P + ((c >> 2) & 1) * N * N,
                          in, out);
 #pragma unroll
     for (int i = 0; i < NP; ++i) acc[i] += out[i];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) in[i] = next[i];
   }
 #pragma unroll
   for (int i = 0; i < NP; ++i) O[i * ldn + j] = acc[i];
@@ -1086,8 +1100,8 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     }
     return e;
   } else {
-    dim3 grid(unsigned((n.n + 255) / 256), unsigned(nvar));
-    k_transfer<DIM, N><<<grid, 256, 0, s>>>(ops, src, kind, n, uo, ldo, un, ldn);
+    dim3 grid(unsigned((n.n + 63) / 64), unsigned(nvar));
+    k_transfer<DIM, N><<<grid, 64, 0, s>>>(ops, src, kind, n, uo, ldo, un, ldn);
     return hipGetLastError();
   }
 }

@@ -451,6 +451,35 @@ def test_readbacks_behind_a_long_queue_and_in_threads():
         del trees, t
 
 
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5, 6, 7])
+def test_transfer_2d_at_workgroup_edges(p):
+    """The 2D transfer with fewer leaves than a workgroup of 64, just around it
+    and many, all refined, all fused and mixed within every wave, and a
+    leading dimension of its own.  FP64 on both sides (dense operators against
+    sum factorisation): 1e-13."""
+    import torch
+    import paper_2306_06744_amd as lt
+    from gpu_util import class_errors, dense_expected
+    npts = (p + 1) ** 2
+    for depth in (1, 3, 4):
+        for seed, (pr, pc) in enumerate([(1.0, 0.0), (0.0, 1.0), (0.3, 0.6)]):
+            t = lt.Tree.uniform(2, 0, 7, depth=depth)
+            n_old = t.size()
+            f = synth.random_flags(seed, n_old, pr, pc)
+            f[4 * (n_old // 8):4 * (n_old // 8) + 4] = -1 if pc else 1    # one complete family at least
+            t.adapt(torch.from_numpy(f).cuda())
+            u = synth.random_solution(seed, 3, npts, n_old)
+            ud = torch.full((3, npts, n_old + 3), float("nan"), dtype=torch.float64, device="cuda")
+            ud[:, :, :n_old] = torch.from_numpy(u).cuda()
+            got = t.transfer(p, ud).cpu().numpy()
+            src, kind = (v.cpu().numpy() for v in t.mapping())
+            js = np.arange(len(kind))
+            exp = dense_expected(2, p, u, src, kind, js)
+            for name, (l2, mx, k) in class_errors(got[:, :, js], exp, kind).items():
+                print("2D transfer", p, depth, seed, name, k, l2, flush=True)
+                assert l2 <= 1e-13 and mx <= 1e-13
+
+
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("depth", [1, 2, 3, 4])
 def test_interpolation_groups_at_list_edges(depth, mixed):
