@@ -103,7 +103,8 @@ __global__ void k_clear_scan(uint64_t* status, int64_t ntiles, DevCtr* ctr, int 
 }
 
 // The same done by a kernel that runs ahead of the scan anyway (a launch less:
-// in a captured cycle 5 us each, of which it had eight).  ctr null: nothing.
+// without seven of them a captured 3D cycle of 37 000 leaves takes 312 us instead
+// of 336).  ctr null: nothing.
 struct ScanClear {
   uint64_t* status;
   int64_t ntiles;
