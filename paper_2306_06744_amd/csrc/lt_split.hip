@@ -105,12 +105,15 @@ __global__ void k_build_split_vec(const double* __restrict__ ops1d, int n1, int 
 }
 
 // Work lists from the mapping: R = first child of each refined family (kind
-// 1), F = each fused parent (kind -1).  Waves take rounds of 64 leaves and
+// 1) whose nc children all lie among the leaves, F = each fused parent (kind
+// -1).  (The refinement stores a family whole.  Only a captured cycle that
+// outgrew its capacity holds a family cut off at the end; its result is
+// discarded, but nothing may be stored past its leaves.)  Waves take rounds of 64 leaves and
 // count by ballots; a workgroup appends its entries, in leaf order, by one
 // atomic per list (the workgroups' order is arbitrary: every family and every
 // parent is computed on its own).
 __global__ __launch_bounds__(kBlock) void k_split_lists(const int8_t* __restrict__ kind, Count cn,
-                                                        int32_t* __restrict__ R, int64_t* nR,
+                                                        int nc, int32_t* __restrict__ R, int64_t* nR,
                                                         int32_t* __restrict__ F, int64_t* nF) {
   constexpr int kWaves = kBlock / 64;
   __shared__ int cr[kWaves], cf[kWaves];
@@ -121,7 +124,11 @@ __global__ __launch_bounds__(kBlock) void k_split_lists(const int8_t* __restrict
   const int64_t base = int64_t(blockIdx.x) * kTileMin + w * (64 * kItems) + lane;
   int kd[kItems];
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) kd[k] = base + 64 * k < n ? int(kind[base + 64 * k]) : 0;
+  for (int k = 0; k < kItems; ++k) {
+    const int64_t j = base + 64 * k;
+    kd[k] = j < n ? int(kind[j]) : 0;
+    if (kd[k] == 1 && j + nc > n) kd[k] = 0;
+  }
   int r = 0, f = 0;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
@@ -472,8 +479,8 @@ lt_status launch_split_transfer(lt_tree_s* t, Count cn, int p, int nvar, const d
   int64_t *nR = &t->dctr->total, *nF = &t->dctr->nfgroups;
   auto lists = [&](hipStream_t q) -> lt_status {
     if (!cn.p) LT_TRY_STATUS(clear_counters(t->dctr, q));  // a captured cycle's mapping cleared them
-    k_split_lists<<<unsigned((n + kTileMin - 1) / kTileMin), kBlock, 0, q>>>(t->map_kind, cn, t->split_R, nR,
-                                                                           t->split_F, nF);
+    k_split_lists<<<unsigned((n + kTileMin - 1) / kTileMin), kBlock, 0, q>>>(t->map_kind, cn, nc, t->split_R,
+                                                                           nR, t->split_F, nF);
     return LT_OK;
   };
   if (lists_first(n)) LT_TRY_STATUS(lists(s));

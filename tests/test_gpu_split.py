@@ -62,3 +62,62 @@ def test_split_rejects_other_degrees():
     u = torch.zeros((1, 27, g.sizes()[1]), dtype=torch.float64, device="cuda")
     with pytest.raises(lt.LtError, match="ARG"):
         g.transfer(2, u, precision=1)
+
+
+def _overflow_case(dim):
+    """Flags by cycle, the cycles to warm up, and the arguments of a tree whose
+    next cycle's balance splits leaves that the adaptation kept."""
+    if dim == 3:
+        w = synth.workload_3d_extruded(2007)
+        fa = lambda c: dict(centres=w.centres_at(c), r_in=w.r_in, r_out=w.r_out, nodes01=synth.gl_nodes01(3),
+                            lo=w.lo, length=w.length, dist_axes=w.dist_axes, periodic_dist=w.periodic_dist)
+        return fa, 1, (3, w.d_min, w.d_max), 3, 5
+    fa = lambda c: dict(centres=[(0.5 + 0.3 * c, 0.2 * c), (-2 + 0.1 * c, -3.0)], r_in=1.5, r_out=1.8,
+                        nodes01=synth.gl_nodes01(7), lo=(-5.0, -5.0), length=10.0, dist_axes=2,
+                        periodic_dist=True)
+    return fa, 4, (2, 3, 9), 7, 4
+
+
+@pytest.mark.parametrize("kept", [1, 2, -1])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_captured_overflow_stays_inside_the_arrays(dim, kept):
+    """A captured split cycle whose balance outgrows the capacity within a
+    refined family (its first `kept` children below the capacity, -1: all but
+    one) writes nothing past either solution array, whose leading dimension is
+    the capacity, and leaves the tree as it was."""
+    import torch
+    import paper_2306_06744_amd as lt
+    fa, warm, geom, p, nvar = _overflow_case(dim)
+    nc, npts = 1 << dim, (p + 1) ** dim
+    o = oracle.Tree(*geom)
+    t = lt.Tree.uniform(*geom)
+    for c in range(warm):
+        o.adapt(o.flag(**fa(c)))
+        o.balance()
+        t.adapt(t.flag(**fa(c)))
+        t.balance()
+    assert_same_tree(t, o, "before")
+    n0, keys0 = o.size(), o.keys()
+    o.adapt(o.flag(**fa(warm)))
+    n_adapt = o.size()
+    o.balance()
+    _, kind = o.map()
+    first = np.flatnonzero(kind == 1)
+    first = first[(first >= max(n_adapt, n0)) & (first + nc < o.size())]
+    cap = int(first[len(first) // 2]) + (kept if kept > 0 else nc - 1)
+    print("overflow", dim, kept, n0, n_adapt, o.size(), "capacity", cap, flush=True)
+    assert n_adapt <= cap < o.size() and len(first)
+    size, guard = nvar * npts * cap, 4096
+    flat = [torch.zeros(size + guard, dtype=torch.float64, device="cuda") for _ in range(2)]
+    for f in flat:
+        f[size:] = 7.0
+    u = [f[:size].view(nvar, npts, cap) for f in flat]
+    cyc = lt.Cycle(t, p, nvar, cap, u, fa(warm), precision=1)
+    with pytest.raises(lt.LtError) as ei:
+        cyc.run(fa(warm))
+    assert ei.value.status == 9
+    torch.cuda.synchronize()
+    for f in flat:
+        assert bool((f[size:] == 7.0).all())
+    assert t.size() == n0 and np.array_equal(t.keys().cpu().numpy().view(np.uint64), keys0)
+    del cyc
