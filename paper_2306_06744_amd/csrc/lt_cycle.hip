@@ -309,8 +309,8 @@ lt_status lt_cycle_create(lt_tree t, const lt_cycle_desc* d, void* stream, lt_cy
   c->d.flag_template = nullptr;
   lt_status st = LT_OK;
   if (dev_malloc(t->A, reinterpret_cast<void**>(&c->dsz), 4 * sizeof(int64_t)) != hipSuccess ||
-      hipHostMalloc(&c->hsz, 4 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(&c->flag_host, flag_args_size() * size_t(c->nmesh), hipHostMallocDefault) != hipSuccess)
+      hipHostMalloc(&c->hsz, 4 * sizeof(int64_t), kPinnedFlags) != hipSuccess ||
+      hipHostMalloc(&c->flag_host, flag_args_size() * size_t(c->nmesh), kPinnedFlags) != hipSuccess)
     st = fail(LT_ERR_OOM, "cycle state");
   if (st == LT_OK && !t->balanced) st = lt_balance(t, stream);  // the graph starts from a balanced tree
   if (st == LT_OK) st = reserve(c, s);

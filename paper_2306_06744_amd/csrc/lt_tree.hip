@@ -1394,7 +1394,7 @@ hipError_t pinned_get(HostCtr** two) {
     }
   }
   hipError_t e = hipSuccess;
-  if (!q) e = hipHostMalloc(&q, 2 * sizeof(HostCtr), hipHostMallocPortable);
+  if (!q) e = hipHostMalloc(&q, 2 * sizeof(HostCtr), kPinnedFlags);
   if (e == hipSuccess) std::memset(q, 0, 2 * sizeof(HostCtr));
   *two = static_cast<HostCtr*>(q);
   return e;

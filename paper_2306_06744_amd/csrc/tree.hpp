@@ -33,6 +33,11 @@ struct HostCtr {
   uint64_t seq;
 };
 
+// Pinned memory that a running kernel and the host share.  Coherent by name:
+// under other flags alone the runtime's environment decides, and a kernel's
+// stores need not become visible, or in order, before it ends.
+constexpr unsigned kPinnedFlags = hipHostMallocPortable | hipHostMallocCoherent;
+
 void set_error(const std::string& msg);
 lt_status fail(lt_status s, const std::string& msg);
 
