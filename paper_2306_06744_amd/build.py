@@ -19,7 +19,7 @@ BUILD = os.path.join(HERE, "_build")
 SOURCES = ["lt_tree.hip", "lt_flag.hip", "lt_transfer.hip", "lt_split.hip", "lt_mlp.hip", "lt_cycle.hip",
            "lt_build.hip", "lt_fr.hip"]
 NO_CONTRACT = {"lt_flag.hip", "lt_build.hip"}
-HEADERS = ["keys.hpp", "scan.hpp", "tree.hpp"]
+HEADERS = ["keys.hpp", "readback.hpp", "scan.hpp", "tree.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

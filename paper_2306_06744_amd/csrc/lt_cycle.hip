@@ -335,9 +335,9 @@ lt_status lt_cycle_run(lt_cycle c, const lt_flag_params* fp, void* stream, int* 
     if (fp[m].p != c->tmpl[m].p) return fail(LT_ERR_ARG, "flag parameters need each mesh's template p");
   LT_TRY_STATUS(fill_flag_table(t->g, fp, c->nmesh, c->flag_host));
   const int q = c->parity;
-  const uint64_t seen = __atomic_load_n(&t->hctr->seq, __ATOMIC_ACQUIRE);
+  const ReadTicket ticket = read_expect(&t->hctr->r);
   if (hipGraphLaunch(c->exec[q], s) != hipSuccess) return fail(LT_ERR_HIP, "graph launch");
-  LT_TRY_STATUS(await_read(t->hctr, seen, s));
+  LT_TRY_STATUS(await_read(t->hctr, ticket, s));
   unsigned err = t->hctr->c.err;
   // an unfinished balance also shows as missing fine leaves at hanging faces
   if (err & ERR_BALANCE_PASSES) err &= ~ERR_UNBALANCED;

@@ -8,7 +8,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
@@ -1324,7 +1323,7 @@ lt_status prep_scan_conn(lt_tree t, int64_t n_items, hipStream_t stream, int fla
 // 209 and 226 instead of 265.
 constexpr int kCtrWords = int(sizeof(DevCtr) / 8);
 static_assert(sizeof(DevCtr) % 8 == 0 && kCtrWords <= 32, "counters are published by 32 lanes");
-static_assert(offsetof(HostCtr, seq) == kCtrWords * 8, "the number follows the counters");
+static_assert(offsetof(HostCtr, r.seq) == kCtrWords * 8, "the number follows the counters");
 
 __global__ void k_publish(DevCtr* ctr, uint64_t* host, const int64_t* more, int64_t* more_host, int words) {
   const int lane = threadIdx.x;
@@ -1348,25 +1347,21 @@ lt_status publish(DevCtr* dev, HostCtr* host, hipStream_t stream, const int64_t*
   return LT_OK;
 }
 
-lt_status await_read(const HostCtr* host, uint64_t seen, hipStream_t stream) {
-  // a short wait watches the number; a long one, or one that cannot end (a
-  // stream being captured, a device error), is the runtime's
-  const auto start = std::chrono::steady_clock::now();
-  for (;;) {
-    for (int i = 0; i < 64; ++i)
-      if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) != seen) return LT_OK;
-    if (std::chrono::steady_clock::now() - start > std::chrono::milliseconds(1)) break;
-  }
-  LT_HIP(hipStreamSynchronize(stream));
-  if (__atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == seen)
-    return fail(LT_ERR_INTERNAL, "a readback did not arrive");
+lt_status await_read(HostCtr* host, ReadTicket ticket, hipStream_t stream) {
+  hipError_t e = hipSuccess;
+  const ReadEnd end = read_await(&host->r, ticket, std::chrono::milliseconds(1), [&] {
+    e = hipStreamSynchronize(stream);
+    return e == hipSuccess;
+  });
+  if (end == ReadEnd::failed) return fail(LT_ERR_HIP, std::string("readback: ") + hipGetErrorString(e));
+  if (end == ReadEnd::missing) return fail(LT_ERR_INTERNAL, "a readback did not arrive");
   return LT_OK;
 }
 
 lt_status read_back(DevCtr* dev, HostCtr* host, hipStream_t stream) {
-  const uint64_t seen = __atomic_load_n(&host->seq, __ATOMIC_ACQUIRE);
+  const ReadTicket ticket = read_expect(&host->r);
   LT_TRY(publish(dev, host, stream));
-  return await_read(host, seen, stream);
+  return await_read(host, ticket, stream);
 }
 
 // Pinned memory of the trees' mirrors.  Allocating and freeing a block takes 20

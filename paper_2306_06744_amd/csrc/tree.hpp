@@ -8,6 +8,7 @@
 
 #include "../../include/lt.h"
 #include "keys.hpp"
+#include "readback.hpp"
 #include "scan.hpp"
 
 namespace lt {
@@ -30,7 +31,7 @@ struct DevCtr {
 // with (see k_publish).
 struct HostCtr {
   DevCtr c;
-  uint64_t seq;
+  ReadSeq r;
 };
 
 // Pinned memory that a running kernel and the host share.  Coherent by name:
@@ -164,11 +165,12 @@ lt_status create_tree(const lt_geom* geom, hipStream_t s, lt_tree_s** out);
 // Copy the device counters to the pinned mirror and wait for the stream.
 lt_status read_ctr(lt_tree_s* t, hipStream_t stream);
 // Enqueues the readback of the counters `dev` and, if given, of `words` further
-// ones to pinned memory; await_read waits for the one after readback number
-// `seen` and for all work before it on the stream.
+// ones to pinned memory (read_expect before it, or before the launch of a graph
+// that holds one); await_read waits for it and for all work before it on the
+// stream.
 lt_status publish(DevCtr* dev, HostCtr* host, hipStream_t stream, const int64_t* more = nullptr,
                   int64_t* more_host = nullptr, int words = 0);
-lt_status await_read(const HostCtr* host, uint64_t seen, hipStream_t stream);
+lt_status await_read(HostCtr* host, ReadTicket ticket, hipStream_t stream);
 // p[0, n) = v (a kernel: a captured graph must hold no memset node).
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream);
 // Zero the counters, but for the error word and the balance lists' lengths.
