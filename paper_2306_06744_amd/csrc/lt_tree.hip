@@ -13,6 +13,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "tree.hpp"
@@ -1368,41 +1369,37 @@ lt_status read_back(DevCtr* dev, HostCtr* host, hipStream_t stream) {
 // to 25 us each (with a device-wide wait for what is in flight), so up to
 // kPinnedKept blocks of destroyed trees wait here for the next ones: a tree from
 // 1M points, balanced and destroyed, takes 887 us instead of 993.
-constexpr size_t kPinnedKept = 16;
+constexpr int kPinnedKept = 16;
 struct PinnedPool {
   std::mutex mu;
-  std::vector<void*> free_;
+  void* kept[kPinnedKept] = {};
+  int n = 0;
 };
-PinnedPool& pinned_pool() {
-  static PinnedPool* p = new PinnedPool;  // outlives every tree
-  return *p;
-}
+// Nothing to construct or destroy at run time, so that it outlives every tree
+// and no call on it can throw.
+static_assert(std::is_trivially_destructible<PinnedPool>::value, "lives until the process ends");
+static PinnedPool g_pinned;
 
 hipError_t pinned_get(HostCtr** two) {
-  PinnedPool& P = pinned_pool();
   void* q = nullptr;
   {
-    std::lock_guard<std::mutex> l(P.mu);
-    if (!P.free_.empty()) {
-      q = P.free_.back();
-      P.free_.pop_back();
-    }
+    std::lock_guard<std::mutex> l(g_pinned.mu);
+    if (g_pinned.n > 0) q = g_pinned.kept[--g_pinned.n];
   }
   hipError_t e = hipSuccess;
   if (!q) e = hipHostMalloc(&q, 2 * sizeof(HostCtr), kPinnedFlags);
   if (e == hipSuccess) std::memset(q, 0, 2 * sizeof(HostCtr));
-  *two = static_cast<HostCtr*>(q);
+  *two = e == hipSuccess ? static_cast<HostCtr*>(q) : nullptr;
   return e;
 }
 
 // After the last work that may write it.
 void pinned_put(HostCtr* two) {
   if (!two) return;
-  PinnedPool& P = pinned_pool();
   {
-    std::lock_guard<std::mutex> l(P.mu);
-    if (P.free_.size() < kPinnedKept) {
-      P.free_.push_back(two);
+    std::lock_guard<std::mutex> l(g_pinned.mu);
+    if (g_pinned.n < kPinnedKept) {
+      g_pinned.kept[g_pinned.n++] = two;
       return;
     }
   }
