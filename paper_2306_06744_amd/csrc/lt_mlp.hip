@@ -233,8 +233,8 @@ struct NetOff {
 // Forward and backward of the mean softmax cross-entropy over the workgroup's
 // tiles of 32 rows; part[blockIdx.x][] receives the sums of the gradients over
 // those rows.  Eight waves: in the row-by-column products wave w takes row
-// tile w & 3 and half w >> 2 of the columns, so that a lane's ReLU masks stay
-// in its registers from the forward to the backward pass; in the weight
+// tile w & 1 (16 rows) and quarter w >> 1 of the columns, so that a lane's
+// ReLU masks stay in its registers from the forward to the backward pass; in the weight
 // gradients (contractions over the rows) wave w takes output tile w of layer 1
 // and the sums stay in accumulators over all tiles.  Each activation and
 // back-propagated error is stored once per orientation that a later product

@@ -191,3 +191,11 @@ def test_training_step_at_tile_edges(B):
     step = lr * G / (np.abs(G) + 1e-8)
     ulp = 2.0 ** -23
     assert np.all(np.abs(got - (params - step)) <= ulp * (4 * np.abs(step) + np.abs(params) + lr))
+
+
+@pytest.mark.parametrize("B", [15, 16, 17, 31, 32, 33, 128 * 32, 128 * 32 + 1, 2 * 128 * 32 + 1])
+def test_training_step_at_row_tile_edges(B):
+    """The same checks at the edges that the training kernel has: the 16 rows
+    of a matrix-core tile, the 32 rows of a workgroup's tile, and the first
+    sizes at which one of the 128 workgroups takes a second and a third."""
+    test_training_step_at_tile_edges(B)
