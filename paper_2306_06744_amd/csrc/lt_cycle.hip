@@ -119,7 +119,6 @@ lt_status reserve(lt_cycle c, hipStream_t s) {
     LT_TRY_STATUS(grow(t->A, &t->split_R, &t->split_R_cap, C));
     LT_TRY_STATUS(grow(t->A, &t->split_F, &t->split_F_cap, C));
   }
-  if (c->d.mlp) LT_TRY_STATUS(mlp_reserve(c->d.mlp, C));
   if (hipStreamSynchronize(s) != hipSuccess) return fail(LT_ERR_HIP, "sync");
   return LT_OK;
 }

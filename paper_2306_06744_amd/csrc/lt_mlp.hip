@@ -965,8 +965,6 @@ struct lt_mlp_s {
   // training: the workgroups' partial gradients
   float* part = nullptr;
   int64_t part_cap = 0;
-  __bf16* X = nullptr;  // features for lt_flag_mlp
-  int64_t xcap = 0;
 
   static constexpr int64_t off_b1 = lt::NetOff::b1, off_b2 = lt::NetOff::b2, off_b3 = lt::NetOff::b3;
   static constexpr int64_t nparam = lt::NetOff::n;
@@ -1045,17 +1043,6 @@ lt_status mlp_backward(lt_mlp_s* m, const __bf16* X, const int8_t* y, int64_t B,
 }  // namespace lt
 
 namespace lt {
-
-lt_status mlp_reserve(lt_mlp m, int64_t n) {
-  if (m->xcap >= n) return LT_OK;
-  (void)dev_free(m->A, m->X);
-  m->X = nullptr;
-  m->xcap = 0;
-  if (dev_malloc(m->A, reinterpret_cast<void**>(&m->X), size_t(n) * 320 * 2) != hipSuccess)
-    return fail(LT_ERR_OOM, "MLP features");
-  m->xcap = n;
-  return LT_OK;
-}
 
 lt_status launch_mlp_flag(lt_tree_s* t, lt_mlp m, Count n, const double* u, int64_t ld, float conf_min,
                           int8_t* flags, float* conf, hipStream_t s) {
@@ -1168,7 +1155,6 @@ lt_status lt_flag_mlp(lt_tree t, lt_mlp m, const lt_flag_params* fallback, const
   if (ld < n) return fail(LT_ERR_ARG, "leading dimension too small");
   LT_TRY_STATUS(launch_flag(t->g, fallback, t->kbuf[t->cur], n, flags, s));
   if (n == 0) return LT_OK;
-  LT_TRY_STATUS(mlp_reserve(m, n));
   return launch_mlp_flag(t, m, Count{n, nullptr}, u, ld, conf_min, flags, conf, s);
 }
 
@@ -1233,7 +1219,7 @@ lt_status lt_flag_modal(lt_tree t, int p, const double* u, int64_t ld, double ta
 void lt_mlp_destroy(lt_mlp m) {
   if (!m) return;
   (void)hipDeviceSynchronize();
-  void* ptrs[] = {m->P, m->G, m->M1, m->M2, m->W1, m->W2, m->W3, m->W2T, m->T4, m->H1, m->H2, m->part, m->X};
+  void* ptrs[] = {m->P, m->G, m->M1, m->M2, m->W1, m->W2, m->W3, m->W2T, m->T4, m->H1, m->H2, m->part};
   for (void* p : ptrs) (void)dev_free(m->A, p);
   delete m;
 }

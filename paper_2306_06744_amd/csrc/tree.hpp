@@ -190,8 +190,7 @@ lt_status prepare_split(lt_tree_s* t, int p, hipStream_t s);
 
 // Learned flags over a count that may live on the device: features of u
 // (5 variables x 64 points), the fused network and the decision over the
-// geometric flags already in `flags`.  mlp_reserve sizes the feature buffer.
-lt_status mlp_reserve(lt_mlp m, int64_t n);
+// geometric flags already in `flags`.
 lt_status launch_mlp_flag(lt_tree_s* t, lt_mlp m, Count n, const double* u, int64_t ld, float conf_min,
                           int8_t* flags, float* conf, hipStream_t s);
 

@@ -199,3 +199,23 @@ def test_training_step_at_row_tile_edges(B):
     of a matrix-core tile, the 32 rows of a workgroup's tile, and the first
     sizes at which one of the 128 workgroups takes a second and a third."""
     test_training_step_at_tile_edges(B)
+
+
+def test_learned_flags_allocate_nothing():
+    """Features and network are one pass over the solution: the learned flags
+    of a mesh take no device memory of their own, and fail for none."""
+    import torch
+    import paper_2306_06744_amd as lt
+    a = lt.TorchAllocator()
+    lt.set_allocator(a)
+    try:
+        m = lt.MLP(synth.mlp_init(5))
+        t, o, w, nodes = small_tree()
+        u = t.vortex_field(w.centres_at(0), w.strengths, nodes, w.lo, w.length)
+        a.limit = a.held
+        f, conf = t.flag_mlp(m, u, w.centres_at(0), 3.0, 3.6, nodes, w.lo, w.length)
+        torch.cuda.synchronize()
+        a.limit = None
+        assert f.numel() == t.size() and bool(((f >= -1) & (f <= 1)).all())
+    finally:
+        lt.set_allocator(None)
