@@ -12,8 +12,9 @@
  *     ordinary host memory read during the call only.
  *   - `stream` is a hipStream_t (may be NULL for the null stream).  Kernels are
  *     enqueued on it in call order.  Calls that must learn a size on the host
- *     (lt_build, lt_adapt, lt_balance, lt_connect, lt_map) synchronise the
- *     stream before returning; lt_flag and lt_transfer do not.
+ *     (lt_build, lt_adapt, lt_balance, lt_connect, lt_map) return once
+ *     everything enqueued on the stream so far, their own kernels included,
+ *     has ended; lt_flag and lt_transfer do not wait.
  *   - Every call returns an lt_status; no exception crosses the ABI.  The text
  *     of the last error of the calling thread is lt_last_error().  On an
  *     error the tree's leaves, its old tree and its connectivity and mapping
@@ -317,7 +318,8 @@ lt_status lt_get_tuning(lt_tree t, lt_tune* tune);
  * (LT_ERR_STATE otherwise), a tree periodic on every axis and a single mesh
  * (LT_ERR_ARG), p 1..3 in 3D and 1..7 in 2D.  Asynchronous; the tree keeps the
  * fluxes of its hanging faces ((2^(dim-1) + 1) (dim+2) (p+1)^(dim-1) doubles a
- * row) and, for lt_fr_rk3, one state array ((dim+2) (p+1)^dim doubles a leaf).
+ * row), where to find them (2 dim int32 and one byte a leaf) and, for
+ * lt_fr_rk3, one state array ((dim+2) (p+1)^dim doubles a leaf).
  * ------------------------------------------------------------------------ */
 
 /* Common normal fluxes at every element face (Section 4.3, Algorithm

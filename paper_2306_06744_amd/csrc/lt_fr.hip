@@ -226,16 +226,6 @@ __device__ inline void euler_flux(const double* U, int a, double gm1, double* F)
   F[DIM + 1] = (U[DIM + 1] + p) * ua;
 }
 
-// One component of the flux along axis a (recomputes the pressure).
-template <int DIM>
-__device__ inline double flux_comp(const double* U, int a, int v, double gm1) {
-  const double ua = U[1 + a] / U[0];
-  if (v == 0) return U[1 + a];
-  const double p = pressure<DIM>(U, gm1);
-  if (v == DIM + 1) return (U[DIM + 1] + p) * ua;
-  return U[v] * ua + (v - 1 == a ? p : 0.0);
-}
-
 // Rusanov flux across a face normal to axis a, UL on the low side.
 template <int DIM>
 __device__ inline void rusanov(const double* UL, const double* UR, int a, double gamma, double* F) {

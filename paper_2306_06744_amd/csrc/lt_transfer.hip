@@ -677,7 +677,7 @@ __global__ __launch_bounds__(64 * N) void k_refine3(const double* __restrict__ o
 // pass writes those here) or lies past the end repeats the loads and stores
 // of the entry's first refined lane of degree N -- the same values to the
 // same address -- so that every lane stores each row.  Every listed entry has
-// such a lane (k_group_list_mixed lists (group, N) only for a group with a
+// such a lane (k_group_list lists (group, N) only for a group with a
 // refined element of degree N and no fused one); the entries fetched ahead
 // past the end, which are never stored, fall back to the lane's own element.
 // The mesh-degree table is read from LDS, so that a group's map needs no

@@ -236,8 +236,8 @@ struct WaveOut {
   int all;   // of the whole block
 };
 
-// Exclusive scan over the block's waves of two small counts packed in one
-// word (each below 2^31 over a block), every thread calling with its wave's.
+// Exclusive scans over the block's waves of two small counts (their sums over
+// a block below 2^31), every thread calling with its wave's.
 __device__ inline void block_waves(int a, int b, WaveOut* A, WaveOut* B) {
   constexpr int kWaves = kScanBig / 64;
   __shared__ int wa[kWaves], wb[kWaves];

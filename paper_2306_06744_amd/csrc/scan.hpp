@@ -19,10 +19,9 @@ constexpr int kBlock = 256;   // workgroup of the plain kernels
 constexpr int kItems = 8;     // items per thread in scan-emit kernels
 // Scan-emit kernels over the leaves on the critical path (adapt, balance
 // refinement) run 1024-thread tiles, each wave over rounds of 64 consecutive
-// leaves.  Short scans (transfer groups) and scans that may run beside another
-// stream's kernels (connectivity rows, the split transfer's lists), where a
-// 1024-thread workgroup would wait for a whole free CU, keep 256-thread tiles
-// of 2048 items.
+// leaves.  Scans that may run beside another stream's kernels (connectivity
+// rows), where a 1024-thread workgroup would wait for a whole free CU, and
+// those of the construction from points keep 256-thread tiles of 2048 items.
 constexpr int kScanBig = 1024;
 constexpr int kScanSmall = kBlock;
 constexpr int kRounds = 8;  // rounds of a wave in a large tile

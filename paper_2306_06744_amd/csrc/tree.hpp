@@ -196,21 +196,21 @@ lt_status launch_mlp_flag(lt_tree_s* t, lt_mlp m, Count n, const double* u, int6
 
 lt_status launch_transfer(lt_tree_s* t, int p, const double* ops, int nvar, const double* u_old,
                           int64_t ld_old, double* u_new, int64_t ld_new, hipStream_t s);
-// FP64 transfer of an ensemble with per-mesh degrees (lt_set_mesh_degree), over
-// a count that may live on the device; asynchronous.  keys: the new leaves'
-// keys (each element's mesh, hence its degree, comes from its key), which a
-// captured cycle holds in another buffer than the tree's current one.
-// The tree's second stream for the interpolation passes of a 3D transfer and
-// its fork/join events, made on first use (default priority, non-blocking).
 // Whether a transfer builds its work lists before the fork: beside the copy
 // pass their short kernels wait for wave slots, which the interpolation passes
 // then wait for.  Up to 2^18 new leaves the passes take as long as the copy
 // and the lists go first (split transfer of 117 000 leaves, two thirds of
 // them refined: 354 us against 414); beyond, the copy outlasts them all.
 inline bool lists_first(int64_t n) { return n <= int64_t(1) << 18; }
+// The tree's second stream for the interpolation passes of a 3D transfer and
+// its fork/join events, made on first use (default priority, non-blocking).
 lt_status transfer_side(lt_tree_s* t, hipStream_t* side, hipEvent_t* fork, hipEvent_t* join);
-lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, int nvar, const double* uo, int64_t ldo, double* un, int64_t ldn,
-                                hipStream_t s);
+// FP64 transfer of an ensemble with per-mesh degrees (lt_set_mesh_degree), over
+// a count that may live on the device; asynchronous.  keys: the new leaves'
+// keys (each element's mesh, hence its degree, comes from its key), which a
+// captured cycle holds in another buffer than the tree's current one.
+lt_status launch_transfer_mixed(lt_tree_s* t, const uint64_t* keys, Count n, int nvar, const double* uo,
+                                int64_t ldo, double* un, int64_t ldn, hipStream_t s);
 
 // COPY elements of the current mapping, all `rows` point rows (nvar * n_p);
 // asynchronous.
