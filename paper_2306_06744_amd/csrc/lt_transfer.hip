@@ -254,9 +254,7 @@ __global__ __launch_bounds__(256) void k_copy_chunks(const int32_t* __restrict__
 // Copy pass (COPY elements).  One block moves one point row (variable v,
 // point i) of one chunk: 256 lanes x EPL elements.  Pure chunks read one
 // offset and move the row like a plain copy (16-byte pairs for EPL >= 2);
-// impure chunks read the map per element and move only the copy elements, one
-// block in IR taking IR rows: the map is read once for them and their loads
-// are in flight together.
+// impure chunks read the map per element and move only the copy elements.
 // SKIP: a wave leaves out its 64 elements (one interpolation group) when any
 // of them is refined or fused -- the interpolation passes then write the
 // group's copies too, so that every row segment of a group is written whole
@@ -264,13 +262,23 @@ __global__ __launch_bounds__(256) void k_copy_chunks(const int32_t* __restrict__
 // Source loads and output stores are streaming (non-temporal): every copied
 // value is touched once, and keeping it out of the caches was measured ~2.5%
 // faster for the whole transfer.
-// IR: eight rows up to 2^18 new leaves, where changed leaves make many chunks
-// impure and the arrays are mostly cached (320 rows of 117 000 leaves, two
-// thirds of them refined, nearly every chunk impure: 150 -> 119 us beside the
-// refinement); one row beyond, where nearly all chunks are pure and blocks that
-// walk distant rows disturb the streaming ones (1.9M leaves, p = 3: the cycle
-// 2034 us with one row, 2073, 2095 and 2149 with 2, 4 and 8).
-constexpr int kImpureRows = 8;
+// IR: impure chunks take IR rows (a divisor of the rows) by one block in IR,
+// reading the map once for them, their loads in flight together.  Not with
+// SKIP: there the listed groups leave few copies to an impure chunk, and the
+// FP64 transfer lost with four or eight rows on moving fronts (236 000 leaves,
+// p = 3: 212 us with one row, 222 with eight).  Without SKIP (the split
+// transfer, whose passes leave every copy between refined leaves to this one)
+// four rows up to 2^18 new leaves.  Split transfers of 5 variables, one row
+// and four: two thirds of the leaves changed, 126 000 leaves 394 -> 343 us,
+// 247 000 794 -> 727; 2% changed at random, 120 000 leaves 235 -> 179; a moving
+// front, 98 000 leaves 133 -> 131, 236 000 230 -> 237.  Beyond, moving fronts
+// lose (516 000 leaves 535 -> 544, with eight rows at 1.84M 1501 -> 1546),
+// although changes at random would still gain (503 000 leaves 870 -> 715).
+// Eight rows instead of four: 349, 757, 184, 133, 236 us.
+// The strides and the chunk's start are hidden from the optimizer where the
+// rows are moved: formed ahead of the loop, for pure chunks too, their
+// addresses took the transfer of the 236 000 leaves to 246 us (237).
+constexpr int kImpureRows = 4;
 constexpr int64_t kImpureLeaves = int64_t(1) << 18;
 
 template <int EPL, bool SKIP, int IR>
@@ -306,21 +314,20 @@ __global__ __launch_bounds__(256) void k_copy3(const int32_t* __restrict__ src,
       continue;
     }
     if (blockIdx.y % IR) continue;
-    const int rows = std::min<int>(IR, int(gridDim.y - blockIdx.y));
+    int64_t j0 = c * CH, so = ldo, sn = ldn;
+    if constexpr (IR > 1) asm volatile("" : "+s"(j0), "+s"(so), "+s"(sn));
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-      const int64_t jj = c * CH + int64_t(e) * 256 + threadIdx.x;
+      const int64_t jj = j0 + int64_t(e) * 256 + threadIdx.x;
       const int kd = jj < n ? int(kind[jj]) : 1;
       if (SKIP && __ballot(jj < n && kd != 0) != 0) continue;  // an interpolation group
       if (kd != 0) continue;
       const double* p = U + src[jj];
       double x[IR];
 #pragma unroll
-      for (int r = 0; r < IR; ++r)
-        if (r < rows) x[r] = __builtin_nontemporal_load(p + int64_t(r) * ldo);
+      for (int r = 0; r < IR; ++r) x[r] = __builtin_nontemporal_load(p + int64_t(r) * so);
 #pragma unroll
-      for (int r = 0; r < IR; ++r)
-        if (r < rows) __builtin_nontemporal_store(x[r], O + int64_t(r) * ldn + jj);
+      for (int r = 0; r < IR; ++r) __builtin_nontemporal_store(x[r], O + int64_t(r) * sn + jj);
     }
   }
 }
@@ -1127,21 +1134,16 @@ lt_status copy_pass(const TransferTune& tune, const int32_t* src, const int8_t* 
   const int64_t nlaunch =
       n.hint > 0 ? std::max<int64_t>(1, std::min(nchunks, (n.hint + n.hint / 32 + CH - 1) / CH)) : nchunks;
   const dim3 grid{unsigned(nlaunch), unsigned(rows), 1u};
-#define LT_COPY_IR(E, SKIP)                                                                       \
-  do {                                                                                          \
-    if (n.n <= kImpureLeaves)                                                                   \
-      k_copy3<E, SKIP, kImpureRows>                                                             \
-          <<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);                    \
-    else                                                                                        \
-      k_copy3<E, SKIP, 1><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);     \
-  } while (0)
 #define LT_COPY(E)                                                                              \
   do {                                                                                          \
     k_copy_chunks<E><<<unsigned(nchunks), 256, 0, s>>>(src, kind, n, copy_delta);               \
     if (skip_groups)                                                                            \
-      LT_COPY_IR(E, true);                                                                      \
+      k_copy3<E, true, 1><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);     \
+    else if (n.n <= kImpureLeaves && rows % kImpureRows == 0)                                   \
+      k_copy3<E, false, kImpureRows>                                                            \
+          <<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);                    \
     else                                                                                        \
-      LT_COPY_IR(E, false);                                                                     \
+      k_copy3<E, false, 1><<<grid, 256, 0, s>>>(src, kind, n, copy_delta, uo, ldo, un, ldn);    \
   } while (0)
   if (epl == 1)
     LT_COPY(1);
@@ -1150,7 +1152,6 @@ lt_status copy_pass(const TransferTune& tune, const int32_t* src, const int8_t* 
   else
     LT_COPY(2);
 #undef LT_COPY
-#undef LT_COPY_IR
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LT_ERR_HIP, std::string("copy pass launch: ") + hipGetErrorString(e));
   return LT_OK;

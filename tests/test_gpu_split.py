@@ -121,3 +121,27 @@ def test_captured_overflow_stays_inside_the_arrays(dim, kept):
         assert bool((f[size:] == 7.0).all())
     assert t.size() == n0 and np.array_equal(t.keys().cpu().numpy().view(np.uint64), keys0)
     del cyc
+
+
+@pytest.mark.parametrize("dim,p,depth", [(3, 3, 3), (3, 3, 4), (2, 7, 5)])
+@pytest.mark.parametrize("width", [1, 2, 4])
+def test_copies_of_small_meshes_at_every_width(dim, p, depth, width):
+    """The split transfer's copies on meshes whose impure chunks are moved
+    several rows to a workgroup, at every copy width and with a last chunk that
+    is not full: bit-exact, and nothing stored past the leaves."""
+    import torch
+    nvar, npts = 3, (p + 1) ** dim
+    g, _ = both(dim, 1, depth + 2, depth=depth)
+    g.set_tuning(width, 2048)
+    for c in range(2):
+        g.adapt(torch.from_numpy(synth.random_flags(500 + c, g.size(), 0.2, 0.4)).cuda())
+    n, n_old, _ = g.sizes()
+    u = torch.from_numpy(synth.random_solution(60 + depth, nvar, npts, n_old)).cuda()
+    out = torch.full((nvar, npts, n + 3), 7.0, dtype=torch.float64, device="cuda")
+    g.transfer(p, u, out, precision=1)
+    src, kind = g.mapping()
+    copies = torch.nonzero(kind == 0).flatten()
+    print("copies", dim, depth, width, n, len(copies), flush=True)
+    assert len(copies) and n % 256
+    assert torch.equal(out[:, :, copies], u[:, :, src[copies].long()])
+    assert bool((out[:, :, n:] == 7.0).all())
