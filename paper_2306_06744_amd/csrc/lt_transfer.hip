@@ -1071,11 +1071,6 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
           KeyGeom{}, nullptr, nullptr, kind, n, X.grp_list, &X.ctr->total, flist, &X.ctr->nfgroups);
       return LT_OK;
     };
-    const bool first = X.side && lists_first(n.n);
-    if (first) {
-      *st_out = lists(s);
-      if (*st_out != LT_OK) return e;
-    }
     if (X.side) {
       e = hipEventRecord(X.fork, s);
       if (e != hipSuccess) return e;
@@ -1083,7 +1078,7 @@ hipError_t launch(const TransferTune& tune, const double* ops, const int32_t* sr
     }
     *st_out = copy_pass(tune, src, kind, n, nvar * N * N * N, uo, ldo, un, ldn, X.copy_delta, true, s);
     if (X.side) e = hipStreamWaitEvent(X.side, X.fork, 0);
-    if (*st_out == LT_OK && e == hipSuccess && !first) *st_out = lists(si);
+    if (*st_out == LT_OK && e == hipSuccess) *st_out = lists(si);
     if (*st_out == LT_OK && e == hipSuccess) {
       const dim3 gi{unsigned(std::max<int64_t>(1, std::min<int64_t>(ngroups, tune.interp_grid))),
                     unsigned(nvar), 1u};

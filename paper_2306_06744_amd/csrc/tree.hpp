@@ -196,12 +196,15 @@ lt_status launch_mlp_flag(lt_tree_s* t, lt_mlp m, Count n, const double* u, int6
 
 lt_status launch_transfer(lt_tree_s* t, int p, const double* ops, int nvar, const double* u_old,
                           int64_t ld_old, double* u_new, int64_t ld_new, hipStream_t s);
-// Whether a transfer builds its work lists before the fork: beside the copy
-// pass their short kernels wait for wave slots, which the interpolation passes
-// then wait for.  Up to 2^18 new leaves the passes take as long as the copy
-// and the lists go first (split transfer of 117 000 leaves, two thirds of
-// them refined: 354 us against 414); beyond, the copy outlasts them all.
-inline bool lists_first(int64_t n) { return n <= int64_t(1) << 18; }
+// Whether a split transfer builds its work lists before the fork: beside the
+// copy pass their short kernels wait for wave slots, which the refinement and
+// fusion then wait for.  Lists after the fork and before it, 5 variables, inputs
+// in turn: a moving front, 50 000 leaves 112 -> 103 us, 98 000 139 -> 131,
+// 236 000 235 -> 237; 2% changed at random, 120 000 leaves 184 -> 179, 240 000
+// 324 -> 319; two thirds changed, 126 000 leaves 345 -> 343.  Beyond, the copy
+// outlasts the passes.  (The FP64 transfer, whose passes are longer, lost by it:
+// 98 000 to 247 000 leaves 305 -> 314, 212 -> 218, 426 -> 433.)
+inline bool lists_first(int64_t n) { return n <= int64_t(1) << 17; }
 // The tree's second stream for the interpolation passes of a 3D transfer and
 // its fork/join events, made on first use (default priority, non-blocking).
 lt_status transfer_side(lt_tree_s* t, hipStream_t* side, hipEvent_t* fork, hipEvent_t* join);
