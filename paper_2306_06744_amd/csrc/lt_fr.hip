@@ -685,12 +685,15 @@ constexpr int kStream = 2;  // cache-policy bit of the buffer access: streaming
 // for at the start, for every axis.  Every lane holds a whole line, so the 1D
 // operators are literal constants.
 //
-// Bound: bytes from beyond the L2.  At 1.90M p = 3 elements in 3D a step of
-// three stages takes 16.8 ms (35.2 ms with the face buffer, 22.2
-// with every neighbour's line loaded and the state read again for each axis;
-// without the lines outside the wave it would take 10.0, of which 3.4 is the
-// issue of their loads).  p = 2: 17.2 -> 8.9 ms, p = 1: 6.2 -> 2.0 ms; 2D p = 4,
-// 40 006 leaves, one residual: 71 -> 42 us.
+// Bound: the reads from beyond the L2, with two waves per SIMD (80 KB of LDS a
+// workgroup) waiting for them.  At 1.90M p = 3 elements in 3D a stage reads 17.9 GB
+// and writes 5.1 (3.7 and 1.05 times the state, of 1.67 and 1 that three stages
+// need on average) at 4.2 TB/s, vector units 38% and LDS 11% busy; a step of three
+// stages takes 16.6 ms (35.2 ms with the face buffer, 22.2 with every
+// neighbour's line loaded and the state read again for each axis; without the
+// lines outside the wave it would take 10.0, of which 3.4 is the issue of their
+// loads).  p = 2: 17.2 -> 8.9 ms, p = 1: 6.2 -> 2.0 ms; 2D p = 4, 40 006 leaves, one
+// residual: 73 -> 41 us.
 // WIDE: 64-bit addresses, for arrays whose rows of one variable pass 2^32
 // bytes.
 template <int DIM, int N, bool WIDE>

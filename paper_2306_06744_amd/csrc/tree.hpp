@@ -203,7 +203,8 @@ lt_status launch_transfer(lt_tree_s* t, int p, const double* ops, int nvar, cons
 // 236 000 235 -> 237; 2% changed at random, 120 000 leaves 184 -> 179, 240 000
 // 324 -> 319; two thirds changed, 126 000 leaves 345 -> 343.  Beyond, the copy
 // outlasts the passes.  (The FP64 transfer, whose passes are longer, lost by it:
-// 98 000 to 247 000 leaves 305 -> 314, 212 -> 218, 426 -> 433.)
+// two thirds changed, 126 000 leaves 305 -> 314; a moving front, 236 000 leaves
+// 212 -> 218.)
 inline bool lists_first(int64_t n) { return n <= int64_t(1) << 17; }
 // The tree's second stream for the interpolation passes of a 3D transfer and
 // its fork/join events, made on first use (default priority, non-blocking).
